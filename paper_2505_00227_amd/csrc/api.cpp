@@ -970,13 +970,13 @@ mdr_status mdr_recompose(mdr_dtype dtype, const void* coeffs, uint64_t n0, uint6
 
 namespace {
 
-// argument checks shared by both table entry points; nmax = the largest level
-mdr_status l2_check(const mdr_refactored* r, const mdr_level_view* levels, uint32_t nlevels, uint64_t& nmax)
+// argument checks shared by both table entry points; any = some level holds values
+mdr_status l2_check(const mdr_refactored* r, const mdr_level_view* levels, uint32_t nlevels, bool& any)
 {
     if (!r || (nlevels && !levels)) return fail(MDR_ERR_INVALID_ARG, "NULL argument");
     if (nlevels != r->levels.size()) return fail(MDR_ERR_INVALID_ARG, "level count differs from the refactored one");
     const uint64_t w = r->dtype == MDR_F64 ? 8 : 4;
-    nmax = 0;
+    any = false;
     for (uint32_t l = 0; l < nlevels; ++l) {
         if (levels[l].n != r->levels[l].n) return fail(MDR_ERR_INVALID_ARG, "level sizes differ from the refactored ones");
         if (levels[l].n == 0) continue;
@@ -985,7 +985,7 @@ mdr_status l2_check(const mdr_refactored* r, const mdr_level_view* levels, uint3
         (void)hipGetLastError();
         if (!device_range(levels[l].data, levels[l].n * w))
             return fail(MDR_ERR_INVALID_ARG, "level data must be device memory holding n values");
-        nmax = std::max(nmax, levels[l].n);
+        any = true;
     }
     return MDR_OK;
 }
@@ -993,22 +993,21 @@ mdr_status l2_check(const mdr_refactored* r, const mdr_level_view* levels, uint3
 // every level's table into `out` (nlevels * (B + 1) doubles, device) through
 // `part` (partial rows, device), then one copy to `host`; waits for the stream,
 // also when a launch fails, so that no queued kernel outlives the buffers
-mdr_status l2_run(mdr_refactored* r, const mdr_level_view* levels, uint32_t nlevels, uint64_t nmax, double* part,
+mdr_status l2_run(mdr_refactored* r, const mdr_level_view* levels, uint32_t nlevels, bool any, double* part,
                   double* out, double* host, hipStream_t s)
 {
     const uint32_t B = r->B;
     hipError_t err = hipSuccess;
     const char* what = nullptr;
     const size_t W = (size_t)B + 2;  // a level's row: the table, then the largest |x| read
-    for (uint32_t l = 0; l < nlevels && err == hipSuccess; ++l) {
-        if (levels[l].n == 0) continue;
-        // the next level reuses the partial sums: the launches stay in stream order
-        err = launch_l2_table(r->dtype == MDR_F64, levels[l].data, levels[l].n, r->levels[l].e, B, part,
-                              out + (size_t)l * W, s);
-        what = "launch_l2_table";
+    if (any) {
+        std::vector<L2Level> lv(nlevels);
+        for (uint32_t l = 0; l < nlevels; ++l) lv[l] = {levels[l].data, levels[l].n, r->levels[l].e, 0, 0, 0};
+        err = launch_l2_tables(r->dtype == MDR_F64, lv.data(), nlevels, B, part, out, s);
+        what = "launch_l2_tables";
     }
     // one copy of every level's row (a copy to pageable memory costs a staging round trip each)
-    if (err == hipSuccess && nmax) {
+    if (err == hipSuccess && any) {
         err = hipMemcpyAsync(host, out, (size_t)nlevels * W * 8, hipMemcpyDeviceToHost, s);
         what = "hipMemcpyAsync(tables)";
     }
@@ -1041,24 +1040,24 @@ extern "C" {
 mdr_status mdr_l2_table(mdr_refactored* r, const mdr_level_view* levels, uint32_t nlevels, void* stream)
 {
     g_err.clear();
-    uint64_t nmax = 0;
-    mdr_status st = l2_check(r, levels, nlevels, nmax);
+    bool any = false;
+    mdr_status st = l2_check(r, levels, nlevels, any);
     if (st) return st;
     const uint32_t B = r->B;
     MDR_HIP(hipSetDevice(r->ctx->device));
     PoolBuf part, out;
-    MDR_HIP(part.alloc(r->ctx->pool, (uint64_t)l2_table_workgroups(nmax) * (B + 2) * 8));
+    MDR_HIP(part.alloc(r->ctx->pool, (uint64_t)kL2MaxWg * (B + 2) * 8));
     MDR_HIP(out.alloc(r->ctx->pool, (uint64_t)nlevels * (B + 2) * 8));
     std::vector<double> host((size_t)nlevels * (B + 2), 0.0);
-    return l2_run(r, levels, nlevels, nmax, static_cast<double*>(part.p), static_cast<double*>(out.p), host.data(),
+    return l2_run(r, levels, nlevels, any, static_cast<double*>(part.p), static_cast<double*>(out.p), host.data(),
                   static_cast<hipStream_t>(stream));
 }
 
 mdr_status mdr_l2_table_noalloc(mdr_refactored* r, const mdr_level_view* levels, uint32_t nlevels, void* stream)
 {
     g_err.clear();
-    uint64_t nmax = 0;
-    mdr_status st = l2_check(r, levels, nlevels, nmax);
+    bool any = false;
+    mdr_status st = l2_check(r, levels, nlevels, any);
     if (st) return st;
     if (nlevels > kL2NoAllocLevels)
         return fail(MDR_ERR_UNSUPPORTED, "mdr_l2_table_noalloc takes at most " + std::to_string(kL2NoAllocLevels) +
@@ -1067,7 +1066,7 @@ mdr_status mdr_l2_table_noalloc(mdr_refactored* r, const mdr_level_view* levels,
     double *part = nullptr, *out = nullptr;
     MDR_HIP(l2_scratch(r->ctx->device, &part, &out));
     double host[kL2NoAllocLevels * kL2RowMax];  // nlevels * (B + 2) <= 64 * 66
-    return l2_run(r, levels, nlevels, nmax, part, out, host, static_cast<hipStream_t>(stream));
+    return l2_run(r, levels, nlevels, any, part, out, host, static_cast<hipStream_t>(stream));
 }
 
 mdr_status mdr_refactored_l2(const mdr_refactored* r, uint32_t level, double* E2)

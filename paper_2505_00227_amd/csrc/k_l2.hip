@@ -4,12 +4,11 @@
 // xhat_k(a) = floor(a 2^(k-e)) 2^(e-k), the magnitude the retrieval rebuilds
 // from k planes of the level aligned to exponent e.  Every residual is exact
 // in fp64 (it is a run of the value's own significand bits); each square is
-// rounded once and the sums run in fp64 in a fixed order (per thread, then a
-// fixed tree per workgroup, then workgroups in index order), so the table is
-// the same on every run.
+// added with one rounding and the sums run in fp64 in a fixed order (per
+// thread, then a fixed tree per workgroup, then workgroups in a fixed order),
+// so the table is the same on every run.
 #include <hip/hip_runtime.h>
 
-#include <cmath>
 #include <cstdint>
 #include <mutex>
 
@@ -20,35 +19,63 @@ namespace {
 
 constexpr uint32_t kL2 = 256;  // threads per workgroup
 
-// table entries KLO..KHI (and <= B) of every workgroup's partial row (B + 2
-// entries: E2[0..B], then the largest |x| the workgroup read, written by the
-// KLO = 0 launch); f64 tables run as two launches so that a thread holds at
-// most 33 accumulators
-template <typename T, int KLO, int KHI>
-__global__ __launch_bounds__(kL2) void k_l2_partial(const T* __restrict__ x, uint64_t n, int e, uint32_t B,
+// One launch covers up to kL2LaunchLevels levels, passed by value.
+struct L2Args {
+    L2Level lv[kL2LaunchLevels];
+};
+
+// Partial rows of every workgroup (B + 2 entries: E2[0..B], then the largest
+// |x| the workgroup read).
+//
+// A value's residual after k planes, in units of 2^(e-k), is fract(z 2^k) with
+// z = |x| 2^-e in [0, 1): exact (z's significand bits below the cut), so an
+// entry costs a scaling, a fract and a fused multiply-add into its accumulator,
+// and the accumulators are scaled back by 2^(2(e-k)) once per workgroup.  (A
+// floor and two scalings per entry, unfused, were six operations: the f32
+// launches of a 512^3 field took 1.34 ms, this one 0.50.)  The bound is fp64
+// issue, three operations of about 4.8 cycles a wavefront and entry.  Values
+// with z < 2^-400, whose scaled squares could underflow, lie below every cut:
+// their residual is |x| itself and they are summed unscaled.
+// KN: accumulators a thread holds, the first of 17, 33, 65 that covers B + 1
+// entries (entries past B are computed and dropped).
+template <typename T, int KN>
+__global__ __launch_bounds__(kL2) void k_l2_partial(const L2Args A, uint32_t nlev, uint32_t B,
                                                     double* __restrict__ part)
 {
-#pragma clang fp contract(off)
-    constexpr int KN = KHI - KLO + 1;
-    __shared__ double red[kL2 / 64][KN];
-    __shared__ double s_amax[kL2 / 64];
+    __shared__ double red[kL2 / 64][KN + 2];  // entries, sum of tiny values' squares, max |x|
+    uint32_t l = 0;
+    while (l + 1 < nlev && blockIdx.x >= A.lv[l + 1].wg_base) ++l;
+    const T* __restrict__ x = static_cast<const T*>(A.lv[l].x);
+    const uint64_t n = A.lv[l].n;
+    const int e = A.lv[l].e;
     double acc[KN];
 #pragma unroll
     for (int j = 0; j < KN; ++j) acc[j] = 0.0;
-    double amax = 0.0;
-    const uint64_t stride = (uint64_t)gridDim.x * kL2;
-    for (uint64_t i = (uint64_t)blockIdx.x * kL2 + threadIdx.x; i < n; i += stride) {
-        const double a = std::fabs((double)x[i]);
-        if (KLO == 0) amax = a > amax ? a : amax;
+    double amax = 0.0, tiny = 0.0;
+    const uint64_t stride = (uint64_t)A.lv[l].nwg * kL2;
+    auto add = [&](T xv) {
+        const double a = __builtin_fabs((double)xv);
+        amax = __builtin_fmax(amax, a);
+        double z = __builtin_amdgcn_ldexp(a, -e);
+        const bool low = z < 0x1p-400;
+        const double t = low ? a : 0.0;
+        z = low ? 0.0 : z;
+        asm volatile("" : "+v"(z));  // select once: the compiler would move it past every entry's scaling
+        tiny = __builtin_fma(t, t, tiny);
 #pragma unroll
-        for (int j = 0; j < KN; ++j) {
-            const int k = KLO + j;
-            if (k <= (int)B) {
-                // exact power-of-two scalings (a scaled value below 1 may round, its floor is 0 either way)
-                const double r = a - std::ldexp(std::floor(std::ldexp(a, k - e)), e - k);
-                acc[j] += r * r;
-            }
+        for (int k = 0; k < KN; ++k) {
+            const double y = __builtin_amdgcn_fract(__builtin_amdgcn_ldexp(z, k));
+            acc[k] = __builtin_fma(y, y, acc[k]);
         }
+    };
+    uint64_t i = (uint64_t)(blockIdx.x - A.lv[l].wg_base) * kL2 + threadIdx.x;
+    // the next value is loaded while this one's entries are summed
+    T next = i < n ? x[i] : T(0);
+    while (i < n) {
+        const T cur = next;
+        i += stride;
+        if (i < n) next = x[i];
+        add(cur);
     }
     const uint32_t lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
@@ -58,50 +85,71 @@ __global__ __launch_bounds__(kL2) void k_l2_partial(const T* __restrict__ x, uin
         for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o, 64);
         if (lane == 0) red[wave][j] = v;
     }
-    if (KLO == 0) {
 #pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {
-            const double v = __shfl_xor(amax, o, 64);
-            amax = v > amax ? v : amax;
-        }
-        if (lane == 0) s_amax[wave] = amax;
+    for (int o = 32; o >= 1; o >>= 1) {
+        tiny += __shfl_xor(tiny, o, 64);
+        amax = __builtin_fmax(amax, __shfl_xor(amax, o, 64));
+    }
+    if (lane == 0) {
+        red[wave][KN] = tiny;
+        red[wave][KN + 1] = amax;
     }
     __syncthreads();
-    const uint32_t k = KLO + threadIdx.x;
-    if (threadIdx.x < (uint32_t)KN && k <= B) {
-        double v = 0.0;
+    const uint32_t k = threadIdx.x;
+    double* row = part + (uint64_t)blockIdx.x * (B + 2);
+    if (k <= B) {
+        double v = 0.0, t = 0.0;
 #pragma unroll
-        for (uint32_t w = 0; w < kL2 / 64; ++w) v += red[w][threadIdx.x];
-        part[(uint64_t)blockIdx.x * (B + 2) + k] = v;
-    }
-    if (KLO == 0 && threadIdx.x == 0) {
+        for (uint32_t w = 0; w < kL2 / 64; ++w) {
+            v += red[w][k];
+            t += red[w][KN];
+        }
+        row[k] = __builtin_amdgcn_ldexp(v, 2 * (e - (int)k)) + t;
+    } else if (k == B + 1) {
         double m = 0.0;
-        for (uint32_t w = 0; w < kL2 / 64; ++w) m = s_amax[w] > m ? s_amax[w] : m;
-        part[(uint64_t)blockIdx.x * (B + 2) + B + 1] = m;
+        for (uint32_t w = 0; w < kL2 / 64; ++w) m = __builtin_fmax(m, red[w][KN + 1]);
+        row[k] = m;
     }
 }
 
-// out[0..B]: the table (workgroup rows summed in index order); out[B + 1]: the
-// largest |x| read, which the caller checks against the refactored level's
-__global__ void k_l2_final(const double* __restrict__ part, uint32_t nwg, uint32_t B, double* __restrict__ out)
+// out[l][0..B]: the tables; out[l][B + 1]: the largest |x| read, which the
+// caller checks against the refactored level's.  A workgroup per level: wave w
+// adds the level's rows w, w + 16, ... in order (lanes over the entries), then
+// the 16 waves' sums are added in order.  (One thread an entry over all the
+// rows took 87 us a level, a chain of a thousand loads.)
+constexpr uint32_t kL2Final = 1024;
+__global__ __launch_bounds__(kL2Final) void k_l2_final(const L2Args A, uint32_t B, const double* __restrict__ part,
+                                                       double* __restrict__ out)
 {
-    const uint32_t k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k > B + 1) return;
-    double v = 0.0;
-    for (uint32_t w = 0; w < nwg; ++w) {
-        const double p = part[(uint64_t)w * (B + 2) + k];
-        v = k <= B ? v + p : (p > v ? p : v);
+    __shared__ double red[kL2Final / 64][kL2RowMax];
+    const uint32_t l = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    if (A.lv[l].n == 0) return;  // its row is not read
+    const uint32_t nwg = A.lv[l].nwg;
+    const double* p = part + (uint64_t)A.lv[l].wg_base * (B + 2);
+    for (uint32_t k = lane; k < B + 2; k += 64) {
+        double v = 0.0;
+#pragma unroll 4
+        for (uint32_t w = wave; w < nwg; w += kL2Final / 64) {
+            const double q = p[(uint64_t)w * (B + 2) + k];
+            v = k <= B ? v + q : __builtin_fmax(v, q);
+        }
+        red[wave][k] = v;
     }
-    out[k] = v;
+    __syncthreads();
+    for (uint32_t k = threadIdx.x; k < B + 2; k += kL2Final) {
+        double v = 0.0;
+        for (uint32_t w = 0; w < kL2Final / 64; ++w) v = k <= B ? v + red[w][k] : __builtin_fmax(v, red[w][k]);
+        out[(uint64_t)A.lv[l].row * (B + 2) + k] = v;
+    }
 }
 
-// Fixed scratch of mdr_l2_table_noalloc: the partial rows of at most 1024
+// Fixed scratch of mdr_l2_table_noalloc: the partial rows of at most kL2MaxWg
 // workgroups, then the rows of at most kL2NoAllocLevels levels, kL2RowMax
 // entries (B + 2 for B <= 64) each: 574,464 bytes per device, held until the
 // process ends.  Host code never passes this name to a kernel: it is a
 // host-side stand-in; the device address comes from hipGetSymbolAddress, per
 // device.
-constexpr uint64_t kL2PartDoubles = 1024ull * kL2RowMax;
+constexpr uint64_t kL2PartDoubles = (uint64_t)kL2MaxWg * kL2RowMax;
 constexpr uint64_t kL2ScratchDoubles = kL2PartDoubles + (uint64_t)kL2NoAllocLevels * kL2RowMax;
 __device__ __align__(256) double scratch[kL2ScratchDoubles];
 
@@ -145,30 +193,66 @@ hipError_t l2_scratch(int device, double** part, double** out)
     return hipSuccess;
 }
 
-uint32_t l2_table_workgroups(uint64_t n)
+// Workgroups of a launch's levels: in proportion to their values, at least 8
+// values a thread, at most kL2MaxWg in all (every workgroup resident at once: a
+// level's share ends when the others do).  A 65-entry table's accumulators
+// leave room for three workgroups a CU instead of four.
+static uint32_t plan_workgroups(L2Args& A, uint32_t cnt, uint32_t B)
 {
-    const uint64_t w = (n + kL2 * 8 - 1) / (kL2 * 8);
-    return (uint32_t)(w < 1 ? 1 : (w > 1024 ? 1024 : w));
+    const uint64_t most = B > 32 ? kL2MaxWg * 3 / 4 : kL2MaxWg;
+    uint64_t total = 0;
+    for (uint32_t l = 0; l < cnt; ++l) total += A.lv[l].n;
+    uint32_t base = 0;
+    for (uint32_t l = 0; l < cnt; ++l) {
+        L2Level& v = A.lv[l];
+        v.wg_base = base;
+        v.nwg = 0;
+        if (v.n) {
+            const uint64_t share = 1 + (uint64_t)((double)(most - cnt) * ((double)v.n / (double)total));
+            const uint64_t useful = (v.n + kL2 * 8 - 1) / (kL2 * 8);
+            v.nwg = (uint32_t)(share < useful ? share : useful);
+        }
+        base += v.nwg;
+    }
+    return base;
 }
 
-hipError_t launch_l2_table(bool f64, const void* x, uint64_t n, int e, uint32_t B, double* part, double* out,
-                           hipStream_t s)
+template <typename T, int KN>
+static hipError_t launch_tables(const L2Args& A, uint32_t cnt, uint32_t nwg, uint32_t B, double* part, double* out,
+                                hipStream_t s)
 {
-    const uint32_t nwg = l2_table_workgroups(n);
-    if (f64) {
-        hipLaunchKernelGGL((k_l2_partial<double, 0, 32>), dim3(nwg), dim3(kL2), 0, s, static_cast<const double*>(x),
-                           n, e, B, part);
-        if (B > 32)
-            hipLaunchKernelGGL((k_l2_partial<double, 33, 64>), dim3(nwg), dim3(kL2), 0, s,
-                               static_cast<const double*>(x), n, e, B, part);
-    } else {
-        hipLaunchKernelGGL((k_l2_partial<float, 0, 32>), dim3(nwg), dim3(kL2), 0, s, static_cast<const float*>(x), n,
-                           e, B, part);
-    }
-    hipError_t err = hipGetLastError();
+    hipLaunchKernelGGL((k_l2_partial<T, KN>), dim3(nwg), dim3(kL2), 0, s, A, cnt, B, part);
+    const hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    hipLaunchKernelGGL(k_l2_final, dim3(1), dim3(128), 0, s, part, nwg, B, out);  // B + 2 <= 66 entries
+    hipLaunchKernelGGL(k_l2_final, dim3(cnt), dim3(kL2Final), 0, s, A, B, part, out);
     return hipGetLastError();
+}
+
+hipError_t launch_l2_tables(bool f64, const L2Level* levels, uint32_t nlevels, uint32_t B, double* part, double* out,
+                            hipStream_t s)
+{
+    // empty levels have no workgroups (their rows are not written)
+    L2Args A;
+    uint32_t cnt = 0;
+    hipError_t err = hipSuccess;
+    for (uint32_t l = 0; l < nlevels && err == hipSuccess; ++l) {
+        if (levels[l].n) {
+            A.lv[cnt] = levels[l];
+            A.lv[cnt++].row = l;
+        }
+        if (cnt == 0 || (cnt < kL2LaunchLevels && l + 1 < nlevels)) continue;
+        // the next launch reuses the partial rows: launches stay in stream order
+        const uint32_t nwg = plan_workgroups(A, cnt, B);
+        if (f64)
+            err = B < 17 ? launch_tables<double, 17>(A, cnt, nwg, B, part, out, s)
+                  : B < 33 ? launch_tables<double, 33>(A, cnt, nwg, B, part, out, s)
+                           : launch_tables<double, 65>(A, cnt, nwg, B, part, out, s);
+        else
+            err = B < 17 ? launch_tables<float, 17>(A, cnt, nwg, B, part, out, s)
+                         : launch_tables<float, 33>(A, cnt, nwg, B, part, out, s);
+        cnt = 0;
+    }
+    return err;
 }
 
 }  // namespace mdr

@@ -245,11 +245,21 @@ constexpr uint32_t kL2RowMax = 66;  // a level's L2 row: E2[0..B] and the larges
 constexpr uint32_t kL2NoAllocLevels = 64;
 hipError_t l2_scratch_init(int device);
 hipError_t l2_scratch(int device, double** part, double** out);
-// part: l2_table_workgroups(n) * (B + 2) doubles; out: B + 2 doubles (the table, then the
-// largest |x| read); B <= 32 for f32, <= 64 for f64
-uint32_t l2_table_workgroups(uint64_t n);
-hipError_t launch_l2_table(bool f64, const void* x, uint64_t n, int e, uint32_t B, double* part, double* out,
-                           hipStream_t s);
+// one level of a table launch: values, exponent, its workgroups in the launch,
+// and its row of the output
+struct L2Level {
+    const void* x;
+    uint64_t n;
+    int32_t e;
+    uint32_t wg_base, nwg, row;  // set by the launcher
+};
+constexpr uint32_t kL2LaunchLevels = 64;  // levels of one launch (passed by value)
+constexpr uint32_t kL2MaxWg = 1024;       // workgroups of one launch, at most
+// part: kL2MaxWg * (B + 2) doubles; out: nlevels rows of B + 2 doubles (the
+// table, then the largest |x| read; an empty level's row is not written);
+// B <= 32 for f32, <= 64 for f64
+hipError_t launch_l2_tables(bool f64, const L2Level* levels, uint32_t nlevels, uint32_t B, double* part, double* out,
+                            hipStream_t s);
 
 // ---- multilevel decomposition (k_multilevel.hip): field <-> coefficient levels
 constexpr uint32_t kMlMaxSteps = 30;
