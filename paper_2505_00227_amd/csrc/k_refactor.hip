@@ -854,29 +854,282 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
 }
 
 // ------------------------------------------------------------------ hybrid selection
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, int l)
+{
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, l);
+}
+__device__ __forceinline__ uint64_t lane_value(uint64_t v, int l)
+{
+    return ((uint64_t)lane_value((uint32_t)(v >> 32), l) << 32) | lane_value((uint32_t)v, l);
+}
+
+// orders LDS traffic between the lanes of one wavefront
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Working memory of one code construction (one wavefront).  W: the weights'
+// type, 32 bits while a unit has fewer than 2^30 bytes.
+template <typename W>
+struct CodeScratch {
+    W w[512];            // node weights: leaves [0, nl) ascending, merged nodes from nl
+    W ow[128];           // a round's nodes in merged order: weights
+    uint32_t ord[128];   // ... and node numbers
+    uint32_t par[512];   // parent of every node; then depth << 16 | ancestor of merged nodes
+    uint32_t bits[256];  // codes per length
+};
+
+// Code lengths of the nl >= 2 symbols sym[0, nl) (ascending (count, symbol)
+// order, weights in cs.w): the two-queue Huffman tree, leaf queue first on
+// weight ties, then the count adjustment of ITU-T T.81 Annex K when it is
+// deeper than lmax.  Runs on one wavefront; returns the longest length.
+//
+// The tree is built in rounds instead of one merge at a time: with t the sum
+// of the two smallest nodes, every node of weight <= t goes before any node
+// that is yet to be made (a new node weighs at least t, and on a tie leaves
+// and older nodes go first), so all of them pair up at once in merged order; an
+// odd last one waits for the next round.  A round looks at the first 64 of
+// each queue; what lies past a full window bounds what the other may give.
+// Serial merging on one lane, with its dependent LDS picks, was most of a
+// selection launch: 71 us for the 45 units of a 32768-value variable.
+template <typename W>
+__device__ __forceinline__ uint32_t huf_lengths(CodeScratch<W>& cs, const uint32_t* sym, int nl, uint32_t lmax, uint8_t* len, uint32_t lane)
+{
+    constexpr W kNone = ~W(0) >> 1;   // above any weight; the sum of two does not wrap
+    int q1 = 0, q2 = nl, next = nl;  // heads of the leaf and merged queues, end of the latter
+    while ((nl - q1) + (next - q2) > 1) {
+        const int nlf = nl - q1, nin = next - q2;
+        const W wl = (int)lane < nlf ? cs.w[q1 + lane] : kNone;
+        const W wi = (int)lane < nin ? cs.w[q2 + lane] : kNone;
+        const W l0 = lane_value(wl, 0), l1 = lane_value(wl, 1);
+        const W i0 = lane_value(wi, 0), i1 = lane_value(wi, 1);
+        W t = l0 + l1;
+        t = l0 + i0 < t ? l0 + i0 : t;
+        t = i0 + i1 < t ? i0 + i1 : t;
+        // a window that is full to its end (more nodes <= t may follow): leaves
+        // past it go before merged nodes of at least their weight, merged nodes
+        // past it before leaves of more than theirs
+        const W lw = lane_value(wl, 63), iw = lane_value(wi, 63);
+        const bool sat_l = nlf > 64 && lw <= t, sat_i = nin > 64 && iw <= t;
+        const bool in_l = wl <= t && (!sat_i || wl <= iw);
+        const bool in_i = wi <= t && (!sat_l || wi < lw);
+        const int cl = __popcll(__ballot(in_l)), ci = __popcll(__ballot(in_i));
+        if (cl + ci <= 3) {  // a single merge, of the two smallest: leaves first on a tie
+            const int leaves = l0 <= i0 ? (l1 <= i0 ? 2 : 1) : (l0 <= i1 ? 1 : 0);
+            if (lane < 2) cs.par[(int)lane < leaves ? q1 + (int)lane : q2 + (int)lane - leaves] = (uint32_t)next;
+            if (lane == 2) cs.w[next] = t;
+            q1 += leaves;
+            q2 += 2 - leaves;
+            ++next;
+            wave_fence();
+            continue;
+        }
+        // positions in merged order, by a walk over the shorter side
+        int pl = (int)lane, pi = (int)lane;
+        if (ci <= cl) {
+            for (int j = 0; j < ci; ++j) {
+                const W v = lane_value(wi, j);
+                const int before = __popcll(__ballot(in_l && wl <= v));
+                pl += v < wl ? 1 : 0;
+                pi = (int)lane == j ? j + before : pi;
+            }
+        } else {
+            for (int j = 0; j < cl; ++j) {
+                const W v = lane_value(wl, j);
+                const int before = __popcll(__ballot(in_i && wi < v));
+                pi += v <= wi ? 1 : 0;
+                pl = (int)lane == j ? j + before : pl;
+            }
+        }
+        if (in_l) {
+            cs.ord[pl] = (uint32_t)(q1 + (int)lane);
+            cs.ow[pl] = wl;
+        }
+        if (in_i) {
+            cs.ord[pi] = (uint32_t)(q2 + (int)lane);
+            cs.ow[pi] = wi;
+        }
+        wave_fence();
+        const int P = cl + ci, np = P >> 1;
+        if ((int)lane < np) {
+            // all four reads before the writes: one LDS round trip
+            const uint32_t node = (uint32_t)(next + (int)lane), na = cs.ord[2 * lane], nb = cs.ord[2 * lane + 1];
+            const W wa = cs.ow[2 * lane], wb = cs.ow[2 * lane + 1];
+            cs.w[node] = wa + wb;
+            cs.par[na] = node;
+            cs.par[nb] = node;
+        }
+        const bool odd_leaf = cl > 0 && __builtin_amdgcn_readlane(pl, cl - 1) == P - 1;
+        q1 += cl - ((P & 1) && odd_leaf ? 1 : 0);
+        q2 += ci - ((P & 1) && !odd_leaf ? 1 : 0);
+        next += np;
+        wave_fence();
+    }
+
+    // depths of the merged nodes (numbers nl .. 2 nl - 2, the last the root) by
+    // pointer jumping, four nodes a lane; then each leaf's is its parent's plus one
+    const uint32_t root = (uint32_t)(2 * nl - 2);
+    uint32_t dp[4], lp[4];
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        const uint32_t leaf = lane + 64 * h, v = (uint32_t)nl + leaf;
+        lp[h] = (int)leaf < nl ? cs.par[leaf] : 0u;
+        dp[h] = v < root ? (1u << 16) | cs.par[v] : root;  // depth so far << 16 | ancestor at that distance
+    }
+    wave_fence();
+    for (;;) {
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            const uint32_t v = (uint32_t)nl + lane + 64 * h;
+            if (v <= root) cs.par[v] = dp[h];
+        }
+        wave_fence();
+        bool open = false;
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            const uint32_t v = (uint32_t)nl + lane + 64 * h;
+            open = open || (v < root && (dp[h] & 0xFFFFu) != root);
+        }
+        if (__ballot(open) == 0) break;
+#pragma unroll
+        for (int h = 0; h < 4; ++h) {
+            const uint32_t a = cs.par[dp[h] & 0xFFFFu];
+            dp[h] = (dp[h] & 0xFFFF0000u) + a;
+        }
+        wave_fence();  // everyone has read before the next round writes
+    }
+    uint32_t d[4], most = 0;
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        const uint32_t leaf = lane + 64 * h;
+        d[h] = (int)leaf < nl ? (cs.par[lp[h]] >> 16) + 1 : 0u;
+        most = d[h] > most ? d[h] : most;
+    }
+    most = wave_max(most);
+    if (most > lmax) {
+#pragma unroll
+        for (int h = 0; h < 4; ++h) cs.bits[lane + 64 * h] = 0;
+        wave_fence();
+#pragma unroll
+        for (int h = 0; h < 4; ++h)
+            if (d[h]) atomicAdd(&cs.bits[d[h]], 1u);
+        wave_fence();
+        if (most >= 64) {
+            // deeper than a wavefront has lanes (counts past 2^40): one lane
+            if (lane == 0) {
+                for (uint32_t i = most; i > lmax; --i) {
+                    while (cs.bits[i] > 0) {
+                        uint32_t j = i - 2;
+                        while (cs.bits[j] == 0) --j;
+                        cs.bits[i] -= 2;
+                        cs.bits[i - 1] += 1;
+                        cs.bits[j + 1] += 2;
+                        cs.bits[j] -= 1;
+                    }
+                }
+            }
+            wave_fence();
+        }
+        // lane l holds the count of length l
+        int b = (int)cs.bits[lane];
+        if (most < 64) {
+            // Per step, two codes of the deepest length i: one moves up to i - 1,
+            // the other to a code split at the longest shorter length j <= i - 2
+            // that has one (j -> two of j + 1).  Splitting one code of length j
+            // all the way down to i - 1, as consecutive steps do, takes
+            // T = 2^(i-1-j) - 1 steps and leaves 2^(i-1-j) codes there, so
+            // codes are split whole while the steps last; of the next one the
+            // steps left split a path (at each length one code stays, or is
+            // split whole).  (One step at a time was up to 50 us of a large
+            // skewed unit's selection.)
+            const int l = (int)lane;
+            for (int i = (int)most; i > (int)lmax; --i) {
+                int left = __builtin_amdgcn_readlane(b, i) >> 1;  // steps at this length, at most 127
+                b += (l == i ? -2 * left : 0) + (l == i - 1 ? left : 0);
+                while (left > 0) {
+                    const unsigned long long nzm = __ballot(b != 0) & ((1ull << (i - 1)) - 1);
+                    if (!nzm) break;  // cannot happen for a full tree
+                    const int j = 63 - __clzll((long long)nzm);
+                    int d = i - 1 - j, T = (1 << min(d, 16)) - 1;  // 16 levels stand for more: T > left
+                    const int bj = __builtin_amdgcn_readlane(b, j);
+                    // left / T, exact for these small numbers
+                    int q = (int)((float)left * __builtin_amdgcn_rcpf((float)T) + 1e-3f);
+                    q = min(__builtin_amdgcn_readfirstlane(q), bj);
+                    left -= q * T;
+                    int deep = q << min(d, 16);       // codes left at i - 1
+                    unsigned long long stay = 0;      // lengths that keep one code of the split path
+                    if (q < bj && left > 0) {
+                        ++q;                          // the partly split code
+                        for (int c = j; left > 0;) {
+                            --left;                   // split: two of length c + 1
+                            ++c;
+                            --d;
+                            T = (1 << min(d, 16)) - 1;
+                            if (left >= T) {          // one of them whole (T = 0 at c = i - 1)
+                                left -= T;
+                                deep += 1 << d;
+                            } else {
+                                stay |= 1ull << c;
+                            }
+                            if (left == 0) {          // the other stays as it is
+                                if (d == 0)
+                                    ++deep;
+                                else
+                                    b += l == c ? 1 : 0;
+                            }
+                        }
+                    }
+                    b += (l == j ? -q : 0) + (l == i - 1 ? deep : 0) + (int)((stay >> l) & 1);
+                }
+            }
+        }
+        // hand the lengths out again, the heaviest leaf (last) the shortest
+        uint32_t cum = 0, nd[4] = {1, 1, 1, 1};
+        for (uint32_t L = 1; L < lmax; ++L) {
+            cum += (uint32_t)__builtin_amdgcn_readlane(b, (int)L);
+#pragma unroll
+            for (int h = 0; h < 4; ++h) nd[h] += (uint32_t)(nl - 1) - (lane + 64 * h) >= cum ? 1u : 0u;
+        }
+#pragma unroll
+        for (int h = 0; h < 4; ++h) d[h] = nd[h];
+        most = lmax;
+    }
+#pragma unroll
+    for (int h = 0; h < 4; ++h) {
+        const uint32_t leaf = lane + 64 * h;
+        if ((int)leaf < nl) len[sym[leaf]] = (uint8_t)d[h];
+    }
+    return most;
+}
+
 // One workgroup of NT threads per (unit, level) (Alg. 2): gather the byte
 // histogram and the run count, build length-limited Huffman code lengths with
 // the two-queue construction, canonical codes, both size estimates, and the
-// method decision.  Units that Alg. 2 can only copy (S <= T_s) skip the codebook.
-// NT = 256, 512 or 1024 threads (a launch knob): the tree is built on one
-// lane, so smaller workgroups let more units build theirs at once (a batch of
-// many variables has thousands; 1024 threads made such a batch's selection 3x
-// slower than 512), while the histogram and rank steps of a few large units
-// go faster with more threads (256 made a single field's 20 % slower).
-template <int NT>
-__global__ __launch_bounds__(NT) void k_select(const SelectParams job,
-                                                         const SelectLevel* __restrict__ levels)
+// method decision.  Units that Alg. 2 can only copy (S <= T_s) skip the
+// codebook, and so do units whose entropy already rules Huffman out: every
+// prefix code takes at least the entropy, so when that (less a margin far above
+// its rounding) plus the stream's overhead fails Alg. 2's test, the code's own
+// estimate fails it too, and nothing else reads the code.
+// NT = 256, 512 or 1024 threads (a launch knob): the code is built by one
+// wavefront, so smaller workgroups let more units build theirs at once, while
+// the boundary and rank steps of a few large units go faster with more threads.
+template <int NT, typename W>
+__global__ __launch_bounds__(NT) void k_select(const SelectParams job, const SelectLevel* __restrict__ levels)
 {
-    __shared__ unsigned long long s_f[256];     // working counts (halved when limiting)
-    __shared__ unsigned long long s_f0[256];    // original counts
-    __shared__ unsigned long long s_w[512];
-    __shared__ int s_parent[512];
-    __shared__ int s_sorted[256];
-    __shared__ int s_dp[1024];  // depths and parents while measuring the tree
+    constexpr uint32_t kWaves = NT / 64;
+    __shared__ __align__(16) unsigned long long s_key[256];  // count << 8 | symbol, ~0 when absent
+    __shared__ CodeScratch<W> s_cs;
+    __shared__ uint32_t s_rank[256];
+    __shared__ uint32_t s_sorted[256];
     __shared__ uint8_t s_len[256];
-    __shared__ unsigned long long s_red[NT / 64];
-    __shared__ int s_nl, s_maxlen;
-    __shared__ uint32_t s_count[33], s_first[33];
+    __shared__ unsigned long long s_red[kWaves], s_red2[kWaves];
+    __shared__ unsigned long long s_bits[4];
+    __shared__ double s_redf[4];
+    __shared__ uint32_t s_cnt[4][kLutBitsMax + 1];
+    __shared__ uint32_t s_maxlen;
 
     const SelectLevel& lv = levels[blockIdx.y];
     const uint32_t u = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -906,281 +1159,194 @@ __global__ __launch_bounds__(NT) void k_select(const SelectParams job,
         return;
     }
 
-    auto block_sum = [&](unsigned long long v) -> unsigned long long {
+    auto wave_sum64 = [](unsigned long long v) {
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-        if (lane == 0) s_red[wave] = v;
-        __syncthreads();
-        unsigned long long t = 0;
-        for (int w = 0; w < NT / 64; ++w) t += s_red[w];
-        __syncthreads();
-        return t;
+        return v;
     };
 
     // ---- byte histogram (level totals from the encoder)
-    unsigned long long f = tid < 256 ? lv.hist[(uint64_t)u * 256 + tid] : 0;
-    unsigned long long nz = block_sum((tid > 0 && tid < 256) ? f : 0);
-    if (tid == 0) f = S - nz;  // zero bytes are not counted by the encoder
-    if (tid < 256) {
-        s_f[tid] = f;
-        s_f0[tid] = f;
-    }
+    unsigned long long f = tid < 256 ? gmem(lv.hist)[(uint64_t)u * 256 + tid] : 0;
 
     // ---- runs of equal W-bit words: transitions inside workgroup ranges (level
     // totals from the encoder), at range boundaries, and between consecutive
     // planes of the group
     const uint32_t nrow = r1 - r0;
-    unsigned long long tr = tid < nrow ? lv.trans[r0 + tid] : 0;
+    unsigned long long tr = 0;
+    for (uint32_t i = tid; i < nrow; i += NT) tr += gmem(lv.trans)[r0 + i];
     {
         // boundary i: first word(s) of range w = 1 + i / nrow against the last
-        // of range w - 1, row r0 + i % nrow; four boundaries per thread in flight
+        // of range w - 1, row r0 + i % nrow, eight boundaries a thread in
+        // flight; a record holds a row's first and last word (G = 1), or its
+        // first two and last two, in 8-byte pieces
+        constexpr int kFly = 8;
         const auto recs = gmem(lv.recs);
+        const auto pieces = gmem(reinterpret_cast<const uint64_t*>(lv.recs));
         const uint32_t nbnd = (grid - 1) * nrow;
-        for (uint32_t i0 = tid; i0 < nbnd; i0 += 4 * NT) {
-            uint32_t cw[4][2], pw[4][2];
+        // i / nrow by a multiplication: exact while i * nrow < 2^32, and
+        // i < 65536 * 65 (encoder workgroups of a level, rows)
+        const uint32_t inv = 0xFFFFFFFFu / nrow + 1;
+        for (uint32_t i0 = tid; i0 < nbnd; i0 += kFly * NT) {
+            uint64_t cw[kFly], pw[kFly];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
+            for (int k = 0; k < kFly; ++k) {
                 const uint32_t i = min(i0 + k * NT, nbnd - 1);
-                const uint32_t w = 1 + i / nrow, r = r0 + i % nrow;
-                const uint64_t cur = ((uint64_t)w * kMaxRows + r) * 2 * G;
-                const uint64_t prv = ((uint64_t)(w - 1) * kMaxRows + r) * 2 * G;
-#pragma unroll
-                for (int g = 0; g < 2; ++g) {
-                    cw[k][g] = g < (int)G ? recs[cur + g] : 0u;
-                    pw[k][g] = g < (int)G ? recs[prv + G + g] : 0u;
-                }
+                const uint32_t w = nrow == 1 ? i : __umulhi(i, inv), r = r0 + i - w * nrow;  // range w + 1
+                cw[k] = pieces[((uint64_t)(w + 1) * kMaxRows + r) * G];
+                pw[k] = pieces[((uint64_t)w * kMaxRows + r) * G + G - 1];
             }
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (i0 + k * NT < nbnd) tr += (cw[k][0] != pw[k][0] || cw[k][1] != pw[k][1]) ? 1 : 0;
+            for (int k = 0; k < kFly; ++k) {
+                const bool ne = G == 1 ? (uint32_t)cw[k] != (uint32_t)(pw[k] >> 32) : cw[k] != pw[k];
+                tr += i0 + k * NT < nbnd && ne ? 1u : 0u;
+            }
+        }
+        for (uint32_t r = r0 + 1 + tid; r < r1; r += NT) {
+            const uint64_t cur = (uint64_t)r * 2 * G;
+            const uint64_t prv = ((uint64_t)(grid - 1) * kMaxRows + (r - 1)) * 2 * G;
+            bool ne = false;
+            for (uint32_t g = 0; g < G; ++g) ne = ne || recs[cur + g] != recs[prv + G + g];
+            tr += ne ? 1 : 0;
         }
     }
-    for (uint32_t r = r0 + 1 + tid; r < r1; r += NT) {
-        const uint32_t* cur = lv.recs + ((uint64_t)0 * kMaxRows + r) * 2 * G;
-        const uint32_t* prv = lv.recs + ((uint64_t)(grid - 1) * kMaxRows + (r - 1)) * 2 * G;
-        bool ne = false;
-        for (uint32_t g = 0; g < G; ++g) ne = ne || cur[g] != prv[G + g];
-        tr += ne ? 1 : 0;
+    {
+        const unsigned long long nzw = wave_sum64(tid > 0 && tid < 256 ? f : 0);
+        const unsigned long long trw = wave_sum64(tr);
+        if (lane == 0) {
+            s_red[wave] = nzw;
+            s_red2[wave] = trw;
+        }
+        if (tid < 256) {
+            s_rank[tid] = 0;
+            s_len[tid] = 0;
+        }
+        if (tid == 0) s_maxlen = 0;
     }
-    const unsigned long long trans = block_sum(tr);
-    const unsigned long long nruns = S ? 1 + trans : 0;
-
-    const bool need_code = job.force_method == 2 || (job.force_method < 0 && S > job.t_s);
-    if (tid < 256) s_len[tid] = 0;
-    if (tid == 0) s_maxlen = 0;
     __syncthreads();
+    unsigned long long nz = 0, trans = 0;
+    for (uint32_t w = 0; w < kWaves; ++w) {
+        nz += s_red[w];
+        trans += s_red2[w];
+    }
+    if (tid == 0) f = S - nz;  // zero bytes are not counted by the encoder
+    const unsigned long long nruns = 1 + trans;
+    const uint64_t nchunks = (S + job.huf_chunk - 1) / job.huf_chunk;
+    bool need_code = job.force_method == 2 || (job.force_method < 0 && S > job.t_s);
+    double ent = 0.0;
+    if (need_code) {
+        if (tid < 256) {
+            s_key[tid] = f ? (f << 8) | tid : ~0ull;
+            // entropy in bits (float logarithms: a relative error of about 1e-6)
+            double h = f ? (double)f * (double)(__log2f((float)S) - __log2f((float)f)) : 0.0;
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) h += __shfl_xor(h, off, 64);
+            const unsigned long long pm = __ballot(f != 0);
+            if (lane == 0) {
+                s_redf[wave] = h;
+                s_cnt[wave][0] = (uint32_t)__popcll(pm);
+            }
+        }
+        __syncthreads();
+        ent = (s_redf[0] + s_redf[1]) + (s_redf[2] + s_redf[3]);
+        if (job.force_method < 0) {
+            const double low = ent * (0.9999 / 8) + (double)(8 + 256 + 4 * (nchunks + 1)) - 1e-4 * (double)S;
+            need_code = !(1000.0 * (double)S < (double)job.t_cr_milli * low);
+        }
+    }
 
-    // ---- Huffman code lengths: two-queue tree, depths by pointer jumping, and
-    // the per-length count adjustment when the tree is deeper than huf_lmax
+    // ---- Huffman code lengths
     if (need_code) {
         // rank of each present symbol in (count, symbol) order: kRankParts
         // threads per symbol, 256 / kRankParts comparisons each
-        {
-            constexpr uint32_t kRankParts = NT / 256;
-            constexpr int kSpan = 256 / kRankParts;
-            const uint32_t sym = tid & 255, part = tid >> 8;
-            const unsigned long long fsym = s_f[sym];
-            if (tid < 256) s_dp[tid] = 0;
-            if (tid == 0) s_nl = 0;
+        constexpr uint32_t kRankParts = kWaves / 4;
+        constexpr uint32_t kSpan = 256 / kRankParts;
+        const uint32_t s = tid & 255, part = tid >> 8;
+        const unsigned long long key = s_key[s];
+        uint32_t r = 0;
+#pragma unroll 8
+        for (uint32_t q = part * kSpan; q < part * kSpan + kSpan; ++q) r += s_key[q] < key ? 1u : 0u;
+        if (kRankParts > 1) {
+            if (r) atomicAdd(&s_rank[s], r);
             __syncthreads();
-            if (fsym) {
-                int r = 0;
-#pragma unroll 16
-                for (int q = (int)part * kSpan; q < (int)part * kSpan + kSpan; ++q) {
-                    const unsigned long long fs = s_f[q];
-                    r += (fs && (fs < fsym || (fs == fsym && q < (int)sym))) ? 1 : 0;
-                }
-                if (r) atomicAdd(&s_dp[sym], r);
-            }
-            __syncthreads();
+            r = s_rank[s];
         }
-        const unsigned long long ft = tid < 256 ? s_f[tid] : 0;
-        const int rank = tid < 256 ? s_dp[tid] : 0;
-        __syncthreads();
-        if (tid < 256 && ft) {
-            s_sorted[rank] = (int)tid;
-            atomicAdd(&s_nl, 1);
+        const int nl = (int)(s_cnt[0][0] + s_cnt[1][0] + s_cnt[2][0] + s_cnt[3][0]);
+        if (part == 0 && key != ~0ull) {
+            s_sorted[r] = s;
+            s_cs.w[r] = (W)(key >> 8);
         }
         __syncthreads();
-        const int nl = s_nl;
-        if (tid < nl) s_w[tid] = s_f[s_sorted[tid]];
-        __syncthreads();
-        if (tid == 0 && nl > 1) {
-            // leaves s_w[0, nl) ascending, merged nodes appended from nl; the
-            // two heads of each queue live in registers (an empty slot holds
-            // ~0, above any weight) and are refilled from LDS one pick ahead.
-            // A tie takes the leaf.
-            constexpr unsigned long long kNone = ~0ull;
-            int q1 = 0, q2 = nl, next = nl;
-            unsigned long long l0 = s_w[0], l1 = s_w[1], i0 = kNone, i1 = kNone;
-            auto pick = [&](unsigned long long& wt) -> int {
-                int at;
-                if (l0 <= i0) {
-                    at = q1++;
-                    wt = l0;
-                    l0 = l1;
-                    l1 = q1 + 1 < nl ? s_w[q1 + 1] : kNone;
-                } else {
-                    at = q2++;
-                    wt = i0;
-                    i0 = i1;
-                    i1 = q2 + 1 < next ? s_w[q2 + 1] : kNone;
+        if (wave == 0) {
+            if (nl == 1) {  // a phantom partner, the smallest other symbol
+                if (lane == 0) {
+                    const uint32_t s0 = s_sorted[0];
+                    s_len[s0] = 1;
+                    s_len[s0 == 0 ? 1 : 0] = 1;
+                    s_maxlen = 1;
                 }
-                return at;
-            };
-            while ((nl - q1) + (next - q2) > 1) {
-                unsigned long long wa, wb;
-                const int a = pick(wa);
-                const int b = pick(wb);
-                const unsigned long long sum = wa + wb;
-                s_w[next] = sum;
-                s_parent[a] = next;
-                s_parent[b] = next;
-                if (q2 == next)
-                    i0 = sum;
-                else if (q2 + 1 == next)
-                    i1 = sum;
-                ++next;
-            }
-            s_parent[next - 1] = next - 1;  // the root points to itself
-        }
-        __syncthreads();
-        // depth of every node: d <- d + d[parent], parent <- parent[parent] (9 rounds for 511 nodes)
-        const int nnodes = nl > 1 ? 2 * nl - 1 : 0;
-        int* s_d = s_dp;
-        int* s_p = s_dp + 512;
-        constexpr int kNodesPer = (512 + NT - 1) / NT;  // nodes per thread
-#pragma unroll
-        for (int h = 0; h < kNodesPer; ++h) {
-            const int v = (int)tid + h * NT;
-            if (v < nnodes) {
-                s_p[v] = s_parent[v];
-                s_d[v] = (v == nnodes - 1) ? 0 : 1;
-            }
-        }
-        __syncthreads();
-        for (int round = 0; round < 9; ++round) {
-            int nd[kNodesPer], np[kNodesPer];
-#pragma unroll
-            for (int h = 0; h < kNodesPer; ++h) {
-                const int v = (int)tid + h * NT;
-                nd[h] = 0, np[h] = 0;
-                if (v < nnodes) {
-                    const int p = s_p[v];
-                    nd[h] = s_d[v] + s_d[p];
-                    np[h] = s_p[p];
-                }
-            }
-            __syncthreads();
-#pragma unroll
-            for (int h = 0; h < kNodesPer; ++h) {
-                const int v = (int)tid + h * NT;
-                if (v < nnodes) {
-                    s_d[v] = nd[h];
-                    s_p[v] = np[h];
-                }
-            }
-            __syncthreads();
-        }
-        if (tid == 0 && nl == 1) {
-            int s0 = s_sorted[0];
-            s_len[s0] = 1;
-            s_len[s0 == 0 ? 1 : 0] = 1;
-            s_maxlen = 1;
-        }
-        if (nl > 1 && tid < nl) atomicMax(&s_maxlen, s_d[tid]);  // leaves are nodes 0 .. nl-1
-        __syncthreads();
-        if (nl > 1 && s_maxlen <= (int)job.huf_lmax) {
-            if (tid < nl) s_len[s_sorted[tid]] = (uint8_t)s_d[tid];
-        } else if (nl > 1) {
-            // ITU-T T.81 Annex K count adjustment on one lane, then hand the
-            // lengths out again: heaviest leaf (last in sorted order) shortest
-            uint32_t* s_bits = reinterpret_cast<uint32_t*>(s_parent);  // 256+1 entries
-            for (uint32_t i = tid; i <= 256; i += NT) s_bits[i] = 0;
-            __syncthreads();
-            if (tid < nl) atomicAdd(&s_bits[s_d[tid]], 1u);
-            __syncthreads();
-            const int maxlen = s_maxlen;
-            if (maxlen < 64) {
-                // one wavefront, lane l holding the count of length l; j is the
-                // longest length below i - 1 with a code
-                if (wave == 0) {
-                    int b = (int)s_bits[lane];
-                    for (int i = maxlen; i > (int)job.huf_lmax; --i) {
-                        while (__builtin_amdgcn_readlane(b, i) > 0) {
-                            const unsigned long long nzm = __ballot(b != 0) & ((1ull << (i - 1)) - 1);
-                            if (!nzm) break;  // cannot happen for a full tree
-                            const int j = 63 - __clzll((long long)nzm);
-                            const int l = (int)lane;
-                            b += (l == i ? -2 : 0) + (l == i - 1 ? 1 : 0) + (l == j + 1 ? 2 : 0) + (l == j ? -1 : 0);
-                        }
-                    }
-                    s_bits[lane] = (uint32_t)b;
-                }
-            } else if (tid == 0) {
-                for (int i = maxlen; i > (int)job.huf_lmax; --i) {
-                    while (s_bits[i] > 0) {
-                        int j = i - 2;
-                        while (s_bits[j] == 0) --j;
-                        s_bits[i] -= 2;
-                        s_bits[i - 1] += 1;
-                        s_bits[j + 1] += 2;
-                        s_bits[j] -= 1;
-                    }
-                }
-            }
-            __syncthreads();
-            if (tid == 0) s_maxlen = (int)job.huf_lmax;
-            if (tid < nl) {
-                const uint32_t pos = (uint32_t)(nl - 1) - tid;  // 0 = heaviest
-                uint32_t cum = 0, Lh = 1;
-                for (; Lh <= job.huf_lmax; ++Lh) {
-                    cum += s_bits[Lh];
-                    if (pos < cum) break;
-                }
-                s_len[s_sorted[tid]] = (uint8_t)Lh;
+            } else {
+                const uint32_t most = huf_lengths(s_cs, s_sorted, nl, job.huf_lmax, s_len, lane);
+                if (lane == 0) s_maxlen = most;
             }
         }
         __syncthreads();
     }
 
-    // ---- canonical codes: (length, symbol) order
-    if (tid < 33) s_count[tid] = 0;
-    __syncthreads();
+    // ---- canonical codes: (length, symbol) order.  A symbol's place among the
+    // codes of its length: ballots within its wavefront, then the earlier ones'
     const uint32_t L = tid < 256 ? s_len[tid] : 0;
-    if (L) atomicAdd(&s_count[L], 1u);
-    __syncthreads();
-    if (tid == 0) {
-        uint32_t c = 0;
-        for (int l = 1; l <= 32; ++l) {
-            s_first[l] = c;
-            c = (c + s_count[l]) << 1;
+    uint32_t before = 0;
+    unsigned long long bits = 0;
+    if (tid < 256) {
+        if (need_code) {
+            uint32_t mine = 0;  // lane l: this wavefront's symbols of length l
+#pragma unroll
+            for (uint32_t l = 1; l <= (uint32_t)kLutBitsMax; ++l) {
+                const unsigned long long bl = __ballot(L == l);
+                mine = lane == l ? (uint32_t)__popcll(bl) : mine;
+                if (L == l) before = (uint32_t)__popcll(bl & ((1ull << lane) - 1));
+            }
+            if (lane >= 1 && lane <= (uint32_t)kLutBitsMax) s_cnt[wave][lane] = mine;
         }
+        bits = wave_sum64(f * (unsigned long long)L);
+        if (lane == 0) s_bits[wave] = bits;
     }
     __syncthreads();
     if (tid < 256) {
         uint32_t code = 0;
-        if (L) {
-            uint32_t before = 0;
-#pragma unroll 16
-            for (uint32_t q = 0; q < tid; ++q) before += s_len[q] == L ? 1u : 0u;
-            code = s_first[L] + before;
+        if (need_code) {
+            // lane l: symbols of length l in all, and in the earlier wavefronts
+            uint32_t all = 0, earlier = 0;
+            if (lane >= 1 && lane <= (uint32_t)kLutBitsMax) {
+#pragma unroll
+                for (uint32_t w = 0; w < 4; ++w) {
+                    const uint32_t c = s_cnt[w][lane];
+                    all += c;
+                    earlier += w < wave ? c : 0u;
+                }
+            }
+            uint32_t first = 0;
+#pragma unroll
+            for (uint32_t l = 1; l <= (uint32_t)kLutBitsMax; ++l) {
+                if (L == l) code = first + lane_value(earlier, (int)l) + before;
+                first = (first + lane_value(all, (int)l)) << 1;
+            }
         }
         lv.lens[u * 256 + tid] = (uint8_t)L;
         lv.codes[u * 256 + tid] = code;
     }
 
     // ---- estimates and the decision
-    unsigned long long bits = block_sum(tid < 256 ? s_f0[tid] * (unsigned long long)L : 0);
     if (tid == 0) {
-        const uint64_t nchunks = (S + job.huf_chunk - 1) / job.huf_chunk;
+        bits = s_bits[0] + s_bits[1] + s_bits[2] + s_bits[3];
+        // (0 for a unit without a code: its Huffman estimate is not needed)
         const uint64_t est_huf = need_code ? (bits + 7) / 8 + 8 + 256 + 4 * (nchunks + 1) : 0;
         const uint64_t est_rle = 8 + nruns * (4ull * G + 4);
         uint32_t method;
         if (job.force_method >= 0) {
             method = (uint32_t)job.force_method;
         } else if (S > job.t_s) {
-            if (1000ull * S > (uint64_t)job.t_cr_milli * est_huf)
+            if (need_code && 1000ull * S > (uint64_t)job.t_cr_milli * est_huf)
                 method = 2;  // MDR_HUF
             else if (1000ull * S > (uint64_t)job.t_cr_milli * est_rle)
                 method = 1;  // MDR_RLE
@@ -1196,7 +1362,7 @@ __global__ __launch_bounds__(NT) void k_select(const SelectParams job,
         ui.nruns = nruns;
         ui.method = method;
         ui.nchunks = (uint32_t)nchunks;
-        ui.maxlen = (uint32_t)s_maxlen;
+        ui.maxlen = s_maxlen;
         ui.pad = 0;
         lv.units[u] = ui;
     }
@@ -1323,12 +1489,26 @@ hipError_t launch_select_batch(const SelectParams& p, const SelectLevel* lv, uin
 {
     if (nlev == 0) return hipSuccess;
     const dim3 g(p.nunits, nlev);
-    if (p.threads == 256)
-        hipLaunchKernelGGL(k_select<256>, g, dim3(256), 0, s, p, lv);
-    else if (p.threads == 1024)
-        hipLaunchKernelGGL(k_select<1024>, g, dim3(1024), 0, s, p, lv);
-    else
-        hipLaunchKernelGGL(k_select<512>, g, dim3(512), 0, s, p, lv);
+    switch (p.threads) {
+    case 256:
+        if (p.wide)
+            hipLaunchKernelGGL((k_select<256, uint64_t>), g, dim3(256), 0, s, p, lv);
+        else
+            hipLaunchKernelGGL((k_select<256, uint32_t>), g, dim3(256), 0, s, p, lv);
+        break;
+    case 1024:
+        if (p.wide)
+            hipLaunchKernelGGL((k_select<1024, uint64_t>), g, dim3(1024), 0, s, p, lv);
+        else
+            hipLaunchKernelGGL((k_select<1024, uint32_t>), g, dim3(1024), 0, s, p, lv);
+        break;
+    default:
+        if (p.wide)
+            hipLaunchKernelGGL((k_select<512, uint64_t>), g, dim3(512), 0, s, p, lv);
+        else
+            hipLaunchKernelGGL((k_select<512, uint32_t>), g, dim3(512), 0, s, p, lv);
+        break;
+    }
     return hipGetLastError();
 }
 

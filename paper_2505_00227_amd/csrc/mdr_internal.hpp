@@ -93,6 +93,7 @@ struct SelectParams {
     uint32_t t_cr_milli, huf_chunk, huf_lmax;
     int32_t force_method;
     uint32_t threads;  // workgroup size of the selection kernel: 256, 512 or 1024
+    uint32_t wide;     // some unit has 2^30 bytes or more: 64-bit symbol counts
     uint64_t t_s;
 };
 

@@ -108,6 +108,7 @@ struct JobPlan {
 
 struct Layout {
     bool f64 = false;
+    bool wide = false;  // some unit has 2^30 bytes or more
     uint32_t G = 1, B = 0, m = 0, nunits = 0, J = 0, U = 0;
     std::vector<JobPlan> jobs;
     std::vector<uint32_t> var_first;  // first job of each variable, plus J
@@ -193,6 +194,7 @@ mdr_status make_layout(const mdr_context* ctx, const VarLevels* vars, uint32_t n
             const uint32_t r1 = i == 0 ? 1 : std::min(B + 1, r0 + L.m);
             const uint64_t S = 4ull * (r1 - r0) * jp.nbd;
             L.pay_cap += unit_cap(S, prm, L.G);
+            L.wide = L.wide || S >= (1ull << 30);
             L.max_chunks += ceil_div(S, prm.huf_chunk);
             L.max_tiles += ceil_div(S / (4ull * L.G), kRleTileWords);
         }
@@ -393,6 +395,7 @@ mdr_status enqueue_pass(mdr_context* ctx, const Layout& L, const mdr_codec_param
         sp.huf_lmax = prm.huf_lmax;
         sp.force_method = prm.force_method;
         sp.threads = L.shape.select_threads;
+        sp.wide = L.wide ? 1u : 0u;
         sp.t_s = prm.t_s_bytes;
         for (uint32_t j0 = 0; j0 < L.J; j0 += 65535)
             MDR_HIP(launch_select_batch(sp, sl + j0, std::min<uint32_t>(65535, L.J - j0), s));
