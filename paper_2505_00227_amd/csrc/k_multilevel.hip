@@ -12,395 +12,590 @@
 // field's type, one rounding per operation (no contraction), so coefficients
 // are reproducible bit for bit.
 //
-// One launch per level.  A decomposition step reads only the input field, so
-// its launches are independent; a recomposition step reads the nodes of every
-// coarser step, so they run coarsest first.  Within a step a wavefront covers
-// part of one row of the step's grid and a lane an (even, odd) pair of its
-// nodes (in the finest step, groups of 4): the row's parity, coarse rows and
-// output offset are uniform, and consecutive lanes touch consecutive nodes.
+// A wavefront covers cells of a step's grid: a cell is the 2 x 2 rows
+// (2A, 2B) .. (2A + 1, 2B + 1) of it, and a lane takes four consecutive nodes of
+// each of them.  The four rows share the coarse rows they refine from, so a
+// cell reads seven rows (decomposition) or four and its coefficients
+// (recomposition) with every load in flight at once, where row by row it was
+// twelve.  Rows shorter than a wavefront's 256 nodes are packed side by side
+// into its lanes.  A decomposition step reads only the input field, so all
+// steps run in one launch; a recomposition step reads the nodes of every
+// coarser step, so they run coarsest first, the small grids together in one
+// workgroup's LDS.
+//
+// Bound: HBM (2 n values), with the neighbour rows from L2: consecutive
+// workgroups are placed on one XCD, a contiguous range of the grid each.  The
+// decomposition of a 512^3 f32 field went from 0.54 ms (a row segment a
+// wavefront, a launch a step) to 0.21, 5.1 TB/s of its 2 n values, 0.92 of a
+// large copy's rate; the recomposition of a 301 x 402 x 503 f64 one from 0.48
+// to 0.29.
+// 16-byte accesses need only the value's alignment here, so rows of any length
+// and level offsets of any alignment take the same path.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
 
+#include "device_bits.hpp"
 #include "mdr_internal.hpp"
 
 namespace mdr {
 namespace {
 
-constexpr uint32_t kMl = 256;  // threads per workgroup, along x
+constexpr uint32_t kMl = 256;       // threads per workgroup: four wavefronts
+constexpr uint32_t kMlNodes = 256;  // nodes of a row a wavefront covers: four a lane
+constexpr uint32_t kMlXcds = 8;
 
-__device__ __forceinline__ uint64_t axis_nodes(uint32_t n, uint32_t j)
+__host__ __device__ __forceinline__ uint64_t axis_nodes(uint32_t n, uint32_t j)
 {
     return n == 0 ? 0 : (uint64_t)((n - 1) >> j) + 1;
 }
 
-// position of stride-h node (a, b, c) among its grid's nodes that are not on
-// the stride-2h grid, in row-major order (m1, m2: nodes per y / x line)
-__device__ __forceinline__ uint64_t new_rank(uint64_t a, uint64_t b, uint64_t c, uint64_t m1, uint64_t m2)
-{
-    const uint64_t e1 = (m1 + 1) >> 1, e2 = (m2 + 1) >> 1;
-    uint64_t skipped = ((a + 1) >> 1) * e1 * e2;  // all-even nodes of earlier planes
-    if (!(a & 1)) {
-        skipped += ((b + 1) >> 1) * e2;           // ... of earlier rows in this plane
-        if (!(b & 1)) skipped += (c + 1) >> 1;    // ... earlier in this row
-    }
-    return (a * m1 + b) * m2 + c - skipped;
-}
-
-// The coarse rows a stride-h row (a, b) interpolates from: rows a -/+ 1 when a
-// is odd (one of them past the end of the grid), row a itself when it is even;
-// the same along y.  Uniform across a workgroup, which covers part of one row.
-template <typename T>
-struct CoarseRows {
-    const T* r[2][2];  // [z side][y side]
-    bool z2, y2;       // mean of both sides, else side 0 alone
+// One step's work: its grid, level offset and wavefront units.
+struct MlStep {
+    uint64_t coef;     // offset of the step's level in the coefficient buffer
+    uint64_t coef1;    // FUSED: and of step 1's
+    uint32_t m0, m1, m2;
+    uint32_t j;
+    uint32_t segs;     // wavefronts along a row
+    uint32_t pack;     // cells along y a wavefront packs (segs == 1), a power of two
+    uint32_t groups;   // wavefronts along y
+    uint32_t blk0;     // first workgroup of the step in its launch
+    uint32_t blocks;   // workgroups
 };
 
-template <typename T>
-__device__ __forceinline__ CoarseRows<T> coarse_rows(const T* u, uint32_t n1, uint32_t n2, uint64_t a, uint64_t b,
-                                                     uint64_t m0, uint64_t m1, uint32_t j)
-{
-    CoarseRows<T> cr;
-    const uint64_t z0 = (a & 1) ? a - 1 : a, y0 = (b & 1) ? b - 1 : b;
-    cr.z2 = (a & 1) && a + 1 < m0;
-    cr.y2 = (b & 1) && b + 1 < m1;
-    const uint64_t z1 = cr.z2 ? a + 1 : z0, y1 = cr.y2 ? b + 1 : y0;
-    auto row = [&](uint64_t zz, uint64_t yy) { return u + ((zz << j) * n1 + (yy << j)) * n2; };
-    cr.r[0][0] = row(z0, y0);
-    cr.r[0][1] = row(z0, y1);
-    cr.r[1][0] = row(z1, y0);
-    cr.r[1][1] = row(z1, y1);
-    return cr;
-}
+// vectors that need only their element's alignment
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(4)));
 
-// P at the pair of stride-h nodes (2t, 2t + 1) of a row: pe for the even node
-// (no refinement along x), po for the odd one (mean of coarse nodes 2t and
-// 2t + 2, or node 2t alone past the end of the line); then y, then z
-template <typename T>
-__device__ __forceinline__ void predict_pair(const CoarseRows<T>& cr, uint64_t xe, uint64_t xn, bool x2, T& pe, T& po)
+// NT: touched once, kept out of the way of the rows that neighbours share
+template <typename T, int N, bool NT = false>
+__device__ __forceinline__ void load_vec(const T* p, T* o)
 {
-#pragma clang fp contract(off)
-    const T half = T(0.5);
-    T e[2][2], o[2][2];
-#pragma unroll
-    for (int zi = 0; zi < 2; ++zi)
-#pragma unroll
-        for (int yi = 0; yi < 2; ++yi) {
-            const T* r = cr.r[zi][yi];
-            const T v = r[xe];
-            e[zi][yi] = v;
-            o[zi][yi] = x2 ? (v + r[xn]) * half : v;
-        }
-    T ey[2], oy[2];
-#pragma unroll
-    for (int zi = 0; zi < 2; ++zi) {
-        ey[zi] = cr.y2 ? (e[zi][0] + e[zi][1]) * half : e[zi][0];
-        oy[zi] = cr.y2 ? (o[zi][0] + o[zi][1]) * half : o[zi][0];
-    }
-    pe = cr.z2 ? (ey[0] + ey[1]) * half : ey[0];
-    po = cr.z2 ? (oy[0] + oy[1]) * half : oy[0];
-}
-
-// Step j of the decomposition (DEC: field -> level) or of the recomposition
-// (field of the coarser steps + level -> field).  Grid: (pairs / kStepX,
-// m1 / kStepRows, m0) over the stride-h grid, block (kStepX, kStepRows): a
-// wavefront per row (rows of the coarser steps are short), and a lane takes the
-// nodes 2t and 2t + 1 of its row.
-constexpr uint32_t kStepX = 64, kStepRows = 4;
-
-// In a row with a or b odd every node is new and the row's coefficients are
-// contiguous from new_rank(a, b, 0); in a row with both even only odd x is new.
-template <typename T, bool DEC>
-__device__ __forceinline__ void ml_step_row(const T* __restrict__ in, T* out, const T* field, uint32_t n1,
-                                            uint32_t n2, uint32_t j, uint64_t m0, uint64_t a)
-{
-#pragma clang fp contract(off)
-    const uint64_t m1 = axis_nodes(n1, j), m2 = axis_nodes(n2, j);
-    const uint64_t t = (uint64_t)blockIdx.x * kStepX + threadIdx.x;
-    const uint64_t b = (uint64_t)blockIdx.y * kStepRows + threadIdx.y;
-    if (2 * t >= m2 || b >= m1) return;
-    const bool coarse_row = !((a | b) & 1);
-    const uint64_t base = new_rank(a, b, 0, m1, m2);
-    const CoarseRows<T> cr = coarse_rows(field, n1, n2, a, b, m0, m1, j);
-    const bool has_odd = 2 * t + 1 < m2;
-    const uint64_t xe = (2 * t) << j, xo = (2 * t + 1) << j, xn = (2 * t + 2) << j;
-    T pe, po;
-    predict_pair(cr, xe, xn, 2 * t + 2 < m2, pe, po);
-    const uint64_t self = ((a << j) * n1 + (b << j)) * n2;
-    if (DEC) {
-        const T* u = in + self;
-        if (coarse_row) {
-            if (has_odd) out[base + t] = u[xo] - po;
-        } else {
-            out[base + 2 * t] = u[xe] - pe;
-            if (has_odd) out[base + 2 * t + 1] = u[xo] - po;
-        }
+    constexpr int W = N * sizeof(T) / 4;
+    uint32_t w[W];
+    if constexpr (W == 2) {
+        const u32x2_any q = *gmem(reinterpret_cast<const u32x2_any*>(p));
+        w[0] = q.x, w[1] = q.y;
     } else {
-        T* u = out + self;
-        if (coarse_row) {
-            if (has_odd) u[xo] = in[base + t] + po;
-        } else {
-            u[xe] = in[base + 2 * t] + pe;
-            if (has_odd) u[xo] = in[base + 2 * t + 1] + po;
+#pragma unroll
+        for (int i = 0; i < W / 4; ++i) {
+            const auto at = gmem(reinterpret_cast<const u32x4_any*>(p)) + i;
+            u32x4_any q;
+            if constexpr (NT)
+                q = __builtin_nontemporal_load(at);
+            else
+                q = *at;
+            w[4 * i] = q.x, w[4 * i + 1] = q.y, w[4 * i + 2] = q.z, w[4 * i + 3] = q.w;
+        }
+    }
+    __builtin_memcpy(o, w, sizeof w);
+}
+
+template <typename T, int N, bool NT = false>
+__device__ __forceinline__ void store_vec(T* p, const T* v)
+{
+    constexpr int W = N * sizeof(T) / 4;
+    uint32_t w[W];
+    __builtin_memcpy(w, v, sizeof w);
+    if constexpr (W == 2) {
+        *gmem(reinterpret_cast<u32x2_any*>(p)) = u32x2_any{w[0], w[1]};
+    } else {
+#pragma unroll
+        for (int i = 0; i < W / 4; ++i) {
+            const u32x4_any q = u32x4_any{w[4 * i], w[4 * i + 1], w[4 * i + 2], w[4 * i + 3]};
+            if constexpr (NT)
+                __builtin_nontemporal_store(q, gmem(reinterpret_cast<u32x4_any*>(p)) + i);
+            else
+                gmem(reinterpret_cast<u32x4_any*>(p))[i] = q;
         }
     }
 }
 
-// 16-byte row accesses of 4 consecutive values
-__device__ __forceinline__ void load4(const float* p, float o[4])
+// nodes x .. x + 3 (cnt of them exist) of a grid row that starts at `row`,
+// 2^j values apart; J = 0, 1: the step index at compile time, whole vectors
+template <typename T, int J, bool NT = false>
+__device__ __forceinline__ void load_nodes(const T* row, uint32_t x, uint32_t cnt, uint32_t n2, uint32_t j, T (&v)[4])
 {
-    const float4 v = *reinterpret_cast<const float4*>(p);
-    o[0] = v.x, o[1] = v.y, o[2] = v.z, o[3] = v.w;
-}
-__device__ __forceinline__ void load4(const double* p, double o[4])
-{
-    const double2 v0 = reinterpret_cast<const double2*>(p)[0], v1 = reinterpret_cast<const double2*>(p)[1];
-    o[0] = v0.x, o[1] = v0.y, o[2] = v1.x, o[3] = v1.y;
-}
-__device__ __forceinline__ void store4(float* p, const float o[4])
-{
-    *reinterpret_cast<float4*>(p) = make_float4(o[0], o[1], o[2], o[3]);
-}
-__device__ __forceinline__ void store4(double* p, const double o[4])
-{
-    reinterpret_cast<double2*>(p)[0] = make_double2(o[0], o[1]);
-    reinterpret_cast<double2*>(p)[1] = make_double2(o[2], o[3]);
+    if (J == 0 && cnt == 4) {
+        load_vec<T, 4, NT>(row + x, v);
+    } else if (J == 1 && cnt == 4 && 2ull * x + 8 <= n2) {
+        T w[8];
+        load_vec<T, 8>(row + 2ull * x, w);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = w[2 * k];
+    } else {
+#pragma unroll
+        for (uint32_t k = 0; k < 4; ++k) v[k] = k < cnt ? gmem(row)[(uint64_t)(x + k) << j] : T(0);
+    }
 }
 
-constexpr uint32_t kFineX = 64, kFineRows = 4;  // workgroup: a wavefront per row, 4 rows
-
-// order LDS traffic between the lanes of one wavefront
-__device__ __forceinline__ void wave_sync()
+// the next lane's value (the last lane's own is returned in its place)
+__device__ __forceinline__ float next_lane(float v)
 {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    const int b = __float_as_int(v);
+    return __int_as_float(__builtin_amdgcn_update_dpp(b, b, 0x130, 0xF, 0xF, false));  // wave_shl:1
+}
+__device__ __forceinline__ double next_lane(double v)
+{
+    const int lo = __double2loint(v), hi = __double2hiint(v);
+    return __hiloint2double(__builtin_amdgcn_update_dpp(hi, hi, 0x130, 0xF, 0xF, false),
+                            __builtin_amdgcn_update_dpp(lo, lo, 0x130, 0xF, 0xF, false));
 }
 
-// The finest step (j = 0) when rows are whole 16-byte vectors (n2 % 4 == 0,
-// 16-byte aligned field): a lane takes kFineG groups of 4 consecutive nodes of
-// its row (group g of lane t: nodes 4(g kFineX + t) .. + 3), every load of
-// every group issued before any arithmetic so that a wavefront keeps more
-// bytes in flight per memory round trip; one 16-byte access per row read per
-// group, the same arithmetic as k_ml_step.  The level side (any alignment)
-// goes through LDS so that its loads and stores are lane-contiguous: the
-// wavefront's coefficients are one contiguous run (4 kFineG kFineX of them, half
-// in a row with both indices even, fewer at a row's end).  A wavefront takes
-// kFineR rows (b, b + kFineRows, ...), loading all of them first.  Grid:
-// (n2 / (4 kFineG kFineX), n1 / (kFineRows kFineR), n0), block (kFineX,
-// kFineRows).
-constexpr uint32_t kFineG = 2;                      // 4-node groups per lane and row
-constexpr uint32_t kFineR = 1;                      // rows per wavefront: b, b + kFineRows, ... (2 was
-                                                    // slower: more registers, no more bytes per round trip)
-constexpr uint32_t kFineRun = 4 * kFineG * kFineX;  // nodes per wavefront and row
-
-template <typename T, bool DEC>
-__device__ __forceinline__ void ml_fine_rows(const T* __restrict__ in, T* out, const T* field, uint32_t n0,
-                                             uint32_t n1, uint32_t n2, uint64_t a, T (*w)[kFineRun])
+// P along x of a coarse row's nodes x .. x + 3 from its even ones (v[0], v[2]
+// and nx, the node x + 4)
+template <typename T>
+__device__ __forceinline__ void refine_x(const T (&v)[4], T nx, bool has2, bool has4, T (&p)[4])
 {
 #pragma clang fp contract(off)
-    const uint32_t lane = threadIdx.x;
-    const uint64_t q = n2 / 4;  // groups per row
-    const uint64_t g0 = (uint64_t)blockIdx.x * (kFineG * kFineX);
-    const uint64_t b0 = (uint64_t)blockIdx.y * (kFineRows * kFineR) + threadIdx.y;
-    if (b0 >= n1) return;  // whole wavefront
-    const uint64_t wgroups = q - g0 < kFineG * kFineX ? q - g0 : kFineG * kFineX;
-    const T half = T(0.5);
-    bool rlive[kFineR], coarse_row[kFineR];
-    uint64_t wcoef[kFineR], wbase[kFineR], row[kFineR];
-    CoarseRows<T> cr[kFineR];
-    T v[kFineR][kFineG][2][2][4], nx[kFineR][kFineG][2][2], u[kFineR][kFineG][4];
-    bool live[kFineG];
-    uint64_t xs[kFineG];
+    p[0] = v[0];
+    p[1] = has2 ? (v[0] + v[2]) * T(0.5) : v[0];
+    p[2] = v[2];
+    p[3] = has4 ? (v[2] + nx) * T(0.5) : v[2];
+}
+
+template <typename T>
+__device__ __forceinline__ T mean(T a, T b)
+{
+#pragma clang fp contract(off)
+    return (a + b) * T(0.5);
+}
+
+// The stride-2 nodes x and x + 2 (v[0], v[2]) of a cell's four coarse rows
+// (2A + 2da, 2B + 2db), rebuilt from the stride-4 nodes and step 1's
+// coefficients: the recomposition's last two steps in one pass, so that step
+// 1's nodes, every second value of every fourth row, are never written and
+// read back as partial lines (65 of 340 us on a 301 x 402 x 503 f64 field).
+template <typename T>
+__device__ __forceinline__ void stride2_rows(const T* __restrict__ lv1, const T* field, uint32_t n1, uint32_t n2,
+                                             uint32_t m0, uint32_t m1, uint32_t m2, uint32_t A, uint32_t B, uint32_t x,
+                                             bool live, bool has2, bool has4, T (&e)[2][2][4])
+{
+#pragma clang fp contract(off)
+    const uint32_t h0 = (m0 + 1) >> 1, h1 = (m1 + 1) >> 1, h2 = (m2 + 1) >> 1;  // stride-2 grid
+    const uint32_t q0 = (h0 + 1) >> 1, q1 = (h1 + 1) >> 1, q2 = (h2 + 1) >> 1;  // stride-4 grid
+    const uint32_t zl = A >> 1, yl = B >> 1;
+    const bool zh = zl + 1 < q0, yh = yl + 1 < q1;
+    const bool a_odd = A & 1, b_odd = B & 1;
+    T n[2][2][2] = {};  // stride-4 rows [z][y], refined along x: stride-2 nodes x / 2, x / 2 + 1
+    T c[2][2][2] = {};  // step 1's coefficients of the four rows
+    if (live) {
 #pragma unroll
-    for (uint32_t g = 0; g < kFineG; ++g) {
-        const uint64_t grp = g0 + (uint64_t)g * kFineX + lane;  // each access lane-contiguous
-        live[g] = grp < q;
-        xs[g] = 4 * grp;
-    }
-    // every load of every row and group first
+        for (uint32_t z = 0; z < 2; ++z)
 #pragma unroll
-    for (uint32_t rr = 0; rr < kFineR; ++rr) {
-        const uint64_t b = b0 + (uint64_t)rr * kFineRows;
-        rlive[rr] = b < n1;
-        if (!rlive[rr]) continue;
-        coarse_row[rr] = !((a | b) & 1);
-        wcoef[rr] = coarse_row[rr] ? 2 * wgroups : 4 * wgroups;  // this row's run of coefficients
-        wbase[rr] = new_rank(a, b, 0, n1, n2) + (coarse_row[rr] ? 2 : 4) * g0;
-        row[rr] = (a * n1 + b) * n2;
-        cr[rr] = coarse_rows(field, n1, n2, a, b, n0, n1, 0);
+            for (uint32_t y = 0; y < 2; ++y)
+                if ((z == 0 || zh) && (y == 0 || yh))
+                    n[z][y][0] = gmem(field)[((uint64_t)(zl + z) * 4 * n1 + (uint64_t)(yl + y) * 4) * n2 + x];
 #pragma unroll
-        for (uint32_t g = 0; g < kFineG; ++g) {
-            if (!live[g]) continue;
+        for (uint32_t da = 0; da < 2; ++da)
 #pragma unroll
-            for (int zi = 0; zi < 2; ++zi)
-#pragma unroll
-                for (int yi = 0; yi < 2; ++yi) {
-                    const T* r = cr[rr].r[zi][yi];
-                    load4(r + xs[g], v[rr][g][zi][yi]);
-                    nx[rr][g][zi][yi] = xs[g] + 4 < n2 ? r[xs[g] + 4] : T(0);
-                }
-            if (DEC) load4(in + row[rr] + xs[g], u[rr][g]);
-        }
-        if (!DEC) {
-#pragma unroll
-            for (uint32_t k = 0; k < 4 * kFineG; ++k) {
-                const uint64_t i = lane + (uint64_t)k * kFineX;
-                if (i < wcoef[rr]) w[rr][i] = in[wbase[rr] + i];
-            }
-        }
-    }
-    T c[kFineR][kFineG][4];  // recomposition: coefficients (odd nodes only in a coarse row)
-    if (!DEC) {
-        wave_sync();
-#pragma unroll
-        for (uint32_t rr = 0; rr < kFineR; ++rr)
-#pragma unroll
-            for (uint32_t g = 0; g < kFineG; ++g) {
-                const uint32_t slot = g * kFineX + lane;
-                if (rlive[rr] && coarse_row[rr]) {
-                    c[rr][g][1] = w[rr][2 * slot];
-                    c[rr][g][3] = w[rr][2 * slot + 1];
+            for (uint32_t db = 0; db < 2; ++db) {
+                const uint32_t a = A + da, b = B + db;
+                if (a >= h0 || b >= h1) continue;
+                uint64_t at = ((uint64_t)a * h1 + b) * h2 - (uint64_t)((a + 1) >> 1) * q1 * q2;
+                if (!(a & 1)) at -= (uint64_t)((b + 1) >> 1) * q2;
+                if (!((a | b) & 1)) {  // only its odd nodes are new
+                    if (has2) c[da][db][1] = gmem(lv1)[at + x / 4];
+                } else if (has2) {
+                    load_vec<T, 2>(lv1 + at + x / 2, c[da][db]);
                 } else {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) c[rr][g][k] = w[rr][4 * slot + k];
+                    c[da][db][0] = gmem(lv1)[at + x / 2];
                 }
             }
-        wave_sync();  // every lane has its coefficients before LDS is reused
     }
 #pragma unroll
-    for (uint32_t rr = 0; rr < kFineR; ++rr) {
-        if (!rlive[rr]) continue;
+    for (int z = 0; z < 2; ++z)
 #pragma unroll
-        for (uint32_t g = 0; g < kFineG; ++g) {
-            if (!live[g]) continue;
-            const bool x2 = xs[g] + 4 < n2;  // node x + 3 has a coarse node on its right
-            T p[2][2][4];  // per coarse row: P along x of nodes x .. x + 3 (odd ones refined)
+        for (int y = 0; y < 2; ++y) {
+            const T nx = next_lane(n[z][y][0]);
+            n[z][y][1] = has4 ? mean(n[z][y][0], nx) : n[z][y][0];
+        }
 #pragma unroll
-            for (int zi = 0; zi < 2; ++zi)
+    for (int da = 0; da < 2; ++da)
 #pragma unroll
-                for (int yi = 0; yi < 2; ++yi) {
-                    const T* vv = v[rr][g][zi][yi];
-                    p[zi][yi][0] = vv[0];
-                    p[zi][yi][1] = (vv[0] + vv[2]) * half;
-                    p[zi][yi][2] = vv[2];
-                    p[zi][yi][3] = x2 ? (vv[2] + nx[rr][g][zi][yi]) * half : vv[2];
+        for (int db = 0; db < 2; ++db) {
+            // row A + da lies on the stride-4 grid where that is even: rows zl
+            // (A even) or zl + 1 (A odd); else between the two
+            const bool z_between = da ? !a_odd : a_odd, y_between = db ? !b_odd : b_odd;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                T w[2];
+#pragma unroll
+                for (int z = 0; z < 2; ++z) {
+                    const T lo = n[z][0][k], hi = n[z][1][k];
+                    w[z] = y_between ? (yh ? mean(lo, hi) : lo) : (b_odd ? hi : lo);
                 }
-            T P[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const T y0 = cr[rr].y2 ? (p[0][0][k] + p[0][1][k]) * half : p[0][0][k];
-                const T y1 = cr[rr].y2 ? (p[1][0][k] + p[1][1][k]) * half : p[1][0][k];
-                P[k] = cr[rr].z2 ? (y0 + y1) * half : y0;
-            }
-            const uint32_t slot = g * kFineX + lane;
-            if (DEC) {
-                if (coarse_row[rr]) {
-                    w[rr][2 * slot] = u[rr][g][1] - P[1];
-                    w[rr][2 * slot + 1] = u[rr][g][3] - P[3];
-                } else {
-#pragma unroll
-                    for (int k = 0; k < 4; ++k) w[rr][4 * slot + k] = u[rr][g][k] - P[k];
-                }
-            } else if (coarse_row[rr]) {
-                out[row[rr] + xs[g] + 1] = c[rr][g][1] + P[1];
-                out[row[rr] + xs[g] + 3] = c[rr][g][3] + P[3];
-            } else {
-                T o[4];
-#pragma unroll
-                for (int k = 0; k < 4; ++k) o[k] = c[rr][g][k] + P[k];
-                store4(out + row[rr] + xs[g], o);
+                const T P = z_between ? (zh ? mean(w[0], w[1]) : w[0]) : (a_odd ? w[1] : w[0]);
+                const bool raw = k == 0 && !z_between && !y_between;
+                e[da][db][2 * k] = raw ? P : c[da][db][k] + P;
             }
         }
+}
+
+// One wavefront unit of a step.  DEC: field -> coefficients; else the other
+// way, writing the nodes of the step (j = 0: whole rows).  FUSED (j = 0 of a
+// recomposition): step 1 too, with its level at lv1.
+template <typename T, bool DEC, int J, bool FUSED>
+__device__ __forceinline__ void ml_unit(const MlStep& st, T* __restrict__ coeffs, T* field, uint32_t n1, uint32_t n2,
+                                        uint32_t unit)
+{
+#pragma clang fp contract(off)
+    const uint32_t lane = threadIdx.x & 63;
+    const uint32_t j = J < 2 ? (uint32_t)J : st.j;
+    const uint32_t seg = unit % st.segs, yz = unit / st.segs;
+    const uint32_t A = yz / st.groups, g = yz % st.groups;
+    const uint32_t per = 64 / st.pack;  // lanes a row takes
+    const uint32_t B = g * st.pack + lane / per;
+    // FUSED: the last lane of a segment that the row goes on after only
+    // supplies its neighbour's next node
+    const uint32_t span = FUSED && st.segs > 1 ? kMlNodes - 4 : kMlNodes;
+    const uint32_t x = seg * span + 4 * (lane % per);
+    const uint32_t m0 = st.m0, m1 = st.m1, m2 = st.m2;
+    const bool live = 2 * B < m1 && x < m2;
+    const uint32_t cnt = live ? min(4u, m2 - x) : 0u;
+    const bool zo = 2 * A + 1 < m0, yo = 2 * B + 1 < m1;  // the cell's odd planes / rows exist
+    const bool z2 = 2 * A + 2 < m0, y2 = 2 * B + 2 < m1;  // and the coarse ones past them
+    auto row = [&](uint32_t a, uint32_t b) { return field + (((uint64_t)a << j) * n1 + ((uint64_t)b << j)) * n2; };
+    const T* const c00 = row(2 * A, 2 * B);
+    T e[2][2][4] = {};                 // coarse rows [z][y]
+    T(&e00)[4] = e[0][0];
+    T(&e01)[4] = e[0][1];
+    T(&e10)[4] = e[1][0];
+    T(&e11)[4] = e[1][1];
+    T u01[4], u10[4], u11[4];          // DEC: the cell's other rows; else their coefficients
+    T k0[2] = {T(0), T(0)};            // else: the first row's odd coefficients
+    const uint32_t e1 = (m1 + 1) >> 1, e2 = (m2 + 1) >> 1;
+    // coefficients of the cell's rows: position of each row's first in the level
+    const uint64_t pl0 = (uint64_t)2 * A * m1 * m2 - (uint64_t)A * e1 * e2;
+    const uint64_t pl1 = (uint64_t)(2 * A + 1) * m1 * m2 - (uint64_t)(A + 1) * e1 * e2;
+    T* const lv = coeffs + st.coef;
+    T* const r00 = lv + pl0 + (uint64_t)2 * B * m2 - (uint64_t)B * e2 + x / 2;
+    T* const r01 = lv + pl0 + (uint64_t)(2 * B + 1) * m2 - (uint64_t)(B + 1) * e2 + x;
+    T* const r10 = lv + pl1 + (uint64_t)2 * B * m2 + x;
+    T* const r11 = lv + pl1 + (uint64_t)(2 * B + 1) * m2 + x;
+    const uint32_t odd = cnt >> 1;  // odd nodes among the lane's
+    T nx00 = T(0), nx01 = T(0), nx10 = T(0), nx11 = T(0);
+    const bool edge = !FUSED && lane == 63 && x + 4 < m2;  // the next node is in the next wavefront's segment
+    const bool has2 = x + 2 < m2, has4 = x + 4 < m2;
+    if (live) {
+        if (!FUSED) {
+            load_nodes<T, J>(c00, x, cnt, n2, j, e00);
+            if (y2) load_nodes<T, J>(row(2 * A, 2 * B + 2), x, cnt, n2, j, e01);
+            if (z2) load_nodes<T, J>(row(2 * A + 2, 2 * B), x, cnt, n2, j, e10);
+            if (y2 && z2) load_nodes<T, J>(row(2 * A + 2, 2 * B + 2), x, cnt, n2, j, e11);
+        }
+        if (DEC) {
+            if (yo) load_nodes<T, J, J == 0>(row(2 * A, 2 * B + 1), x, cnt, n2, j, u01);
+            if (zo) load_nodes<T, J, J == 0>(row(2 * A + 1, 2 * B), x, cnt, n2, j, u10);
+            if (yo && zo) load_nodes<T, J, J == 0>(row(2 * A + 1, 2 * B + 1), x, cnt, n2, j, u11);
+        } else {
+            if (odd == 2)
+                load_vec<T, 2>(r00, k0);
+            else if (odd == 1)
+                k0[0] = *gmem(r00);
+            if (yo) load_nodes<T, 0, true>(r01 - x, x, cnt, m2, 0, u01);
+            if (zo) load_nodes<T, 0, true>(r10 - x, x, cnt, m2, 0, u10);
+            if (yo && zo) load_nodes<T, 0, true>(r11 - x, x, cnt, m2, 0, u11);
+        }
+        if (edge) {
+            const uint64_t at = (uint64_t)(x + 4) << j;
+            nx00 = gmem(c00)[at];
+            if (y2) nx01 = gmem(row(2 * A, 2 * B + 2))[at];
+            if (z2) nx10 = gmem(row(2 * A + 2, 2 * B))[at];
+            if (y2 && z2) nx11 = gmem(row(2 * A + 2, 2 * B + 2))[at];
+        }
+    }
+    if constexpr (FUSED) stride2_rows(coeffs + st.coef1, field, n1, n2, m0, m1, m2, A, B, x, live, has2, has4, e);
+    T p00[4], p01[4], p10[4], p11[4];
+    {
+        const T s00 = next_lane(e00[0]), s01 = next_lane(e01[0]), s10 = next_lane(e10[0]), s11 = next_lane(e11[0]);
+        refine_x(e00, edge ? nx00 : s00, has2, has4, p00);
+        refine_x(e01, edge ? nx01 : s01, has2, has4, p01);
+        refine_x(e10, edge ? nx10 : s10, has2, has4, p10);
+        refine_x(e11, edge ? nx11 : s11, has2, has4, p11);
+    }
+    if (!live || (FUSED && st.segs > 1 && lane == 63)) return;
+    // along y, then z: P of rows (even, odd), (odd, even) and (odd, odd)
+    T q01[4], q10[4], q11[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        q01[k] = y2 ? mean(p00[k], p01[k]) : p00[k];
+        const T far = y2 ? mean(p10[k], p11[k]) : p10[k];
+        q10[k] = z2 ? mean(p00[k], p10[k]) : p00[k];
+        q11[k] = z2 ? mean(q01[k], far) : q01[k];
     }
     if (DEC) {
-        wave_sync();
+        T o[4];
+        o[0] = e00[1] - p00[1], o[1] = e00[3] - p00[3];
+        if (odd == 2)
+            store_vec<T, 2>(r00, o);
+        else if (odd == 1)
+            *gmem(r00) = o[0];
+        auto put = [&](T* r, const T (&u)[4], const T (&q)[4]) {
+#pragma clang fp contract(off)
 #pragma unroll
-        for (uint32_t rr = 0; rr < kFineR; ++rr) {
-            if (!rlive[rr]) continue;
+            for (int k = 0; k < 4; ++k) o[k] = u[k] - q[k];
+            if (cnt == 4) {
+                store_vec<T, 4, true>(r, o);
+            } else {
 #pragma unroll
-            for (uint32_t k = 0; k < 4 * kFineG; ++k) {
-                const uint64_t i = lane + (uint64_t)k * kFineX;
-                if (i < wcoef[rr]) out[wbase[rr] + i] = w[rr][i];
+                for (uint32_t k = 0; k < 4; ++k)
+                    if (k < cnt) gmem(r)[k] = o[k];
             }
+        };
+        if (yo) put(r01, u01, q01);
+        if (zo) put(r10, u10, q10);
+        if (yo && zo) put(r11, u11, q11);
+    } else {
+        T* const f00 = row(2 * A, 2 * B);
+        T o[4] = {e00[0], k0[0] + p00[1], e00[2], k0[1] + p00[3]};
+        if (J == 0 && cnt == 4) {
+            // the even values again, unchanged: whole lines, where single odd
+            // values would be partial ones (readers of the row see the same bits)
+            store_vec<T, 4>(f00 + x, o);
+        } else {
+            // (FUSED: the even nodes may be step 1's)
+#pragma unroll
+            for (uint32_t k = FUSED ? 0 : 1; k < 4; k += FUSED ? 1 : 2)
+                if (k < cnt) gmem(f00)[(uint64_t)(x + k) << j] = o[k];
         }
+        auto put = [&](T* r, const T (&c)[4], const T (&q)[4]) {
+#pragma clang fp contract(off)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) o[k] = c[k] + q[k];
+            if (J == 0 && cnt == 4) {
+                store_vec<T, 4, true>(r + x, o);
+            } else {
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k)
+                    if (k < cnt) gmem(r)[(uint64_t)(x + k) << j] = o[k];
+            }
+        };
+        if (yo) put(row(2 * A, 2 * B + 1), u01, q01);
+        if (zo) put(row(2 * A + 1, 2 * B), u10, q10);
+        if (yo && zo) put(row(2 * A + 1, 2 * B + 1), u11, q11);
     }
 }
 
-template <typename T, bool DEC>
-__global__ __launch_bounds__(kStepX* kStepRows) void k_ml_step(const T* __restrict__ in, T* out, const T* field,
-                                                 uint32_t n1, uint32_t n2, uint32_t j, uint64_t m0)
+// workgroup -> its place in a launch of `blocks`, consecutive ones on one XCD
+// (the hardware deals workgroups to the XCDs in turn); ~0 past the end
+__device__ __forceinline__ uint32_t xcd_block(uint32_t id, uint32_t blocks)
 {
-    ml_step_row<T, DEC>(in, out, field, n1, n2, j, m0, blockIdx.z);
+    const uint32_t per = (blocks + kMlXcds - 1) / kMlXcds;
+    const uint32_t at = (id % kMlXcds) * per + id / kMlXcds;
+    return id / kMlXcds < per && at < blocks ? at : ~0u;
 }
 
-template <typename T, bool DEC>
-__global__ __launch_bounds__(kFineX* kFineRows) void k_ml_fine(const T* __restrict__ in, T* out, const T* field,
-                                                               uint32_t n0, uint32_t n1, uint32_t n2)
+template <typename T, bool DEC, int J, bool FUSED = false>
+__device__ __forceinline__ void ml_block(const MlStep& st, T* coeffs, T* field, uint32_t n1, uint32_t n2, uint32_t blk)
 {
-    __shared__ T xch[kFineRows][kFineR][kFineRun];
-    ml_fine_rows<T, DEC>(in, out, field, n0, n1, n2, blockIdx.z, xch[threadIdx.y]);
+    const uint32_t at = xcd_block(blk, st.blocks);
+    const uint32_t unit = at * (kMl / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t cells0 = (st.m0 + 1) >> 1;
+    if (at == ~0u || unit >= cells0 * st.groups * st.segs) return;
+    ml_unit<T, DEC, J, FUSED>(st, coeffs, field, n1, n2, unit);
 }
+
+// The decomposition: every step and the raw coarsest grid in one launch.
+struct MlSteps {
+    MlStep st[kMlMaxSteps];
+    uint32_t count;  // steps, finest first
+    uint32_t blk_raw;
+};
 
 // coarsest grid (stride 2^nsteps): DEC copies field -> level 0, else back
 template <typename T, bool DEC>
-__global__ __launch_bounds__(kMl) void k_ml_coarse(const T* __restrict__ in, T* __restrict__ out, uint32_t n1,
-                                                   uint32_t n2, uint32_t nsteps)
+__device__ __forceinline__ void ml_raw(T* coeffs, T* field, uint32_t n0, uint32_t n1, uint32_t n2, uint32_t nsteps,
+                                       uint64_t first, uint64_t stride)
 {
-    const uint64_t m2 = axis_nodes(n2, nsteps), m1 = axis_nodes(n1, nsteps);
-    const uint64_t b2 = (uint64_t)blockIdx.x * kMl + threadIdx.x;
-    if (b2 >= m2) return;
-    const uint64_t b1 = blockIdx.y, b0 = blockIdx.z;
-    const uint64_t f = ((b0 << nsteps) * n1 + (b1 << nsteps)) * n2 + (b2 << nsteps);
-    const uint64_t c = (b0 * m1 + b1) * m2 + b2;
-    if (DEC)
-        out[c] = in[f];
-    else
-        out[f] = in[c];
-}
-
-dim3 line_grid(uint64_t m0, uint64_t m1, uint64_t m2)
-{
-    return dim3((uint32_t)((m2 + kMl - 1) / kMl), (uint32_t)m1, (uint32_t)m0);
+    const uint64_t m0 = axis_nodes(n0, nsteps), m1 = axis_nodes(n1, nsteps), m2 = axis_nodes(n2, nsteps);
+    for (uint64_t c = first; c < m0 * m1 * m2; c += stride) {
+        const uint64_t b2 = c % m2, b1 = c / m2 % m1, b0 = c / m2 / m1;
+        const uint64_t f = ((b0 << nsteps) * n1 + (b1 << nsteps)) * n2 + (b2 << nsteps);
+        if (DEC)
+            gmem(coeffs)[c] = gmem(field)[f];
+        else
+            gmem(field)[f] = gmem(coeffs)[c];
+    }
 }
 
 template <typename T>
-hipError_t ml_run(bool dec, const T* in, uint32_t n0, uint32_t n1, uint32_t n2, uint32_t nsteps,
-                  const MlOffsets& off, T* out, hipStream_t s)
+__global__ __launch_bounds__(kMl) void k_ml_decompose(const MlSteps S, T* field, T* coeffs, uint32_t n0, uint32_t n1,
+                                                      uint32_t n2, uint32_t nsteps)
 {
-    auto m = [&](uint32_t n, uint32_t j) { return n == 0 ? 0ull : (uint64_t)((n - 1) >> j) + 1; };
-    const dim3 gc = line_grid(m(n0, nsteps), m(n1, nsteps), m(n2, nsteps));
-    if (dec)
-        hipLaunchKernelGGL((k_ml_coarse<T, true>), gc, dim3(kMl), 0, s, in, out + off.off[0], n1, n2, nsteps);
+    const uint32_t blk = blockIdx.x;
+    if (blk >= S.blk_raw) {
+        ml_raw<T, true>(coeffs, field, n0, n1, n2, nsteps, (uint64_t)(blk - S.blk_raw) * kMl + threadIdx.x,
+                        (uint64_t)(gridDim.x - S.blk_raw) * kMl);
+        return;
+    }
+    uint32_t i = 0;
+    while (i + 1 < S.count && blk >= S.st[i + 1].blk0) ++i;
+    const MlStep& st = S.st[i];
+    if (st.j == 0)
+        ml_block<T, true, 0>(st, coeffs, field, n1, n2, blk - st.blk0);
+    else if (st.j == 1)
+        ml_block<T, true, 1>(st, coeffs, field, n1, n2, blk - st.blk0);
     else
-        hipLaunchKernelGGL((k_ml_coarse<T, false>), gc, dim3(kMl), 0, s, in + off.off[0], out, n1, n2, nsteps);
-    hipError_t e = hipGetLastError();
-    // decomposition steps are independent (each reads only the field); the
-    // recomposition needs every coarser step first
-    const T* field = dec ? in : out;
-    const bool fine_vec = n2 % 4 == 0 && reinterpret_cast<uintptr_t>(field) % 16 == 0;
-    for (uint32_t l = 1; l <= nsteps && e == hipSuccess; ++l) {
+        ml_block<T, true, 2>(st, coeffs, field, n1, n2, blk - st.blk0);
+}
+
+// One step of the recomposition (FUSED: steps 1 and 0).
+template <typename T, int J, bool FUSED>
+__global__ __launch_bounds__(kMl) void k_ml_recompose(const MlStep st, T* coeffs, T* field, uint32_t n1, uint32_t n2)
+{
+    ml_block<T, false, J, FUSED>(st, coeffs, field, n1, n2, blockIdx.x);
+}
+
+template <typename T>
+__global__ __launch_bounds__(kMl) void k_ml_raw(T* coeffs, T* field, uint32_t n0, uint32_t n1, uint32_t n2,
+                                                uint32_t nsteps)
+{
+    ml_raw<T, false>(coeffs, field, n0, n1, n2, nsteps, (uint64_t)blockIdx.x * kMl + threadIdx.x,
+                     (uint64_t)gridDim.x * kMl);
+}
+
+// The recomposition's first steps, in one workgroup: the raw grid and `steps`
+// refinements of it (each of at most kMlSmall nodes) in LDS, the last one's
+// nodes then written to the field.  (A launch each, they cost about 5 us.)
+constexpr uint32_t kMlSmallThreads = 1024;
+constexpr uint32_t kMlSmallBytes = 32768;  // of one grid; two in LDS
+template <typename T>
+__global__ __launch_bounds__(kMlSmallThreads) void k_ml_recompose_small(const MlOffsets off, const T* coeffs, T* field,
+                                                                        uint32_t n0, uint32_t n1, uint32_t n2,
+                                                                        uint32_t nsteps, uint32_t steps)
+{
+#pragma clang fp contract(off)
+    constexpr uint32_t kMlSmall = kMlSmallBytes / sizeof(T);
+    __shared__ T s_g[2][kMlSmall];
+    const uint32_t tid = threadIdx.x;
+    uint32_t o0 = (uint32_t)axis_nodes(n0, nsteps), o1 = (uint32_t)axis_nodes(n1, nsteps),
+             o2 = (uint32_t)axis_nodes(n2, nsteps);
+    for (uint32_t i = tid; i < o0 * o1 * o2; i += kMlSmallThreads) s_g[0][i] = gmem(coeffs)[off.off[0] + i];
+    __syncthreads();
+    uint32_t cur = 0;
+    for (uint32_t l = 1; l <= steps; ++l) {
         const uint32_t j = nsteps - l;
-        if (j == 0 && fine_vec) {
-            const dim3 g((uint32_t)((n2 / 4 + kFineG * kFineX - 1) / (kFineG * kFineX)),
-                         (n1 + kFineRows * kFineR - 1) / (kFineRows * kFineR), n0);
-            if (dec)
-                hipLaunchKernelGGL((k_ml_fine<T, true>), g, dim3(kFineX, kFineRows), 0, s, in, out + off.off[l], in,
-                                   n0, n1, n2);
-            else
-                hipLaunchKernelGGL((k_ml_fine<T, false>), g, dim3(kFineX, kFineRows), 0, s, in + off.off[l], out,
-                                   out, n0, n1, n2);
-            e = hipGetLastError();
-            continue;
+        const uint32_t m0 = (uint32_t)axis_nodes(n0, j), m1 = (uint32_t)axis_nodes(n1, j),
+                       m2 = (uint32_t)axis_nodes(n2, j);
+        const uint32_t e1 = (m1 + 1) >> 1, e2 = (m2 + 1) >> 1;
+        const T* g = s_g[cur];
+        T* out = s_g[cur ^ 1];
+        const auto lv = gmem(coeffs + off.off[l]);
+        for (uint32_t i = tid; i < m0 * m1 * m2; i += kMlSmallThreads) {
+            const uint32_t c = i % m2, b = i / m2 % m1, a = i / m2 / m1;
+            const uint32_t z0 = a >> 1, y0 = b >> 1, x0 = c >> 1;
+            const bool zm = (a & 1) && z0 + 1 < o0, ym = (b & 1) && y0 + 1 < o1, xm = (c & 1) && x0 + 1 < o2;
+            auto line = [&](uint32_t z, uint32_t y) {
+                const T* r = g + (z * o1 + y) * o2 + x0;
+                return xm ? mean(r[0], r[1]) : r[0];
+            };
+            auto plane = [&](uint32_t z) { return ym ? mean(line(z, y0), line(z, y0 + 1)) : line(z, y0); };
+            T v = zm ? mean(plane(z0), plane(z0 + 1)) : plane(z0);
+            if ((a | b | c) & 1) {
+                uint32_t skipped = ((a + 1) >> 1) * e1 * e2;  // nodes of the coarser grid before this one
+                if (!(a & 1)) {
+                    skipped += ((b + 1) >> 1) * e2;
+                    if (!(b & 1)) skipped += (c + 1) >> 1;
+                }
+                v = lv[i - skipped] + v;
+            }
+            out[i] = v;
         }
-        const dim3 g((uint32_t)(((m(n2, j) + 1) / 2 + kStepX - 1) / kStepX),
-                     (uint32_t)((m(n1, j) + kStepRows - 1) / kStepRows), (uint32_t)m(n0, j));
-        if (dec)
-            hipLaunchKernelGGL((k_ml_step<T, true>), g, dim3(kStepX, kStepRows), 0, s, in, out + off.off[l], in, n1,
-                               n2, j, m(n0, j));
+        __syncthreads();
+        cur ^= 1;
+        o0 = m0, o1 = m1, o2 = m2;
+    }
+    const uint32_t j = nsteps - steps;
+    for (uint32_t i = tid; i < o0 * o1 * o2; i += kMlSmallThreads) {
+        const uint64_t c = i % o2, b = i / o2 % o1, a = i / o2 / o1;
+        gmem(field)[((a << j) * n1 + (b << j)) * n2 + (c << j)] = s_g[cur][i];
+    }
+}
+
+// host: the work of step j; false if its grid has no new nodes beyond the
+// coarser one (a step past the grid's extent: an empty level)
+bool plan_step(uint32_t n0, uint32_t n1, uint32_t n2, uint32_t j, uint64_t coef, MlStep& st, bool fused = false)
+{
+    st.m0 = (uint32_t)axis_nodes(n0, j);
+    st.m1 = (uint32_t)axis_nodes(n1, j);
+    st.m2 = (uint32_t)axis_nodes(n2, j);
+    st.j = j;
+    st.coef = coef;
+    st.coef1 = 0;
+    st.blk0 = 0;
+    if (st.m0 == 1 && st.m1 == 1 && st.m2 == 1) return false;
+    const uint32_t lanes = (st.m2 + 3) / 4;
+    st.segs = (st.m2 + kMlNodes - 1) / kMlNodes;
+    if (fused && st.segs > 1) st.segs = (st.m2 + kMlNodes - 5) / (kMlNodes - 4);
+    st.pack = 1;
+    while (st.segs == 1 && st.pack < 64 && lanes * st.pack * 2 <= 64) st.pack *= 2;
+    const uint32_t cells0 = (st.m0 + 1) >> 1, cells1 = (st.m1 + 1) >> 1;
+    st.groups = (cells1 + st.pack - 1) / st.pack;
+    const uint64_t units = (uint64_t)cells0 * st.groups * st.segs;
+    st.blocks = (uint32_t)((units + kMl / 64 - 1) / (kMl / 64));
+    return true;
+}
+
+// workgroups a step is launched with: whole rounds over the XCDs
+uint32_t launch_blocks(const MlStep& st) { return (st.blocks + kMlXcds - 1) / kMlXcds * kMlXcds; }
+
+uint32_t raw_blocks(uint64_t nodes)
+{
+    const uint64_t b = (nodes + kMl - 1) / kMl;
+    return (uint32_t)(b < 4096 ? b : 4096);
+}
+
+template <typename T>
+hipError_t ml_decompose(T* field, uint32_t n0, uint32_t n1, uint32_t n2, uint32_t nsteps, const MlOffsets& off,
+                        T* coeffs, hipStream_t s)
+{
+    MlSteps S{};
+    uint32_t blk = 0;
+    for (uint32_t j = 0; j < nsteps; ++j) {
+        MlStep& st = S.st[S.count];
+        if (!plan_step(n0, n1, n2, j, off.off[nsteps - j], st)) continue;
+        st.blk0 = blk;
+        blk += launch_blocks(st);
+        ++S.count;
+    }
+    S.blk_raw = blk;
+    blk += raw_blocks(axis_nodes(n0, nsteps) * axis_nodes(n1, nsteps) * axis_nodes(n2, nsteps));
+    hipLaunchKernelGGL(k_ml_decompose<T>, dim3(blk), dim3(kMl), 0, s, S, field, coeffs, n0, n1, n2, nsteps);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t ml_recompose(T* coeffs, uint32_t n0, uint32_t n1, uint32_t n2, uint32_t nsteps, const MlOffsets& off,
+                        T* field, hipStream_t s)
+{
+    auto nodes = [&](uint32_t j) { return axis_nodes(n0, j) * axis_nodes(n1, j) * axis_nodes(n2, j); };
+    // the raw grid and as many steps as fit one workgroup's LDS; a grid too
+    // large for it is copied by a launch of its own
+    uint32_t l = 0;
+    if (nodes(nsteps) <= kMlSmallBytes / sizeof(T)) {
+        while (l < nsteps && nodes(nsteps - l - 1) <= kMlSmallBytes / sizeof(T)) ++l;
+        hipLaunchKernelGGL(k_ml_recompose_small<T>, dim3(1), dim3(kMlSmallThreads), 0, s, off, coeffs, field, n0, n1, n2,
+                           nsteps, l);
+    } else {
+        hipLaunchKernelGGL(k_ml_raw<T>, dim3(raw_blocks(nodes(nsteps))), dim3(kMl), 0, s, coeffs, field, n0, n1, n2,
+                           nsteps);
+    }
+    hipError_t e = hipGetLastError();
+    while (l < nsteps && e == hipSuccess) {
+        const uint32_t j = nsteps - ++l;
+        const bool fused = j == 1;
+        MlStep st;
+        if (fused) ++l;
+        if (!plan_step(n0, n1, n2, fused ? 0 : j, off.off[l], st, fused)) continue;
+        st.coef1 = fused ? off.off[l - 1] : 0;
+        const dim3 g(launch_blocks(st));
+        if (fused)
+            hipLaunchKernelGGL((k_ml_recompose<T, 0, true>), g, dim3(kMl), 0, s, st, coeffs, field, n1, n2);
+        else if (j == 0)
+            hipLaunchKernelGGL((k_ml_recompose<T, 0, false>), g, dim3(kMl), 0, s, st, coeffs, field, n1, n2);
         else
-            hipLaunchKernelGGL((k_ml_step<T, false>), g, dim3(kStepX, kStepRows), 0, s, in + off.off[l], out, out,
-                               n1, n2, j, m(n0, j));
+            hipLaunchKernelGGL((k_ml_recompose<T, 2, false>), g, dim3(kMl), 0, s, st, coeffs, field, n1, n2);
         e = hipGetLastError();
     }
     return e;
@@ -408,20 +603,24 @@ hipError_t ml_run(bool dec, const T* in, uint32_t n0, uint32_t n1, uint32_t n2, 
 
 }  // namespace
 
+// (the kernels share one unit for both directions, so they take the input
+// unqualified; only the output is written)
 hipError_t launch_decompose(bool f64, const void* u, uint32_t n0, uint32_t n1, uint32_t n2, uint32_t nsteps,
                             const MlOffsets& off, void* out, hipStream_t s)
 {
     if ((uint64_t)n0 * n1 * n2 == 0) return hipSuccess;
-    return f64 ? ml_run(true, static_cast<const double*>(u), n0, n1, n2, nsteps, off, static_cast<double*>(out), s)
-               : ml_run(true, static_cast<const float*>(u), n0, n1, n2, nsteps, off, static_cast<float*>(out), s);
+    void* in = const_cast<void*>(u);
+    return f64 ? ml_decompose(static_cast<double*>(in), n0, n1, n2, nsteps, off, static_cast<double*>(out), s)
+               : ml_decompose(static_cast<float*>(in), n0, n1, n2, nsteps, off, static_cast<float*>(out), s);
 }
 
 hipError_t launch_recompose(bool f64, const void* c, uint32_t n0, uint32_t n1, uint32_t n2, uint32_t nsteps,
                             const MlOffsets& off, void* u, hipStream_t s)
 {
     if ((uint64_t)n0 * n1 * n2 == 0) return hipSuccess;
-    return f64 ? ml_run(false, static_cast<const double*>(c), n0, n1, n2, nsteps, off, static_cast<double*>(u), s)
-               : ml_run(false, static_cast<const float*>(c), n0, n1, n2, nsteps, off, static_cast<float*>(u), s);
+    void* in = const_cast<void*>(c);
+    return f64 ? ml_recompose(static_cast<double*>(in), n0, n1, n2, nsteps, off, static_cast<double*>(u), s)
+               : ml_recompose(static_cast<float*>(in), n0, n1, n2, nsteps, off, static_cast<float*>(u), s);
 }
 
 }  // namespace mdr
