@@ -153,6 +153,106 @@ mdr_status check_payload(const mdr_refactored* r, const LevelRec& L, uint32_t sl
     }
     return corrupt("unknown lossless method");
 }
+
+// One payload between its place in device memory and its place in the blob.
+struct Span {
+    uint8_t* dev;
+    uint64_t at;     // offset in the blob
+    uint64_t bytes;  // a multiple of 4, > 0
+    uint32_t crc;    // filled by move_payloads
+};
+
+// Payloads below this go through one staging buffer, laid out as in the blob:
+// a copy per run of them instead of one each (about 13 us whatever its size).
+constexpr uint64_t kStagedPayload = 256u << 10;
+
+// Every payload from the device into the blob (to_host) or the other way, and
+// its CRC-32 computed on the device: one pass over the bytes there, which also
+// moves the small ones between their places and the staging buffer.
+// hipErrorOutOfMemory (nothing done) when the staging does not fit.
+hipError_t move_payloads(mdr_context* ctx, std::vector<Span>& sp, uint8_t* blob, bool to_host)
+{
+    if (sp.empty()) return hipSuccess;
+    struct Run {
+        uint64_t at, bytes, stage;  // of the blob, and where it starts in the staging buffer
+    };
+    std::vector<Run> runs;
+    std::vector<CrcJob> jobs(sp.size());
+    uint64_t staged = 0, blocks = 0;
+    bool open = false;
+    for (size_t i = 0; i < sp.size(); ++i) {
+        CrcJob& j = jobs[i];
+        j = {reinterpret_cast<const uint32_t*>(sp[i].dev), nullptr, sp[i].bytes / 4, (uint32_t)blocks, 0};
+        blocks += (j.words + kCrcBlockWords - 1) / kCrcBlockWords;
+        if (sp[i].bytes >= kStagedPayload) {
+            open = false;
+            continue;
+        }
+        // a level's record lies between two levels' payloads: a run goes on over it
+        if (!open) runs.push_back({sp[i].at, 0, staged});
+        open = true;
+        runs.back().bytes = sp[i].at + sp[i].bytes - runs.back().at;
+        staged = align256(runs.back().stage + runs.back().bytes);
+    }
+    PoolBuf stage, meta;
+    hipError_t e = stage.alloc(ctx->pool, staged);
+    if (e != hipSuccess) return e;
+    const uint64_t o_out = align256(sizeof(CrcJob) * jobs.size());
+    e = meta.alloc(ctx->pool, o_out + 4 * blocks);
+    if (e != hipSuccess) return e;
+    uint8_t* st = static_cast<uint8_t*>(stage.p);
+    {
+        size_t r = 0;
+        for (size_t i = 0; i < sp.size(); ++i) {
+            if (sp[i].bytes >= kStagedPayload) continue;
+            while (sp[i].at >= runs[r].at + runs[r].bytes) ++r;
+            uint32_t* p = reinterpret_cast<uint32_t*>(st + runs[r].stage + (sp[i].at - runs[r].at));
+            if (to_host) {
+                jobs[i].dst = p;
+            } else {
+                jobs[i].dst = const_cast<uint32_t*>(jobs[i].src);
+                jobs[i].src = p;
+            }
+        }
+    }
+    auto big = [&]() -> hipError_t {
+        for (const Span& s : sp) {
+            if (s.bytes < kStagedPayload) continue;
+            const hipError_t ce = to_host ? hipMemcpy(blob + s.at, s.dev, s.bytes, hipMemcpyDeviceToHost)
+                                          : hipMemcpy(s.dev, blob + s.at, s.bytes, hipMemcpyHostToDevice);
+            if (ce != hipSuccess) return ce;
+        }
+        return hipSuccess;
+    };
+    auto small = [&]() -> hipError_t {
+        for (const Run& r : runs) {
+            const hipError_t ce = to_host ? hipMemcpy(blob + r.at, st + r.stage, r.bytes, hipMemcpyDeviceToHost)
+                                          : hipMemcpy(st + r.stage, blob + r.at, r.bytes, hipMemcpyHostToDevice);
+            if (ce != hipSuccess) return ce;
+        }
+        return hipSuccess;
+    };
+    e = hipMemcpy(meta.p, jobs.data(), sizeof(CrcJob) * jobs.size(), hipMemcpyHostToDevice);
+    if (e == hipSuccess && !to_host) e = big();
+    if (e == hipSuccess && !to_host) e = small();
+    uint32_t* out = reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(meta.p) + o_out);
+    (void)hipGetLastError();  // only this launch is checked
+    if (e == hipSuccess)
+        e = launch_crc_blocks(static_cast<const CrcJob*>(meta.p), (uint32_t)jobs.size(), (uint32_t)blocks, out, nullptr);
+    if (e == hipSuccess && to_host) e = big();
+    if (e == hipSuccess && to_host) e = small();
+    std::vector<uint32_t> rem(blocks);
+    if (e == hipSuccess) e = hipMemcpy(rem.data(), out, 4 * blocks, hipMemcpyDeviceToHost);
+    // the buffers go back to the pool: nothing may still use them
+    const hipError_t es = hipStreamSynchronize(nullptr);
+    if (e == hipSuccess) e = es;
+    if (e != hipSuccess) return e == hipErrorOutOfMemory ? hipErrorUnknown : e;
+    for (size_t i = 0; i < sp.size(); ++i) {
+        const uint64_t b1 = i + 1 < sp.size() ? jobs[i + 1].block0 : blocks;
+        sp[i].crc = crc_join(rem.data() + jobs[i].block0, (uint32_t)(b1 - jobs[i].block0), jobs[i].words);
+    }
+    return hipSuccess;
+}
 }  // namespace
 
 }  // namespace mdr
@@ -175,7 +275,7 @@ mdr_status mdr_serialize(const mdr_refactored* r, void* host, uint64_t cap, uint
     he = hipDeviceSynchronize();
     if (he != hipSuccess) return hip_fail(he, "hipDeviceSynchronize");
     uint8_t* out = static_cast<uint8_t*>(host);
-    std::memset(out, 0, total);
+    std::memset(out, 0, kHeader);
     const uint32_t B = r->B;
     put<uint32_t>(out, kMagic);
     out[4] = 1;
@@ -190,9 +290,34 @@ mdr_status mdr_serialize(const mdr_refactored* r, void* host, uint64_t cap, uint
     put<int32_t>(out + 32, r->prm.force_method);
     put<uint64_t>(out + 40, total);
     put<uint32_t>(out + 48, crc32(out, 48));
+    // payloads first (their CRCs go into the tables); they start behind each
+    // level's record, in slot order
+    std::vector<Span> sp;
     uint64_t pos = kHeader;
     for (const LevelRec& L : r->levels) {
+        pos += record_bytes(B);
+        for (uint32_t s = 0; s <= B; ++s) {
+            const UnitRec& u = L.units[s];
+            if (u.method == MDR_PLACEHOLDER) continue;
+            if (u.bytes) sp.push_back({u.dev, pos, u.bytes, 0});
+            pos += pad8(u.bytes);
+        }
+    }
+    he = move_payloads(r->ctx, sp, out, true);
+    if (he == hipErrorOutOfMemory) {  // no room for the staging: one by one, CRCs on the host
+        (void)hipGetLastError();
+        for (Span& x : sp) {
+            he = hipMemcpy(out + x.at, x.dev, x.bytes, hipMemcpyDeviceToHost);
+            if (he != hipSuccess) break;
+            x.crc = crc32(out + x.at, x.bytes);
+        }
+    }
+    if (he != hipSuccess) return hip_fail(he, "hipMemcpy(payload)");
+    pos = kHeader;
+    size_t next = 0;
+    for (const LevelRec& L : r->levels) {
         const uint64_t rec = pos;
+        std::memset(out + rec, 0, record_bytes(B));
         put<uint64_t>(out + pos, L.n);
         put<int32_t>(out + pos + 8, L.e);
         put<uint32_t>(out + pos + 12, 1 + B);
@@ -203,19 +328,16 @@ mdr_status mdr_serialize(const mdr_refactored* r, void* host, uint64_t cap, uint
         for (uint32_t k = 0; k <= B; ++k, pos += 8) put<double>(out + pos, L.E[k]);
         const uint64_t table = pos;
         pos += 16ull * (1 + B) + 8;
-        // payloads first (their CRCs go into the table)
         for (uint32_t s = 0; s <= B; ++s) {
             const UnitRec& u = L.units[s];
             uint8_t* ent = out + table + 16ull * s;
             ent[0] = (uint8_t)u.method;
-            uint64_t nb = u.method == MDR_PLACEHOLDER ? 0 : u.bytes;
+            const uint64_t nb = u.method == MDR_PLACEHOLDER ? 0 : u.bytes;
             put<uint64_t>(ent + 8, nb);
-            if (nb) {
-                he = hipMemcpy(out + pos, u.dev, nb, hipMemcpyDeviceToHost);
-                if (he != hipSuccess) return hip_fail(he, "hipMemcpy(payload)");
-            }
-            put<uint32_t>(ent + 4, crc32(out + pos, nb));
-            if (u.method != MDR_PLACEHOLDER) pos += pad8(nb);
+            put<uint32_t>(ent + 4, nb ? sp[next++].crc : 0);
+            if (u.method == MDR_PLACEHOLDER) continue;
+            if (pad8(nb) != nb) std::memset(out + pos + nb, 0, pad8(nb) - nb);
+            pos += pad8(nb);
         }
         const uint64_t rec_end = table + 16ull * (1 + B);
         put<uint32_t>(out + rec_end, crc32(out + rec, rec_end - rec));
@@ -258,21 +380,29 @@ mdr_status mdr_deserialize(mdr_context* ctx, const void* host, uint64_t bytes, m
     if (nlevels == 0 || nlevels > (bytes - kHeader) / record_bytes(B)) return corrupt("bad level count");
     R->levels.resize(nlevels);
 
-    // ---- parse and validate everything on the host first
+    // ---- parse and validate everything but the payloads' CRCs on the host first
     struct Src {
         uint32_t level, slot;
         const uint8_t* p;
+        uint32_t crc;  // as recorded
     };
     std::vector<Src> srcs;
+    // an error past some payloads: the first of them whose CRC is wrong comes before it
+    auto after_crcs = [&](mdr_status st) {
+        const std::string what = mdr_last_error();
+        for (const Src& sr : srcs)
+            if (crc32(sr.p, R->levels[sr.level].units[sr.slot].bytes) != sr.crc) return corrupt("payload CRC mismatch");
+        return fail(st, what);
+    };
     uint64_t pos = kHeader, rows_bytes = 0, pay_bytes = 0;
     for (uint32_t l = 0; l < nlevels; ++l) {
         LevelRec& L = R->levels[l];
-        if (bytes - pos < record_bytes(B)) return corrupt("truncated level record");
+        if (bytes - pos < record_bytes(B)) return after_crcs(corrupt("truncated level record"));
         const uint64_t rec = pos;
         L.n = get<uint64_t>(in + pos);
         L.e = get<int32_t>(in + pos + 8);
-        if (get<uint32_t>(in + pos + 12) != 1 + B) return corrupt("stream count mismatch");
-        if (L.n > 0xFFFFFFFFull) return corrupt("level too large");
+        if (get<uint32_t>(in + pos + 12) != 1 + B) return after_crcs(corrupt("stream count mismatch"));
+        if (L.n > 0xFFFFFFFFull) return after_crcs(corrupt("level too large"));
         L.nbd = R->G == 2 ? (uint32_t)(2 * ((L.n + 63) / 64)) : (uint32_t)((L.n + 31) / 32);
         L.vmin = get<double>(in + pos + 16);
         L.vmax = get<double>(in + pos + 24);
@@ -281,11 +411,11 @@ mdr_status mdr_deserialize(mdr_context* ctx, const void* host, uint64_t bytes, m
         L.E.resize(B + 1);
         for (uint32_t k = 0; k <= B; ++k, pos += 8) {
             L.E[k] = get<double>(in + pos);
-            if (!(L.E[k] >= 0.0) || std::isinf(L.E[k])) return corrupt("bad error table");
+            if (!(L.E[k] >= 0.0) || std::isinf(L.E[k])) return after_crcs(corrupt("bad error table"));
         }
         const uint64_t table = pos;
         const uint64_t rec_end = table + 16ull * (1 + B);
-        if (get<uint32_t>(in + rec_end) != crc32(in + rec, rec_end - rec)) return corrupt("level record CRC mismatch");
+        if (get<uint32_t>(in + rec_end) != crc32(in + rec, rec_end - rec)) return after_crcs(corrupt("level record CRC mismatch"));
         pos = rec_end + 8;
         for (uint32_t s = 0; s <= B; ++s) {
             const uint8_t* ent = in + table + 16ull * s;
@@ -294,39 +424,40 @@ mdr_status mdr_deserialize(mdr_context* ctx, const void* host, uint64_t bytes, m
             const uint64_t nb = get<uint64_t>(ent + 8);
             const bool leader = s == 0 || (s - 1) % m == 0;
             if (!leader) {
-                if (u.method != MDR_PLACEHOLDER || nb != 0) return corrupt("bad placeholder slot");
+                if (u.method != MDR_PLACEHOLDER || nb != 0) return after_crcs(corrupt("bad placeholder slot"));
                 continue;
             }
-            if (u.method > MDR_HUF) return corrupt("bad method in a leading slot");
-            if (nb > bytes - pos) return corrupt("payload runs past the end of the blob");
-            if (get<uint32_t>(ent + 4) != crc32(in + pos, nb)) return corrupt("payload CRC mismatch");
+            if (u.method > MDR_HUF) return after_crcs(corrupt("bad method in a leading slot"));
+            if (nb > bytes - pos) return after_crcs(corrupt("payload runs past the end of the blob"));
             u.bytes = nb;
+            srcs.push_back({l, s, in + pos, get<uint32_t>(ent + 4)});
             mdr_status st = check_payload(R.get(), L, s, in + pos, nb, u);
-            if (st) return st;
-            srcs.push_back({l, s, in + pos});
+            if (st) return after_crcs(st);
+            if (nb == 0 && srcs.back().crc != 0) return after_crcs(corrupt("payload CRC mismatch"));
             if (u.method != MDR_DC) pay_bytes += (nb + 255) & ~255ull;
             pos += pad8(nb);
-            if (pos > bytes) return corrupt("payload padding runs past the end of the blob");
+            if (pos > bytes) return after_crcs(corrupt("payload padding runs past the end of the blob"));
         }
         rows_bytes += (4ull * (B + 1) * L.nbd + 255) & ~255ull;
     }
-    if (pos != bytes) return corrupt("trailing bytes after the last level");
+    if (pos != bytes) return after_crcs(corrupt("trailing bytes after the last level"));
 
     // ---- upload: direct-copy payloads become plane rows, others go to the payload arena
     hipError_t he = hipSetDevice(ctx->device);
-    if (he != hipSuccess) return hip_fail(he, "hipSetDevice");
+    if (he != hipSuccess) return after_crcs(hip_fail(he, "hipSetDevice"));
     R->rows_arena = std::make_shared<PoolBuf>();
     R->payload_arena = std::make_shared<PoolBuf>();
     he = R->rows_arena->alloc(ctx->pool, rows_bytes);
-    if (he != hipSuccess) return hip_fail(he, "hipMalloc(planes)");
+    if (he != hipSuccess) return after_crcs(hip_fail(he, "hipMalloc(planes)"));
     he = R->payload_arena->alloc(ctx->pool, pay_bytes + 256);  // padded for the Huffman decoder's block reads
-    if (he != hipSuccess) return hip_fail(he, "hipMalloc(payloads)");
+    if (he != hipSuccess) return after_crcs(hip_fail(he, "hipMalloc(payloads)"));
     uint8_t* rb = static_cast<uint8_t*>(R->rows_arena->p);
     for (uint32_t l = 0; l < nlevels; ++l) {
         R->levels[l].rows = reinterpret_cast<uint32_t*>(rb);
         rb += (4ull * (B + 1) * R->levels[l].nbd + 255) & ~255ull;
     }
     uint8_t* pb = static_cast<uint8_t*>(R->payload_arena->p);
+    std::vector<Span> sp;
     for (const Src& sr : srcs) {
         LevelRec& L = R->levels[sr.level];
         UnitRec& u = L.units[sr.slot];
@@ -338,11 +469,22 @@ mdr_status mdr_deserialize(mdr_context* ctx, const void* host, uint64_t bytes, m
             u.dev = pb;
             pb += (u.bytes + 255) & ~255ull;
         }
-        if (u.bytes) {
-            he = hipMemcpy(u.dev, sr.p, u.bytes, hipMemcpyHostToDevice);
-            if (he != hipSuccess) return hip_fail(he, "hipMemcpy(payload)");
+        if (u.bytes) sp.push_back({u.dev, (uint64_t)(sr.p - in), u.bytes, sr.crc});
+    }
+    std::vector<uint32_t> want;
+    for (const Span& x : sp) want.push_back(x.crc);
+    he = move_payloads(ctx, sp, const_cast<uint8_t*>(in), false);
+    if (he == hipErrorOutOfMemory) {  // no room for the staging: CRCs on the host, one by one
+        (void)hipGetLastError();
+        for (Span& x : sp) {
+            x.crc = crc32(in + x.at, x.bytes);
+            he = hipMemcpy(x.dev, in + x.at, x.bytes, hipMemcpyHostToDevice);
+            if (he != hipSuccess) break;
         }
     }
+    if (he != hipSuccess) return after_crcs(hip_fail(he, "hipMemcpy(payload)"));
+    for (size_t i = 0; i < sp.size(); ++i)
+        if (sp[i].crc != want[i]) return corrupt("payload CRC mismatch");
     *out = R.release();
     return MDR_OK;
 }

@@ -262,6 +262,21 @@ constexpr uint32_t kL2MaxWg = 1024;       // workgroups of one launch, at most
 hipError_t launch_l2_tables(bool f64, const L2Level* levels, uint32_t nlevels, uint32_t B, double* part, double* out,
                             hipStream_t s);
 
+// ---- CRC-32 of payloads on the device (k_crc.hip)
+constexpr uint32_t kCrcBlockWords = 4096;  // 32-bit words a workgroup takes
+struct CrcJob {
+    const uint32_t* src;  // device, `words` 32-bit words
+    uint32_t* dst;        // copied here on the way (device; NULL: not copied)
+    uint64_t words;
+    uint32_t block0;      // first block of the job in the launch, ascending
+    uint32_t pad;
+};
+// out[b]: block b's remainder (ceil(words / kCrcBlockWords) blocks a job; jobs
+// of no words are left out by the caller)
+hipError_t launch_crc_blocks(const CrcJob* jobs, uint32_t njobs, uint32_t nblocks, uint32_t* out, hipStream_t s);
+// the CRC-32 of a payload of `words` words from its blocks' remainders (host)
+uint32_t crc_join(const uint32_t* block, uint32_t nblocks, uint64_t words);
+
 // ---- multilevel decomposition (k_multilevel.hip): field <-> coefficient levels
 constexpr uint32_t kMlMaxSteps = 30;
 struct MlOffsets {
