@@ -16,6 +16,10 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
+// the same with only the element's alignment (an access may start anywhere)
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(4)));
+
 template <typename T>
 __device__ __forceinline__ __attribute__((address_space(1))) T* gmem(T* p)
 {

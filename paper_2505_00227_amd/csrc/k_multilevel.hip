@@ -63,10 +63,6 @@ struct MlStep {
     uint32_t blocks;   // workgroups
 };
 
-// vectors that need only their element's alignment
-typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(4)));
-
 // NT: touched once, kept out of the way of the rows that neighbours share
 template <typename T, int N, bool NT = false>
 __device__ __forceinline__ void load_vec(const T* p, T* o)

@@ -61,6 +61,23 @@ __device__ __forceinline__ T wave_min(T v)
     return v;
 }
 
+__device__ __forceinline__ uint32_t lane_value(uint32_t v, int l)
+{
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, l);
+}
+__device__ __forceinline__ uint64_t lane_value(uint64_t v, int l)
+{
+    return ((uint64_t)lane_value((uint32_t)(v >> 32), l) << 32) | lane_value((uint32_t)v, l);
+}
+
+// orders LDS traffic between the lanes of one wavefront
+__device__ __forceinline__ void wave_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // ------------------------------------------------------------------ fills
 __global__ void k_fill_u32(uint32_t* p, uint64_t count, uint32_t value)
 {
@@ -853,24 +870,229 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
     encode_body<true, VEC, true>(job, blockIdx.x - job.wg_base);
 }
 
+// ------------------------------------------------------------------ bitplane encoder, small passes
+// The same results for a pass of few values, where the kernels above leave most
+// of the chip idle and a thread's 32 values, one after the other through 20 to
+// 70 KB of unrolled code fetched cold, are the pass's latency (33 us for 32768
+// f32 values, 74 us for 2^21 f64 ones).  Eight lanes share a block of 32 values,
+// four values each (a wavefront reads 1 or 2 KiB in one go); the bit transpose
+// exchanges words between the eight lanes in three rounds and finishes in
+// registers; the tile's rows go through LDS and are stored, counted and compared
+// by a rolled loop; and the error keys are taken directly: lane c walks the
+// wavefront's aligned values in LDS and keeps the largest fraction at cut c.
+// About twice the instructions a value of the kernels above, a sixth of the
+// code.
+template <bool F64>
+__global__ __launch_bounds__(kThreads) void k_encode_small(const EncodeJob* __restrict__ jobs,
+                                                           const uint32_t* __restrict__ wg_job)
+{
+    using T = std::conditional_t<F64, double, float>;
+    constexpr int G = F64 ? 2 : 1;
+    constexpr uint32_t kPad = kSmallTileBlocks + 1;
+    extern __shared__ uint32_t s_dyn[];  // [nunits][256] byte histograms, then three tiles' rows [B + 1][kPad]
+    __shared__ __align__(16) T s_y[kThreads / 64][256];
+    __shared__ unsigned long long s_key[kKeyStride];
+    __shared__ uint32_t s_trans[kMaxRows];
+    __shared__ uint32_t s_hoff[kMaxRows];
+    const EncodeJob& job = jobs[wg_job[blockIdx.x]];
+    const uint32_t wg = blockIdx.x - job.wg_base;
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, sub = lane & 7;
+    const uint32_t B = job.B, nbd = job.nbd, nunits = job.nunits;
+    const uint64_t n = job.n;
+    const uint64_t amax = job.stats->maxabs_bits;  // 0: every value is zero
+    const int e = amax == 0 ? 0 : (F64 ? frexp_exp_f64(amax) : frexp_exp_f32((uint32_t)amax));
+    const T* xg = static_cast<const T*>(job.x);
+    const auto rows = gmem(job.rows);
+    const auto recs = gmem(job.recs);
+    uint32_t* s_hist = s_dyn;
+    uint32_t* s_pl0 = s_dyn + nunits * 256;
+    const uint32_t pl_words = (B + 1) * kPad;
+    for (uint32_t i = tid; i < nunits * 256; i += kThreads) s_hist[i] = 0;
+    if (tid < kMaxRows) {
+        s_trans[tid] = 0;
+        s_hoff[tid] = job.hist_off[tid];
+    }
+    if (tid < kKeyStride) s_key[tid] = 0;
+    // exchange rounds with the lane 4, 2, 1 away: a lane keeps the bits of `keep`
+    // and takes the others from its partner's word turned by `turn`
+    const uint32_t keep16 = sub & 4 ? 0xFFFF0000u : 0x0000FFFFu, turn16 = 16;
+    const uint32_t keep8 = sub & 2 ? 0xFF00FF00u : 0x00FF00FFu, turn8 = sub & 2 ? 8 : 24;
+    const uint32_t keep4 = sub & 1 ? 0xF0F0F0F0u : 0x0F0F0F0Fu, turn4 = sub & 1 ? 4 : 28;
+    auto transpose = [&](uint32_t (&a)[4]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t o = (uint32_t)__builtin_amdgcn_ds_swizzle((int)a[i], 0x101F);  // lane ^ 4
+            a[i] = (a[i] & keep16) | (__builtin_amdgcn_alignbit(o, o, turn16) & ~keep16);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a[i], 0x4E, 0xF, 0xF, false);  // lane ^ 2
+            a[i] = (a[i] & keep8) | (__builtin_amdgcn_alignbit(o, o, turn8) & ~keep8);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)a[i], 0xB1, 0xF, 0xF, false);  // lane ^ 1
+            a[i] = (a[i] & keep4) | (__builtin_amdgcn_alignbit(o, o, turn4) & ~keep4);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t x = a[i], y = a[i + 2];
+            a[i] = (x & 0x33333333u) | ((y << 2) & 0xCCCCCCCCu);
+            a[i + 2] = ((x >> 2) & 0x33333333u) | (y & 0xCCCCCCCCu);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; i += 2) {
+            const uint32_t x = a[i], y = a[i + 1];
+            a[i] = (x & 0x55555555u) | ((y << 1) & 0xAAAAAAAAu);
+            a[i + 1] = ((x >> 1) & 0x55555555u) | (y & 0xAAAAAAAAu);
+        }
+    };
+    const uint32_t t0 = wg * job.tiles_per_wg, t1 = min(job.ntiles, t0 + job.tiles_per_wg);
+    const uint32_t nrows = B + 1;
+    // f32: two halves of a wavefront walk its values for the same 32 cuts
+    constexpr uint32_t kWalk = F64 ? 256 : 128;
+    const uint32_t cut = F64 ? lane : lane & 31;
+    T km = 0, small = 0;
+    __syncthreads();
+    for (uint32_t t = t0; t < t1; ++t) {
+        // three buffers: a wavefront may fill the next tile's while another
+        // still reads this one's and the last words of the one before
+        uint32_t* s_pl = s_pl0 + (t - t0) % 3 * pl_words;
+        const uint32_t* s_before = s_pl0 + (t - t0 + 2) % 3 * pl_words;
+        const uint32_t blk0 = t * kSmallTileBlocks, lblk = wave * 8 + (lane >> 3);
+        // ---- four values a lane, aligned: y = |x| 2^(B-e), mag = floor(y)
+        const uint64_t i0 = (uint64_t)(blk0 + lblk) * 32 + 4 * sub;
+        T v[4];
+        if (i0 + 4 <= n) {
+            constexpr int W = sizeof(T) / 4;  // 16-byte pieces of four values
+            uint32_t w[4 * W];
+#pragma unroll
+            for (int k = 0; k < W; ++k) {
+                const u32x4_any q = gmem(reinterpret_cast<const u32x4_any*>(xg + i0))[k];
+                w[4 * k] = q.x, w[4 * k + 1] = q.y, w[4 * k + 2] = q.z, w[4 * k + 3] = q.w;
+            }
+            __builtin_memcpy(v, w, sizeof w);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) v[j] = i0 + j < n ? gmem(xg)[i0 + j] : T(0);
+        }
+        uint32_t sgn = 0, lo[4], hi[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            T y;
+            if constexpr (F64) {
+                const uint64_t bits = (uint64_t)__double_as_longlong(v[j]);
+                sgn |= (uint32_t)(bits >> 63) << j;
+                const double a = __longlong_as_double((long long)(bits & 0x7FFFFFFFFFFFFFFFull));
+                y = __builtin_amdgcn_ldexp(a, (int)B - e);
+                if (y < 1.0) {  // mag = 0: below every cut
+                    small = a > small ? a : small;
+                    y = 0.0;
+                }
+                const double yh = __builtin_trunc(y * 0x1p-32);
+                hi[j] = (uint32_t)yh;
+                lo[j] = (uint32_t)(y - yh * 0x1p32);
+            } else {
+                const uint32_t bits = __float_as_uint(v[j]);
+                sgn |= (bits >> 31) << j;
+                const float a = __uint_as_float(bits & 0x7FFFFFFFu);
+                y = __builtin_amdgcn_ldexpf(a, (int)B - e);
+                if (y < 1.0f) {
+                    small = a > small ? a : small;
+                    y = 0.0f;
+                }
+                lo[j] = (uint32_t)y;
+                hi[j] = 0;
+            }
+            s_y[wave][(lane << 2) + j] = y;
+        }
+        // ---- the block's sign word, then the plane words of bits 4 sub .. 4 sub + 3 (and 32 more)
+        sgn <<= 4 * sub;
+        sgn |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)sgn, 0xB1, 0xF, 0xF, false);
+        sgn |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)sgn, 0x4E, 0xF, 0xF, false);
+        sgn |= (uint32_t)__builtin_amdgcn_ds_swizzle((int)sgn, 0x101F);
+        transpose(lo);
+        if constexpr (F64) transpose(hi);
+        if (sub == 0) s_pl[lblk] = sgn;
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) {
+            const uint32_t c = 4 * sub + i;  // bit c is row B - c
+            if (c < B) s_pl[(B - c) * kPad + lblk] = lo[i];
+            if (F64 && 32 + c < B) s_pl[(B - 32 - c) * kPad + lblk] = hi[i];
+        }
+        // ---- error keys: cut c = B - k (k = 1 .. B) of the wavefront's values
+        wave_fence();
+        if (cut < B) {
+            const T* yw = s_y[wave] + (F64 ? 0 : (lane >> 5) * kWalk);
+#pragma unroll 4
+            for (uint32_t i = 0; i < kWalk; i += 16 / sizeof(T)) {
+#pragma unroll
+                for (uint32_t q = 0; q < 16 / sizeof(T); ++q) {
+                    T key;
+                    if constexpr (F64) {
+                        key = __builtin_amdgcn_fract(__builtin_amdgcn_ldexp(yw[i + q], -(int)cut));
+                        km = __builtin_fmax(km, key);
+                    } else {
+                        key = __builtin_amdgcn_fractf(__builtin_amdgcn_ldexpf(yw[i + q], -(int)cut));
+                        km = __builtin_fmaxf(km, key);
+                    }
+                }
+            }
+        }
+        __syncthreads();  // the tile's rows are in LDS
+        // ---- per row: store, count the nonzero bytes, compare with the left neighbour
+        for (uint32_t i = tid; i < nrows * kSmallTileBlocks; i += kThreads) {
+            const uint32_t r = i / kSmallTileBlocks, b = i % kSmallTileBlocks, blk = blk0 + b;
+            const uint32_t* row = s_pl + r * kPad;
+            const uint32_t w = row[b];
+            const bool valid = blk < nbd;
+            bool flag = false;
+            if (valid) {
+                rows[(uint64_t)r * nbd + blk] = w;
+                uint32_t* h = s_hist + s_hoff[r];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const uint32_t byte = (w >> (8 * q)) & 0xFFu;
+                    if (byte) atomicAdd(&h[byte], 1u);
+                }
+                if (b % G == 0 && (b >= G || t > t0)) {  // a W-bit word against the one before it
+                    const uint32_t* left = b >= G ? row + b : s_before + r * kPad + kSmallTileBlocks;
+                    flag = w != left[-G];
+                    if (G == 2) flag = flag || row[b + 1] != left[-1];
+                }
+                // the range's first and last words, for the boundaries between ranges
+                if (t == t0 && b < G) recs[((uint64_t)wg * kMaxRows + r) * 2 * G + b] = w;
+                const uint32_t last = min(nbd, t1 * kSmallTileBlocks);
+                if (blk + G >= last) recs[((uint64_t)wg * kMaxRows + r) * 2 * G + G + (blk + G - last)] = w;
+            }
+            // a row's 32 words sit in one half of a wavefront
+            const unsigned long long bal = __ballot(flag);
+            const uint32_t cnt = (uint32_t)__popc((uint32_t)(bal >> (lane & 32)));
+            if (b == 0 && cnt) atomicAdd(&s_trans[r], cnt);
+        }
+    }
+    // ---- flush: the workgroup's results into the level totals (zeroed before the pass)
+    if (cut < B) {
+        if constexpr (F64)
+            atomicMax(&s_key[B - cut], (unsigned long long)__double_as_longlong(km));
+        else
+            atomicMax(&s_key[B - cut], (unsigned long long)__float_as_uint(km));
+    }
+    small = wave_max(small);
+    if (lane == 0) {
+        if constexpr (F64)
+            atomicMax(&s_key[kKeyStride - 1], (unsigned long long)__double_as_longlong(small));
+        else
+            atomicMax(&s_key[kKeyStride - 1], (unsigned long long)__float_as_uint(small));
+    }
+    __syncthreads();
+    if (tid < kKeyStride && s_key[tid]) atomicMax(&job.keys[tid], s_key[tid]);
+    for (uint32_t i = tid; i < nunits * 256; i += kThreads)
+        if (s_hist[i]) atomicAdd(&job.hist[i], s_hist[i]);
+    if (tid < kMaxRows && s_trans[tid]) atomicAdd(&job.trans[tid], s_trans[tid]);
+}
+
 // ------------------------------------------------------------------ hybrid selection
-__device__ __forceinline__ uint32_t lane_value(uint32_t v, int l)
-{
-    return (uint32_t)__builtin_amdgcn_readlane((int)v, l);
-}
-__device__ __forceinline__ uint64_t lane_value(uint64_t v, int l)
-{
-    return ((uint64_t)lane_value((uint32_t)(v >> 32), l) << 32) | lane_value((uint32_t)v, l);
-}
-
-// orders LDS traffic between the lanes of one wavefront
-__device__ __forceinline__ void wave_fence()
-{
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Working memory of one code construction (one wavefront).  W: the weights'
 // type, 32 bits while a unit has fewer than 2^30 bytes.
 template <typename W>
@@ -1436,8 +1658,18 @@ size_t encode_lds_bytes(uint32_t nunits, uint32_t B, uint32_t m, bool f64)
     return (size_t)nunits * 256 * sizeof(uint32_t) + planes;
 }
 
-hipError_t encode_set_lds(uint32_t nunits, uint32_t B, uint32_t m, bool f64)
+size_t encode_small_lds_bytes(uint32_t nunits, uint32_t B)
 {
+    return (size_t)nunits * 256 * sizeof(uint32_t) + 3ull * (B + 1) * (kSmallTileBlocks + 1) * sizeof(uint32_t);
+}
+
+hipError_t encode_set_lds(uint32_t nunits, uint32_t B, uint32_t m, bool f64, bool small)
+{
+    if (small) {
+        if (encode_small_lds_bytes(nunits, B) <= 48 * 1024) return hipSuccess;  // beside up to 10 KB of its own
+        const void* fn = f64 ? (const void*)k_encode_small<true> : (const void*)k_encode_small<false>;
+        return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)encode_small_lds_bytes(nunits, B));
+    }
     const size_t shmem = encode_lds_bytes(nunits, B, m, f64);
     if (shmem <= 64 * 1024) return hipSuccess;  // the fast path always fits
     const void* fns[2] = {f64 ? (const void*)k_encode_f64<true, false> : (const void*)k_encode_f32<true, false>,
@@ -1481,6 +1713,18 @@ hipError_t launch_encode_batch(const EncodeJob* jobs, const uint32_t* wg_job, ui
                 hipLaunchKernelGGL((k_encode_f32<false, false>), g, b, shmem, s, jobs, wg_job);
         }
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_encode_small(const EncodeJob* jobs, const uint32_t* wg_job, uint32_t grid, uint32_t nunits, uint32_t B,
+                               bool f64, hipStream_t s)
+{
+    if (grid == 0) return hipSuccess;
+    const size_t shmem = encode_small_lds_bytes(nunits, B);
+    if (f64)
+        hipLaunchKernelGGL(k_encode_small<true>, dim3(grid), dim3(kThreads), shmem, s, jobs, wg_job);
+    else
+        hipLaunchKernelGGL(k_encode_small<false>, dim3(grid), dim3(kThreads), shmem, s, jobs, wg_job);
     return hipGetLastError();
 }
 

@@ -10,6 +10,7 @@ namespace mdr {
 
 constexpr int kThreads = 256;     // threads per workgroup: 4 wavefronts of 64
 constexpr int kTileBlocks = 256;  // 32-value blocks per tile: one per thread
+constexpr uint32_t kSmallTileBlocks = 32;  // the same in a small pass: eight lanes a block
 constexpr int kMaxRows = 65;      // sign row + up to 64 magnitude planes
 constexpr int kMaxWgEncode = 768;  // three encoder workgroups per CU run at once
 constexpr int kLutBitsMax = 12;   // Huffman decode table: 2^lmax entries
@@ -137,9 +138,12 @@ hipError_t launch_stats_batch(const StatsJob* jobs, const uint32_t* wg_job, uint
                               bool vec, hipStream_t s);
 size_t encode_lds_bytes(uint32_t nunits, uint32_t B, uint32_t m, bool f64);
 // raise the encoder kernels' dynamic LDS limit (call outside graph capture)
-hipError_t encode_set_lds(uint32_t nunits, uint32_t B, uint32_t m, bool f64);
+hipError_t encode_set_lds(uint32_t nunits, uint32_t B, uint32_t m, bool f64, bool small);
 hipError_t launch_encode_batch(const EncodeJob* jobs, const uint32_t* wg_job, uint32_t grid,
                                uint32_t nunits, uint32_t B, uint32_t m, bool f64, bool vec, hipStream_t s);
+// the encoder of small passes: the jobs' tiles are kSmallTileBlocks blocks
+hipError_t launch_encode_small(const EncodeJob* jobs, const uint32_t* wg_job, uint32_t grid, uint32_t nunits, uint32_t B,
+                               bool f64, hipStream_t s);
 hipError_t launch_select_batch(const SelectParams& p, const SelectLevel* lv, uint32_t nlev,
                                hipStream_t s);
 

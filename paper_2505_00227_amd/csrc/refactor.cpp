@@ -96,6 +96,15 @@ uint64_t unit_cap(uint64_t S, const mdr_codec_params& prm, uint32_t G)
     return align256(cap);
 }
 
+// Passes of at most this many values take the small passes' encoder (eight
+// lanes a block, tiles of 32 blocks).  Its advantage is latency (32768 values:
+// 10 against 29 us in f32, 16 against 47 in f64; 2^20: 23 against 29, 39
+// against 44), its cost instructions a value (2^22: 43 against 37, 87 against 60).
+constexpr uint64_t kSmallPassValues = 1u << 20;
+// and aims for this many workgroups at most: each adds its histograms into the
+// level's with device atomics (2^20 f32 values: 23 us at 512, 43 at 1024)
+constexpr uint32_t kSmallTargetWg = 512;
+
 struct JobPlan {
     uint32_t var = 0, level = 0;
     const void* x = nullptr;
@@ -108,7 +117,8 @@ struct JobPlan {
 
 struct Layout {
     bool f64 = false;
-    bool wide = false;  // some unit has 2^30 bytes or more
+    bool wide = false;   // some unit has 2^30 bytes or more
+    bool small = false;  // few values: the small passes' encoder
     uint32_t G = 1, B = 0, m = 0, nunits = 0, J = 0, U = 0;
     std::vector<JobPlan> jobs;
     std::vector<uint32_t> var_first;  // first job of each variable, plus J
@@ -173,7 +183,13 @@ mdr_status make_layout(const mdr_context* ctx, const VarLevels* vars, uint32_t n
 
     // every encoder workgroup walks about the same number of tiles, so that a
     // batch of mixed level sizes finishes together
-    const uint64_t tpw_all = std::max<uint64_t>(1, ceil_div(total_tiles, std::max<uint32_t>(1, L.shape.enc_target_wg)));
+    L.small = total_values <= kSmallPassValues;
+    if (L.small) {
+        total_tiles = 0;
+        for (JobPlan& jp : L.jobs) total_tiles += jp.ntiles = (uint32_t)ceil_div(jp.nbd, kSmallTileBlocks);
+    }
+    const uint32_t target = L.small ? std::min(L.shape.enc_target_wg, kSmallTargetWg) : L.shape.enc_target_wg;
+    const uint64_t tpw_all = std::max<uint64_t>(1, ceil_div(total_tiles, std::max<uint32_t>(1, target)));
     uint64_t hist = 0, recs = 0, trans = 0;
     for (JobPlan& jp : L.jobs) {
         if (jp.ntiles) {
@@ -213,7 +229,7 @@ mdr_status make_layout(const mdr_context* ctx, const VarLevels* vars, uint32_t n
                      [&](uint32_t a, uint32_t b) { return L.jobs[a].tpw > L.jobs[b].tpw; });
     for (uint32_t j : order) {
         JobPlan& jp = L.jobs[j];
-        std::vector<uint32_t>& me = L.map[jp.vec ? 3 : 2];
+        std::vector<uint32_t>& me = L.map[jp.vec || L.small ? 3 : 2];
         jp.wg_base_e = (uint32_t)me.size();
         me.insert(me.end(), jp.grid_e, j);
     }
@@ -380,8 +396,12 @@ mdr_status enqueue_pass(mdr_context* ctx, const Layout& L, const mdr_codec_param
     }
     {
         StageTimer tm(tctx, MDR_STAGE_ENCODE, s);
-        MDR_HIP(launch_encode_batch(ej, map[2], (uint32_t)L.map[2].size(), L.nunits, L.B, L.m, L.f64, false, s));
-        MDR_HIP(launch_encode_batch(ej, map[3], (uint32_t)L.map[3].size(), L.nunits, L.B, L.m, L.f64, true, s));
+        if (L.small) {
+            MDR_HIP(launch_encode_small(ej, map[3], (uint32_t)L.map[3].size(), L.nunits, L.B, L.f64, s));
+        } else {
+            MDR_HIP(launch_encode_batch(ej, map[2], (uint32_t)L.map[2].size(), L.nunits, L.B, L.m, L.f64, false, s));
+            MDR_HIP(launch_encode_batch(ej, map[3], (uint32_t)L.map[3].size(), L.nunits, L.B, L.m, L.f64, true, s));
+        }
     }
     {
         StageTimer tm(tctx, MDR_STAGE_SELECT, s);
@@ -535,7 +555,7 @@ mdr_status refactor_batch(mdr_context* ctx, const VarLevels* vars, uint32_t nvar
         if (e != hipSuccess) return hip_fail(e, "hipMalloc(payloads)");
     }
     if (L.J == 0) return assemble(ctx, L, dtype, prm, nullptr, rows, pay, nvars, outs);
-    MDR_HIP(encode_set_lds(L.nunits, L.B, L.m, L.f64));
+    MDR_HIP(encode_set_lds(L.nunits, L.B, L.m, L.f64, L.small));
 
     // on failure after the first launch, let queued work end before the pool reuses the memory
     struct SyncOnFail {
