@@ -97,9 +97,8 @@ __global__ void k_copy_in(const uint64_t* src, uint64_t* __restrict__ dst, uint6
 }
 
 // Start of a refactor pass: the level statistics to their neutral values and
-// two regions of accumulators to zero, in one launch.
-__global__ void k_init_pass(LevelStats* st, uint32_t count, uint32_t* z0, uint64_t n0, uint32_t* z1,
-                            uint64_t n1)
+// a region of accumulators to zero, in one launch.
+__global__ void k_init_pass(LevelStats* st, uint32_t count, uint32_t* z, uint64_t n)
 {
     const uint64_t i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
@@ -108,8 +107,7 @@ __global__ void k_init_pass(LevelStats* st, uint32_t count, uint32_t* z0, uint64
         st[i0].maxkey = 0;
         st[i0].maxabs_bits = 0;
     }
-    for (uint64_t i = i0; i < n0; i += stride) z0[i] = 0;
-    for (uint64_t i = i0; i < n1; i += stride) z1[i] = 0;
+    for (uint64_t i = i0; i < n; i += stride) z[i] = 0;
 }
 
 // ------------------------------------------------------------------ level statistics
@@ -828,18 +826,19 @@ __device__ __forceinline__ void encode_body(const EncodeJob& job, const uint32_t
         }
     }
     __syncthreads();
-    // fold this workgroup's results into the level totals (zeroed before the
-    // pass): key maxima (nonnegative float bits order as integers), nonzero
-    // byte counts and transitions
+    // fold this workgroup's results into its copy of the level totals (zeroed
+    // before the pass): key maxima (nonnegative float bits order as integers),
+    // nonzero byte counts and transitions
+    const uint32_t copy = wg & (job.copies - 1);
     if (tid < kKeyStride) {
         const unsigned long long kv = F64 ? s_key64[tid] : (unsigned long long)s_key32[tid];
-        if (kv) atomicMax(&job.keys[tid], kv);
+        if (kv) atomicMax(&job.keys[copy * kKeyStride + tid], kv);
     }
     for (uint32_t i = tid; i < nunits * 256; i += kThreads) {
         const uint32_t hv = s_hist[FAST ? (i >> 8) * HSTRIDE + (i & 255u) : i];
-        if (hv) atomicAdd(&job.hist[i], hv);
+        if (hv) atomicAdd(&job.hist[copy * nunits * 256 + i], hv);
     }
-    if (tid < kMaxRows && s_trans[tid]) atomicAdd(&job.trans[tid], s_trans[tid]);
+    if (tid < kMaxRows && s_trans[tid]) atomicAdd(&job.trans[copy * kMaxRows + tid], s_trans[tid]);
 }
 
 // f32 fits five waves per SIMD (96 registers) with LDS to spare; f64 two
@@ -1071,7 +1070,7 @@ __global__ __launch_bounds__(kThreads) void k_encode_small(const EncodeJob* __re
             if (b == 0 && cnt) atomicAdd(&s_trans[r], cnt);
         }
     }
-    // ---- flush: the workgroup's results into the level totals (zeroed before the pass)
+    // ---- flush: the workgroup's results into its copy of the level totals (zeroed before the pass)
     if (cut < B) {
         if constexpr (F64)
             atomicMax(&s_key[B - cut], (unsigned long long)__double_as_longlong(km));
@@ -1086,10 +1085,11 @@ __global__ __launch_bounds__(kThreads) void k_encode_small(const EncodeJob* __re
             atomicMax(&s_key[kKeyStride - 1], (unsigned long long)__float_as_uint(small));
     }
     __syncthreads();
-    if (tid < kKeyStride && s_key[tid]) atomicMax(&job.keys[tid], s_key[tid]);
+    const uint32_t copy = wg & (job.copies - 1);
+    if (tid < kKeyStride && s_key[tid]) atomicMax(&job.keys[copy * kKeyStride + tid], s_key[tid]);
     for (uint32_t i = tid; i < nunits * 256; i += kThreads)
-        if (s_hist[i]) atomicAdd(&job.hist[i], s_hist[i]);
-    if (tid < kMaxRows && s_trans[tid]) atomicAdd(&job.trans[tid], s_trans[tid]);
+        if (s_hist[i]) atomicAdd(&job.hist[copy * nunits * 256 + i], s_hist[i]);
+    if (tid < kMaxRows && s_trans[tid]) atomicAdd(&job.trans[copy * kMaxRows + tid], s_trans[tid]);
 }
 
 // ------------------------------------------------------------------ hybrid selection
@@ -1387,15 +1387,30 @@ __global__ __launch_bounds__(NT) void k_select(const SelectParams job, const Sel
         return v;
     };
 
-    // ---- byte histogram (level totals from the encoder)
-    unsigned long long f = tid < 256 ? gmem(lv.hist)[(uint64_t)u * 256 + tid] : 0;
+    // ---- byte histogram (the copies of the level's totals from the encoder)
+    const uint32_t copies = lv.copies;
+    unsigned long long f = 0;
+    if (tid < 256) {
+        const auto h = gmem(lv.hist) + u * 256 + tid;
+#pragma unroll 8
+        for (uint32_t c = 0; c < copies; ++c) f += h[(uint64_t)c * job.nunits * 256];
+    }
+    if (u == 0 && tid < kKeyStride) {
+        unsigned long long k = 0;
+#pragma unroll 8
+        for (uint32_t c = 0; c < copies; ++c) {
+            const unsigned long long v = gmem(lv.keys)[c * kKeyStride + tid];
+            k = v > k ? v : k;
+        }
+        lv.keys_out[tid] = k;
+    }
 
     // ---- runs of equal W-bit words: transitions inside workgroup ranges (level
     // totals from the encoder), at range boundaries, and between consecutive
     // planes of the group
     const uint32_t nrow = r1 - r0;
     unsigned long long tr = 0;
-    for (uint32_t i = tid; i < nrow; i += NT) tr += gmem(lv.trans)[r0 + i];
+    for (uint32_t i = tid; i < nrow * copies; i += NT) tr += gmem(lv.trans)[i / nrow * kMaxRows + r0 + i % nrow];
     {
         // boundary i: first word(s) of range w = 1 + i / nrow against the last
         // of range w - 1, row r0 + i % nrow, eight boundaries a thread in
@@ -1622,13 +1637,11 @@ hipError_t launch_copy_in(void* dst, const void* host, uint64_t bytes, hipStream
     return hipGetLastError();
 }
 
-hipError_t launch_init_pass(LevelStats* st, uint32_t count, uint32_t* z0, uint64_t n0, uint32_t* z1,
-                            uint64_t n1, hipStream_t s)
+hipError_t launch_init_pass(LevelStats* st, uint32_t count, uint32_t* z, uint64_t n, hipStream_t s)
 {
-    const uint64_t most = std::max<uint64_t>(count, std::max(n0, n1));
+    const uint64_t most = std::max<uint64_t>(count, n);
     if (most == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_init_pass, dim3(grid_for(most, kThreads, 4096)), dim3(kThreads), 0, s, st, count, z0,
-                       n0, z1, n1);
+    hipLaunchKernelGGL(k_init_pass, dim3(grid_for(most, kThreads, 4096)), dim3(kThreads), 0, s, st, count, z, n);
     return hipGetLastError();
 }
 

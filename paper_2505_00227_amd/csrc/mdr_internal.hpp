@@ -68,11 +68,13 @@ struct EncodeJob {
     uint32_t wg_base;       // first workgroup of this job in its launch
     uint32_t* rows;         // [(B+1)][nbd]: row 0 sign, row 1+p plane p (bit B-1-p)
     LevelStats* stats;
-    // level totals, zeroed before the pass; workgroups add (max) theirs in
-    uint32_t* hist;         // [nunits][256] nonzero-byte counts
-    uint32_t* trans;        // [kMaxRows] word transitions inside workgroup ranges
-    unsigned long long* keys;  // [kKeyStride] max error keys (float/double bits), small
+    // level totals, zeroed before the pass; workgroup w adds (max) its results
+    // into copy w % copies of them
+    uint32_t* hist;         // [copies][nunits][256] nonzero-byte counts
+    uint32_t* trans;        // [copies][kMaxRows] word transitions inside workgroup ranges
+    unsigned long long* keys;  // [copies][kKeyStride] max error keys (float/double bits), small
     uint32_t* recs;         // [grid][kMaxRows][2G] first / last words of each workgroup's range
+    uint32_t copies;        // a power of two
     uint16_t hist_off[kMaxRows];   // row r -> its unit's histogram offset (unit * 256)
 };
 
@@ -80,9 +82,11 @@ struct EncodeJob {
 struct SelectLevel {
     uint64_t nbd;           // 0 for an empty level
     uint32_t grid;          // workgroups of that level's encode job
-    uint32_t pad;
-    const uint32_t* hist;   // [nunits][256] level totals from the encoder
-    const uint32_t* trans;  // [kMaxRows] level totals from the encoder
+    uint32_t copies;        // of the level totals
+    const uint32_t* hist;   // [copies][nunits][256] level totals from the encoder
+    const uint32_t* trans;  // [copies][kMaxRows] level totals from the encoder
+    const unsigned long long* keys;  // [copies][kKeyStride]
+    unsigned long long* keys_out;    // [kKeyStride] their maxima (unit 0's workgroup)
     const uint32_t* recs;   // [grid][kMaxRows][2G]
     UnitInfo* units;        // [nunits]
     uint8_t* lens;          // [nunits][256]
@@ -130,9 +134,8 @@ hipError_t launch_fill_u32(uint32_t* p, uint64_t count, uint32_t value, hipStrea
 // behind it start without waiting on another engine; under capture the kernel
 // reads the host memory at every replay
 hipError_t launch_copy_in(void* dst, const void* host, uint64_t bytes, hipStream_t s);
-// level statistics [count] to their neutral values, z0[n0] and z1[n1] to zero
-hipError_t launch_init_pass(LevelStats* st, uint32_t count, uint32_t* z0, uint64_t n0, uint32_t* z1,
-                            uint64_t n1, hipStream_t s);
+// level statistics [count] to their neutral values, z[n] to zero
+hipError_t launch_init_pass(LevelStats* st, uint32_t count, uint32_t* z, uint64_t n, hipStream_t s);
 // statistics of every job; wg_job maps each of `grid` workgroups to its job
 hipError_t launch_stats_batch(const StatsJob* jobs, const uint32_t* wg_job, uint32_t grid, bool f64,
                               bool vec, hipStream_t s);

@@ -97,13 +97,21 @@ uint64_t unit_cap(uint64_t S, const mdr_codec_params& prm, uint32_t G)
 }
 
 // Passes of at most this many values take the small passes' encoder (eight
-// lanes a block, tiles of 32 blocks).  Its advantage is latency (32768 values:
-// 10 against 29 us in f32, 16 against 47 in f64; 2^20: 23 against 29, 39
-// against 44), its cost instructions a value (2^22: 43 against 37, 87 against 60).
-constexpr uint64_t kSmallPassValues = 1u << 20;
-// and aims for this many workgroups at most: each adds its histograms into the
-// level's with device atomics (2^20 f32 values: 23 us at 512, 43 at 1024)
-constexpr uint32_t kSmallTargetWg = 512;
+// lanes a block, tiles of 32 blocks).  Its advantage is latency (2^18 values: 11
+// against 28 us in f32, 18 against 44 in f64; 2^21 f32 values 22 against 30,
+// 2^20 f64 ones 30 against 44), its cost instructions a value (2^22: 33 against
+// 35, a unit per plane 46 against 46; f64 78 against 57).
+constexpr uint64_t small_pass_values(bool f64) { return f64 ? 1u << 20 : 1u << 21; }
+// and aims for this many workgroups at most: each ends by adding its
+// histograms into the level's, a KiB a unit (2^21 f32 values in 9 units: 22 us
+// at 1024, 25 at 512; in 33 units: 43 and 33; 2^20 f64 in 17: 36 and 30)
+constexpr uint32_t small_target_wg(uint32_t nunits) { return nunits <= 12 ? 1024 : 512; }
+
+// A level's totals are kept in this many copies, a power of two, one per
+// kWgPerCopy of its encoder workgroups: device atomics on one cache line take
+// turns, about 40 ns each (2^20 f32 values, 512 workgroups: 22.5 us with one
+// copy, 17.1 with eight; more copies cost the selection what they save).
+constexpr uint32_t kTotalCopiesMax = 8, kWgPerCopy = 64;
 
 struct JobPlan {
     uint32_t var = 0, level = 0;
@@ -112,7 +120,8 @@ struct JobPlan {
     uint32_t nbd = 0, ntiles = 0, tpw = 0, grid_e = 0, grid_s = 0;
     uint32_t wg_base_s = 0, wg_base_e = 0;
     bool vec = false;
-    uint64_t rows_off = 0, hist_off = 0, recs_off = 0, trans_off = 0;
+    uint64_t rows_off = 0, hist_off = 0, recs_off = 0, trans_off = 0, keys_off = 0;
+    uint32_t copies = 1;
 };
 
 struct Layout {
@@ -126,7 +135,7 @@ struct Layout {
     // workspace: metadata block (read back in one copy), then scratch
     uint64_t o_stats = 0, o_keys = 0, o_units = 0, o_payoff = 0, o_ubytes = 0, o_counts = 0,
              meta_bytes = 0;
-    uint64_t o_lens = 0, o_codes = 0, o_hist = 0, o_recs = 0, o_trans = 0, o_tot_end = 0, o_cbase = 0,
+    uint64_t o_lens = 0, o_codes = 0, o_hist = 0, o_recs = 0, o_trans = 0, o_kcopy = 0, o_tot_end = 0, o_cbase = 0,
              o_tbase = 0, o_cwords = 0, o_truns = 0, o_scan = 0, o_desc = 0, ws_bytes = 0;
     // descriptor (uploaded before every pass)
     uint64_t d_sjobs = 0, d_ejobs = 0, d_slev = 0, d_largs = 0, d_map[4] = {}, desc_bytes = 0;
@@ -183,14 +192,14 @@ mdr_status make_layout(const mdr_context* ctx, const VarLevels* vars, uint32_t n
 
     // every encoder workgroup walks about the same number of tiles, so that a
     // batch of mixed level sizes finishes together
-    L.small = total_values <= kSmallPassValues;
+    L.small = total_values <= small_pass_values(L.f64);
     if (L.small) {
         total_tiles = 0;
         for (JobPlan& jp : L.jobs) total_tiles += jp.ntiles = (uint32_t)ceil_div(jp.nbd, kSmallTileBlocks);
     }
-    const uint32_t target = L.small ? std::min(L.shape.enc_target_wg, kSmallTargetWg) : L.shape.enc_target_wg;
+    const uint32_t target = L.small ? std::min(L.shape.enc_target_wg, small_target_wg(L.nunits)) : L.shape.enc_target_wg;
     const uint64_t tpw_all = std::max<uint64_t>(1, ceil_div(total_tiles, std::max<uint32_t>(1, target)));
-    uint64_t hist = 0, recs = 0, trans = 0;
+    uint64_t hist = 0, recs = 0, trans = 0, keys = 0;
     for (JobPlan& jp : L.jobs) {
         if (jp.ntiles) {
             jp.tpw = (uint32_t)std::min<uint64_t>(jp.ntiles, tpw_all);
@@ -200,11 +209,14 @@ mdr_status make_layout(const mdr_context* ctx, const VarLevels* vars, uint32_t n
         jp.rows_off = L.rows_bytes;
         L.rows_bytes += align256(4ull * (B + 1) * jp.nbd);
         jp.hist_off = hist;
-        hist += 4ull * L.nunits * 256;
+        while (jp.copies < kTotalCopiesMax && jp.grid_e > jp.copies * kWgPerCopy) jp.copies *= 2;
+        hist += 4ull * L.nunits * 256 * jp.copies;
         jp.recs_off = recs;
         recs += align256(4ull * jp.grid_e * kMaxRows * 2 * L.G);
         jp.trans_off = trans;
-        trans += 4ull * kMaxRows;
+        trans += 4ull * kMaxRows * jp.copies;
+        jp.keys_off = keys;
+        keys += 8ull * kKeyStride * jp.copies;
         for (uint32_t i = 0; i < L.nunits; ++i) {
             const uint32_t r0 = i == 0 ? 0 : 1 + (i - 1) * L.m;
             const uint32_t r1 = i == 0 ? 1 : std::min(B + 1, r0 + L.m);
@@ -251,8 +263,9 @@ mdr_status make_layout(const mdr_context* ctx, const VarLevels* vars, uint32_t n
     L.o_lens = take(256ull * L.U);
     L.o_codes = take(1024ull * L.U);
     L.o_recs = take(recs);
-    L.o_hist = take(hist);  // level totals: histograms, then transitions, zeroed per pass
+    L.o_hist = take(hist);  // level totals: histograms, transitions, keys; zeroed per pass
     L.o_trans = take(trans);
+    L.o_kcopy = take(keys);
     L.o_tot_end = o;
     L.o_cbase = take(4ull * (L.U + 1));
     L.o_tbase = take(4ull * (L.U + 1));
@@ -330,7 +343,8 @@ void fill_descriptor(const Layout& L, const mdr_codec_params& prm, uint8_t* ws, 
         e.hist = reinterpret_cast<uint32_t*>(ws + L.o_hist + jp.hist_off);
         e.trans = reinterpret_cast<uint32_t*>(ws + L.o_trans + jp.trans_off);
         e.recs = reinterpret_cast<uint32_t*>(ws + L.o_recs + jp.recs_off);
-        e.keys = reinterpret_cast<unsigned long long*>(ws + L.o_keys) + (uint64_t)j * kKeyStride;
+        e.keys = reinterpret_cast<unsigned long long*>(ws + L.o_kcopy + jp.keys_off);
+        e.copies = jp.copies;
         for (uint32_t r = 0; r <= L.B; ++r)
             e.hist_off[r] = (uint16_t)((r == 0 ? 0 : 1 + (r - 1) / L.m) * 256);
 
@@ -339,6 +353,9 @@ void fill_descriptor(const Layout& L, const mdr_codec_params& prm, uint8_t* ws, 
         s.grid = jp.grid_e;
         s.hist = e.hist;
         s.trans = e.trans;
+        s.copies = jp.copies;
+        s.keys = e.keys;
+        s.keys_out = reinterpret_cast<unsigned long long*>(ws + L.o_keys) + (uint64_t)j * kKeyStride;
         s.recs = e.recs;
         s.units = reinterpret_cast<UnitInfo*>(ws + L.o_units) + (uint64_t)j * L.nunits;
         s.lens = ws + L.o_lens + (uint64_t)j * L.nunits * 256;
@@ -389,7 +406,6 @@ mdr_status enqueue_pass(mdr_context* ctx, const Layout& L, const mdr_codec_param
         // the encoder adds its workgroups' histograms, transitions and key
         // maxima into zeroed level totals (a kernel: safe under capture)
         MDR_HIP(launch_init_pass(reinterpret_cast<LevelStats*>(ws + L.o_stats), L.J,
-                                 reinterpret_cast<uint32_t*>(ws + L.o_keys), 2ull * kKeyStride * L.J,
                                  reinterpret_cast<uint32_t*>(ws + L.o_hist), (L.o_tot_end - L.o_hist) / 4, s));
         MDR_HIP(launch_stats_batch(sj, map[0], (uint32_t)L.map[0].size(), L.f64, false, s));
         MDR_HIP(launch_stats_batch(sj, map[1], (uint32_t)L.map[1].size(), L.f64, true, s));
