@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kThreads) void k_scan_add(uint32_t* out, uint64_t n
 // Every kernel below has a fixed grid and reads its amount of work from device
 // memory (counts[]), so the whole stage runs without the host learning which
 // units chose which method.
-constexpr uint64_t kHufHeader = 8 + 256;
+constexpr uint64_t kHufHeader = kHufHeaderBytes;
 
 __device__ __forceinline__ uint64_t wave_incl_scan64(uint64_t v, uint32_t lane)
 {
@@ -137,34 +137,44 @@ __device__ __forceinline__ const uint32_t* unit_rows(const LosslessArgs& A, uint
     return job.rows + (uint64_t)r0 * job.nbd;
 }
 
+// Threads of the two one-workgroup kernels take consecutive units each, from
+// compact arrays, four units' loads at a time: one scan for all of them (1024
+// units a scan, from the 48-byte unit records, a batch of 11520 took 36 and 43 us).
+constexpr uint32_t kUnitFly = 4;
+
 __global__ __launch_bounds__(1024) void k_unit_plan(const LosslessArgs* __restrict__ Ap)
 {
     __shared__ uint64_t s_wave[16];
     const LosslessArgs& A = *Ap;
-    uint64_t carry_c = 0, carry_t = 0;
-    for (uint32_t b = 0; b < A.U; b += 1024) {
-        const uint32_t u = b + threadIdx.x;
-        uint64_t hc = 0, rt = 0;
-        if (u < A.U) {
-            const UnitInfo& ui = A.units[u];
-            if (ui.method == 2) hc = ui.nchunks;
-            if (ui.method == 1) rt = (ui.S / (4ull * A.G) + kRleTileWords - 1) / kRleTileWords;
+    const uint32_t per = (A.U + 1023) / 1024, u0 = min(threadIdx.x * per, A.U), u1 = min(u0 + per, A.U);
+    const auto work = gmem(A.work);
+    uint64_t sum = 0;  // chunks (low half) and run-length tiles (high half) of the thread's units
+    for (uint32_t u = u0; u < u1; u += kUnitFly) {
+        uint64_t w[kUnitFly];
+#pragma unroll
+        for (uint32_t k = 0; k < kUnitFly; ++k) w[k] = work[min(u + k, u1 - 1)];
+#pragma unroll
+        for (uint32_t k = 0; k < kUnitFly; ++k) sum += u + k < u1 ? w[k] & kWorkCounts : 0;
+    }
+    uint64_t at;
+    const uint64_t total = block_scan64<1024>(sum, s_wave, at);
+    for (uint32_t u = u0; u < u1; u += kUnitFly) {
+        uint64_t w[kUnitFly];
+#pragma unroll
+        for (uint32_t k = 0; k < kUnitFly; ++k) w[k] = work[min(u + k, u1 - 1)];
+#pragma unroll
+        for (uint32_t k = 0; k < kUnitFly; ++k) {
+            if (u + k >= u1) break;
+            gmem(A.chunk_base)[u + k] = (uint32_t)at;
+            gmem(A.tile_base)[u + k] = (uint32_t)(at >> 32);
+            at += w[k] & kWorkCounts;
         }
-        uint64_t ec, et;
-        const uint64_t tc = block_scan64<1024>(hc, s_wave, ec);
-        const uint64_t tt = block_scan64<1024>(rt, s_wave, et);
-        if (u < A.U) {
-            A.chunk_base[u] = (uint32_t)(carry_c + ec);
-            A.tile_base[u] = (uint32_t)(carry_t + et);
-        }
-        carry_c += tc;
-        carry_t += tt;
     }
     if (threadIdx.x == 0) {
-        A.chunk_base[A.U] = (uint32_t)carry_c;
-        A.tile_base[A.U] = (uint32_t)carry_t;
-        A.counts[0] = (uint32_t)carry_c;
-        A.counts[1] = (uint32_t)carry_t;
+        A.chunk_base[A.U] = (uint32_t)total;
+        A.tile_base[A.U] = (uint32_t)(total >> 32);
+        A.counts[0] = (uint32_t)total;
+        A.counts[1] = (uint32_t)(total >> 32);
         A.counts[2] = 0;
     }
 }
@@ -236,36 +246,40 @@ __device__ __forceinline__ bool huf_load_batch(const uint32_t* g, uint64_t wb, u
     return false;
 }
 
-__device__ __forceinline__ void wave_share(uint32_t total, uint32_t& c0, uint32_t& c1)
+// chunks a wavefront takes of `total`, and the tiles a workgroup takes: the
+// counting and the writing launch share them out alike (kPersistWg workgroups)
+constexpr uint32_t kPersistWaves = kPersistWg * (kThreads / 64);
+__host__ __device__ __forceinline__ uint32_t chunk_share(uint32_t total)
 {
-    const uint32_t nw = gridDim.x * (kThreads / 64), w = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
-    const uint32_t per = (total + nw - 1) / nw;
+    return (total + kPersistWaves - 1) / kPersistWaves;
+}
+__host__ __device__ __forceinline__ uint32_t tile_share(uint32_t total) { return (total + kPersistWg - 1) / kPersistWg; }
+
+__device__ __forceinline__ void wave_share(uint32_t total, uint32_t& w, uint32_t& c0, uint32_t& c1)
+{
+    w = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6);
+    const uint32_t per = chunk_share(total);
     c0 = min(w * per, total);
     c1 = min(c0 + per, total);
 }
 
-__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-// code bits of every Huffman chunk -> chunk_words[c] (words): per lane the
-// code lengths of its sixteen symbols, summed over each chunk's lanes by a
-// segmented scan (chunks over several loads carry their sum across them)
+// Words of every wavefront's share of the Huffman chunks -> wave_part, and where
+// each unit's first chunk starts and its last one ends within its wavefront's
+// share: per lane the code lengths of its sixteen symbols, summed over each
+// chunk's lanes by a segmented scan (chunks over several loads carry their sum
+// across them).  The writing launch walks the same shares, so these are all the
+// offsets it needs: no word count is kept per chunk.
 __device__ __forceinline__ void huf_count_body(const LosslessArgs& A)
 {
     __shared__ uint32_t s_len[kThreads / 64][256];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t total = A.counts[0];
-    if (blockIdx.x == 0 && tid == 0) A.chunk_words[total] = 0;
     uint32_t* L = s_len[wave];
     const uint32_t cw = A.huf_chunk / 4, wpl = A.huf_chunk / 256;  // words, 256-symbol groups per chunk
     const uint32_t cpb = 4 * kHufLoads / wpl;                       // chunks per batch
     const uint32_t seg = min(64u, 16 * wpl), lpc = wpl > 4 ? wpl / 4 : 1;  // lanes a chunk takes of a load; loads a chunk
-    uint32_t c0, c1;
-    wave_share(total, c0, c1);
+    uint32_t wv, c0, c1, acc = 0;  // acc: words of the share so far
+    wave_share(total, wv, c0, c1);
     uint32_t u = 0, cb_lo = 1, cb_hi = 0;  // chunks [cb_lo, cb_hi) belong to unit u
     uint64_t nwu = 0;                      // words of unit u
     for (uint32_t c = c0; c < c1;) {
@@ -279,6 +293,7 @@ __device__ __forceinline__ void huf_count_body(const LosslessArgs& A)
             __builtin_amdgcn_wave_barrier();
             __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         }
+        if (c == cb_lo && lane == 0) A.huf_lo[u] = acc;
         const uint32_t nbt = min(cpb, min(c1, cb_hi) - c);  // chunks in this batch
         HufBatch hb;
         huf_load_batch(unit_rows(A, u), (uint64_t)(c - cb_lo) * cw, nbt * cw, nwu, lane, hb);
@@ -294,20 +309,20 @@ __device__ __forceinline__ void huf_count_body(const LosslessArgs& A)
             }
             const uint32_t x = seg_incl_scan(T, seg);
             if (lpc == 1) {
-                const uint32_t cj = (r * 256 + 4 * lane) / cw;
-                if ((lane & (seg - 1)) == seg - 1 && cj < nbt) A.chunk_words[c + cj] = (x + 31) / 32;
+                for (uint32_t k = 0; k < 64 / seg; ++k)  // no chunk: no bits
+                    acc += ((uint32_t)__builtin_amdgcn_readlane((int)x, (int)(k * seg + seg - 1)) + 31) / 32;
             } else {
                 if (r % lpc == 0) run = 0;
                 run += (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
-                const uint32_t cj = r / lpc;
-                if (r % lpc == lpc - 1 && lane == 0 && cj < nbt) A.chunk_words[c + cj] = (run + 31) / 32;
+                if (r % lpc == lpc - 1) acc += (run + 31) / 32;
             }
         }
+        if (c + nbt == cb_hi && lane == 0) A.huf_hi[u] = acc;
         c += nbt;
     }
+    if (lane == 0) A.wave_part[wv] = acc;
 }
 
-// runs starting inside each run-length tile -> tile_runs[t]; one workgroup per tile
 __device__ __forceinline__ bool word_ne(const uint32_t* g, uint64_t i, uint64_t j, uint32_t G)
 {
     bool ne = g[i * G] != g[j * G];
@@ -315,36 +330,49 @@ __device__ __forceinline__ bool word_ne(const uint32_t* g, uint64_t i, uint64_t 
     return ne;
 }
 
+// A workgroup takes a contiguous share of the tiles: its runs -> tile_part, the
+// runs before each unit's first tile within the share -> rle_lo, and every
+// tile's first run start -> tile_first (kNoStart: none starts in it).
+constexpr uint32_t kNoStart = ~0u;
 __device__ __forceinline__ void rle_count_body(const LosslessArgs& A)
 {
-    __shared__ uint32_t s_red[kThreads / 64];
+    __shared__ uint32_t s_cnt[kThreads / 64], s_first[kThreads / 64];
     const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t total = A.counts[1];
-    if (blockIdx.x == 0 && tid == 0) A.tile_runs[total] = 0;
-    uint32_t u = 0, tb_lo = 1, tb_hi = 0;  // tiles [tb_lo, tb_hi) belong to unit u
-    for (uint32_t t = blockIdx.x; t < total; t += gridDim.x) {
+    const uint32_t t0 = min(blockIdx.x * tile_share(total), total), t1 = min(t0 + tile_share(total), total);
+    uint32_t u = 0, tb_lo = 1, tb_hi = 0, acc = 0;  // tiles [tb_lo, tb_hi) belong to unit u
+    for (uint32_t t = t0; t < t1; ++t) {
         if (t < tb_lo || t >= tb_hi) {
             u = find_unit(A.tile_base, A.U, t);
             tb_lo = A.tile_base[u];
             tb_hi = A.tile_base[u + 1];
         }
+        if (t == tb_lo && tid == 0) A.rle_lo[u] = acc;
         const uint32_t* g = unit_rows(A, u);
         const uint64_t nw = A.units[u].S / (4ull * A.G);
         const uint64_t i0 = (uint64_t)(t - tb_lo) * kRleTileWords;
         const uint64_t i1 = min(nw, i0 + kRleTileWords);
-        uint32_t cnt = 0;
-        for (uint64_t i = i0 + tid; i < i1; i += kThreads) cnt += (i == 0 || word_ne(g, i, i - 1, A.G)) ? 1u : 0u;
+        uint32_t cnt = 0, first = kNoStart;
+        for (uint64_t i = i0 + tid; i < i1; i += kThreads)
+            if (i == 0 || word_ne(g, i, i - 1, A.G)) {
+                ++cnt;
+                first = min(first, (uint32_t)i);
+            }
 #pragma unroll
-        for (int o = 32; o > 0; o >>= 1) cnt += __shfl_xor(cnt, o, 64);
-        if (lane == 0) s_red[wave] = cnt;
-        __syncthreads();
-        if (tid == 0) {
-            uint32_t sum = 0;
-            for (int w = 0; w < kThreads / 64; ++w) sum += s_red[w];
-            A.tile_runs[t] = sum;
+        for (int o = 32; o > 0; o >>= 1) {
+            cnt += __shfl_xor(cnt, o, 64);
+            first = min(first, (uint32_t)__shfl_xor((int)first, o, 64));
+        }
+        if (lane == 0) {
+            s_cnt[wave] = cnt;
+            s_first[wave] = first;
         }
         __syncthreads();
+        for (int w = 0; w < kThreads / 64; ++w) acc += s_cnt[w];
+        if (tid == 0) A.tile_first[t] = min(min(s_first[0], s_first[1]), min(s_first[2], s_first[3]));
+        __syncthreads();
     }
+    if (tid == 0) A.tile_part[blockIdx.x] = acc;
 }
 
 // Both statistics of the planned units in one launch: Huffman chunk sizes, then
@@ -356,148 +384,92 @@ __global__ __launch_bounds__(kThreads) void k_counts(const LosslessArgs* __restr
     rle_count_body(A);
 }
 
-// Exclusive scans, in place, of the first *count[a] + 1 entries of data[a] for
-// both arrays at once, with a fixed grid: per-workgroup range sums, one scan of
-// the sums, then each range rescanned from its base.
-constexpr int kScanDevTile = kThreads * 4;
-
-__device__ __forceinline__ void dev_range(uint32_t n, uint32_t& lo, uint32_t& hi)
-{
-    const uint32_t per = ((n + gridDim.x - 1) / gridDim.x + 3) & ~3u;
-    lo = min(n, blockIdx.x * per);
-    hi = min(n, lo + per);
-}
-
-struct ScanPair {
-    uint32_t* data[2];
-    const uint32_t* count[2];
-    uint32_t* part[2];  // [gridDim.x] range sums, then their exclusive scan
-};
-
-__global__ __launch_bounds__(kThreads) void k_scan_dev_part(const ScanPair sp)
-{
-    __shared__ uint32_t s_red[2][kThreads / 64];
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-        const uint32_t n = *sp.count[a] + 1;
-        const uint32_t* data = sp.data[a];
-        uint32_t lo, hi;
-        dev_range(n, lo, hi);
-        uint32_t sum = 0;
-        for (uint32_t i = lo + threadIdx.x; i < hi; i += kThreads) sum += data[i];
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o, 64);
-        if ((threadIdx.x & 63) == 0) s_red[a][threadIdx.x >> 6] = sum;
-    }
-    __syncthreads();
-    if (threadIdx.x < 2) {
-        const uint32_t a = threadIdx.x;
-        sp.part[a][blockIdx.x] = s_red[a][0] + s_red[a][1] + s_red[a][2] + s_red[a][3];
-    }
-}
-
-__global__ __launch_bounds__(1024) void k_scan_dev_mid(const ScanPair sp, uint32_t np)
-{
-    __shared__ uint64_t s_wave[16];
-    for (int a = 0; a < 2; ++a) {
-        uint32_t* part = sp.part[a];
-        uint64_t carry = 0;
-        for (uint32_t b = 0; b < np; b += 1024) {
-            const uint32_t i = b + threadIdx.x;
-            const uint64_t v = i < np ? part[i] : 0;
-            uint64_t ex;
-            const uint64_t t = block_scan64<1024>(v, s_wave, ex);
-            if (i < np) part[i] = (uint32_t)(carry + ex);
-            carry += t;
-        }
-    }
-}
-
-// data[lo, hi) -> its exclusive scan plus carry, a tile of kScanDevTile at a time
-__device__ __forceinline__ void scan_range(uint32_t* __restrict__ data, uint32_t lo, uint32_t hi,
-                                           uint32_t carry, uint32_t* s_wave)
-{
-    for (uint32_t b = lo; b < hi; b += kScanDevTile) {
-        const uint32_t i0 = b + threadIdx.x * 4;
-        uint32_t v[4], sum = 0;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            v[j] = i0 + j < hi ? data[i0 + j] : 0;
-            sum += v[j];
-        }
-        uint32_t excl;
-        const uint32_t total = block_excl_scan(sum, s_wave, excl);
-        excl += carry;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (i0 + j < hi) data[i0 + j] = excl;
-            excl += v[j];
-        }
-        carry += total;
-    }
-}
-
-__global__ __launch_bounds__(kThreads) void k_scan_dev_fin(const ScanPair sp)
-{
-    __shared__ uint32_t s_wave[kThreads / 64];
-    for (int a = 0; a < 2; ++a) {
-        uint32_t* __restrict__ data = sp.data[a];
-        const uint32_t n = *sp.count[a] + 1;
-        uint32_t lo, hi;
-        dev_range(n, lo, hi);
-        uint32_t carry = sp.part[a][blockIdx.x];
-        scan_range(data, lo, hi, carry, s_wave);
-    }
-}
-
-// stream bytes of every unit and its arena offset (exclusive scan of the
-// 256-byte-aligned sizes); headers of empty streams
+// The shares' totals to their exclusive scans, each unit's first word / run to
+// its absolute place, then every unit's stream bytes and arena offset (exclusive
+// scan of the 256-byte-aligned sizes), and the headers of empty streams.
 __global__ __launch_bounds__(1024) void k_unit_sizes(const LosslessArgs* __restrict__ Ap)
 {
     __shared__ uint64_t s_wave[16];
+    __shared__ uint32_t s_part[kPersistWaves];
     const LosslessArgs& A = *Ap;
-    uint64_t carry = 0;
-    for (uint32_t b = 0; b < A.U; b += 1024) {
-        const uint32_t u = b + threadIdx.x;
-        uint64_t bytes = 0, asz = 0;
-        if (u < A.U) {
-            const UnitInfo& ui = A.units[u];
-            if (ui.method == 2) {
-                const uint64_t words = A.chunk_words[A.chunk_base[u + 1]] - A.chunk_words[A.chunk_base[u]];
-                bytes = kHufHeader + 4ull * (ui.nchunks + 1) + 4 * words;
-            } else if (ui.method == 1) {
-                bytes = 8 + ui.nruns * (4ull * A.G + 4);
-            } else {
-                bytes = ui.S;
-            }
-            asz = ui.method == 0 ? 0 : (bytes + 255) & ~255ull;
-        }
+    const uint32_t tid = threadIdx.x;
+    static_assert(kPersistWaves == 4096 && kPersistWg == 1024, "four shares and one a thread");
+    {
+        const u32x4 p = reinterpret_cast<const u32x4*>(A.wave_part)[tid];
+        const uint32_t q = A.tile_part[tid];
+        // words (low half; sums may wrap, only differences are used) and runs
         uint64_t ex;
-        const uint64_t t = block_scan64<1024>(asz, s_wave, ex);
-        if (u < A.U) {
-            A.pay_off[u] = carry + ex;
-            A.unit_bytes[u] = bytes;
-        }
-        carry += t;
+        block_scan64<1024>(((uint64_t)q << 32) | 0u, s_wave, ex);
+        A.tile_part[tid] = (uint32_t)(ex >> 32);
+        block_scan64<1024>((uint64_t)p.x + p.y + p.z + p.w, s_wave, ex);
+        const uint32_t b = (uint32_t)ex;
+        const u32x4 o = u32x4{b, b + p.x, b + p.x + p.y, b + p.x + p.y + p.z};
+        reinterpret_cast<u32x4*>(A.wave_part)[tid] = o;
+        reinterpret_cast<u32x4*>(s_part)[tid] = o;
     }
-    __syncthreads();
-    const bool over = carry > A.cap;
-    if (threadIdx.x == 0) {
+    __syncthreads();  // (also the tile parts: read back below by other threads of this workgroup)
+    const uint32_t cs = max(1u, chunk_share(A.counts[0])), ts = max(1u, tile_share(A.counts[1]));
+    const uint32_t per = (A.U + 1023) / 1024, u0 = min(tid * per, A.U), u1 = min(u0 + per, A.U);
+    const auto work = gmem(A.work);
+    const auto ubytes = gmem(A.unit_bytes);  // Huffman: without its words so far
+    const auto hlo = gmem(A.huf_lo);
+    const auto hhi = gmem(A.huf_hi);
+    const auto cbase = gmem(A.chunk_base);
+    uint64_t sum = 0;
+    for (uint32_t u = u0; u < u1; u += kUnitFly) {
+        uint64_t w[kUnitFly], by[kUnitFly];
+        uint32_t lo[kUnitFly], hi[kUnitFly], c0[kUnitFly];
+#pragma unroll
+        for (uint32_t k = 0; k < kUnitFly; ++k) {
+            const uint32_t i = min(u + k, u1 - 1);
+            w[k] = work[i], by[k] = ubytes[i], lo[k] = hlo[i], hi[k] = hhi[i], c0[k] = cbase[i];
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < kUnitFly; ++k) {
+            if (u + k >= u1) break;
+            const uint32_t nch = (uint32_t)w[k], tiles = (uint32_t)((w[k] & kWorkCounts) >> 32);
+            if (nch) {
+                const uint32_t first = s_part[c0[k] / cs] + lo[k];
+                by[k] += 4ull * (s_part[(c0[k] + nch - 1) / cs] + hi[k] - first);
+                hlo[u + k] = first;
+                ubytes[u + k] = by[k];
+            }
+            if (tiles) A.rle_lo[u + k] += A.tile_part[A.tile_base[u + k] / ts];
+            sum += w[k] >> 62 ? (by[k] + 255) & ~255ull : 0;
+        }
+    }
+    uint64_t at;
+    const uint64_t total = block_scan64<1024>(sum, s_wave, at);
+    const bool over = total > A.cap;
+    for (uint32_t u = u0; u < u1; u += kUnitFly) {
+        uint64_t w[kUnitFly], by[kUnitFly];
+#pragma unroll
+        for (uint32_t k = 0; k < kUnitFly; ++k) {
+            const uint32_t i = min(u + k, u1 - 1);
+            w[k] = work[i], by[k] = ubytes[i];
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < kUnitFly; ++k) {
+            if (u + k >= u1) break;
+            gmem(A.pay_off)[u + k] = at;
+            const uint32_t method = (uint32_t)(w[k] >> 62);
+            if (method == 0) continue;
+            if ((w[k] & kWorkCounts) == 0 && !over) {  // an empty stream's header
+                uint32_t* p = reinterpret_cast<uint32_t*>(A.arena + at);
+                if (method == 2) {  // nsym 0, no code lengths, off[0] = 0
+                    for (uint32_t q = 0; q < (kHufHeader + 4) / 4; ++q) p[q] = 0;
+                } else {
+                    p[0] = 0;
+                    p[1] = 4 * A.G;
+                }
+            }
+            at += (by[k] + 255) & ~255ull;
+        }
+    }
+    if (tid == 0) {
         A.counts[2] = over ? 1u : 0u;
-        A.counts[4] = (uint32_t)carry;
-        A.counts[5] = (uint32_t)(carry >> 32);
-    }
-    if (over) return;
-    for (uint32_t u = threadIdx.x; u < A.U; u += 1024) {
-        const UnitInfo& ui = A.units[u];
-        if (ui.S != 0) continue;
-        uint32_t* p = reinterpret_cast<uint32_t*>(A.arena + A.pay_off[u]);
-        if (ui.method == 2) {  // nsym 0, no code lengths, off[0] = 0
-            for (uint32_t k = 0; k < (kHufHeader + 4) / 4; ++k) p[k] = 0;
-        } else if (ui.method == 1) {
-            p[0] = 0;
-            p[1] = 4 * A.G;
-        }
+        A.counts[4] = (uint32_t)total;
+        A.counts[5] = (uint32_t)(total >> 32);
     }
 }
 
@@ -590,8 +562,9 @@ __device__ __forceinline__ void huf_write_body(const LosslessArgs& A, uint32_t b
     const uint32_t seg = min(64u, 16 * wpl), lpc = wpl > 4 ? wpl / 4 : 1;
     const uint32_t cmax = (A.huf_chunk * kLutBitsMax + 31) / 32;  // words of a chunk at most
     uint32_t* buf = s_buf + wave * buf_words;
-    uint32_t c0, c1;
-    wave_share(total, c0, c1);
+    uint32_t wv, c0, c1;
+    wave_share(total, wv, c0, c1);
+    uint32_t acc = c0 < c1 ? A.wave_part[wv] : 0u;  // words before the batch, over every unit
     uint32_t u = 0, cb_lo = 1, cb_hi = 0, nch = 0, base = 0;
     uint64_t nwu = 0;
     uint8_t* pay = nullptr;
@@ -607,7 +580,7 @@ __device__ __forceinline__ void huf_write_body(const LosslessArgs& A, uint32_t b
             cb_hi = A.chunk_base[u + 1];
             nwu = A.units[u].S / 4;
             nch = A.units[u].nchunks;
-            base = A.chunk_words[cb_lo];
+            base = A.huf_lo[u];
             pay = A.arena + A.pay_off[u];
             for (uint32_t k = lane; k < 256; k += 64)
                 LC[k] = A.codes[(uint64_t)u * 256 + k] | ((uint32_t)A.lens[(uint64_t)u * 256 + k] << 16);
@@ -620,7 +593,7 @@ __device__ __forceinline__ void huf_write_body(const LosslessArgs& A, uint32_t b
         HufBatch hb;
         const bool full = huf_load_batch(unit_rows(A, u), (uint64_t)(c - cb_lo) * cw, nbt * cw, nwu, lane, hb);
         const uint32_t lc0 = c - cb_lo;               // the batch's first chunk in the unit
-        const uint32_t gw = A.chunk_words[c] - base;  // and its first word in the stream
+        const uint32_t gw = acc - base;               // and its first word in the stream
         uint32_t* const poff = reinterpret_cast<uint32_t*>(pay + kHufHeader);
         const auto off = gmem(poff);
         const auto words = off + nch + 1;
@@ -646,24 +619,28 @@ __device__ __forceinline__ void huf_write_body(const LosslessArgs& A, uint32_t b
         }
         sync_wave();  // the buffer is cleared again by the next batch
         c += nbt;
+        acc += boff;
     }
 }
 
-// run-length payloads.  Pass 1 (write): every run start stores its symbol and,
-// in the lengths slot, its start position.  Pass 2 (len): every run's last
-// word turns that slot into the length.  Run r of a unit = runs starting in
-// its earlier tiles + starts before the word inside the tile.
+// Run-length payloads: every run start stores its symbol and its length, the
+// distance to the next run's start.  Run r of a unit = the runs of its earlier
+// tiles + starts before the word inside the tile; the next start is the
+// thread's, else the first of a later thread of the tile, else the first of a
+// later tile (tile_first), else the unit's end.
 constexpr int kRlePer = kRleTileWords / kThreads;  // consecutive words per thread
 
-template <bool LEN>
-__device__ __forceinline__ void rle_pass_body(const LosslessArgs& A)
+__device__ __forceinline__ void rle_write_body(const LosslessArgs& A)
 {
     __shared__ uint32_t s_wave[kThreads / 64];
+    __shared__ uint32_t s_first[kThreads], s_wfirst[kThreads / 64 + 1];
     if (A.counts[2]) return;
-    const uint32_t tid = threadIdx.x;
+    const uint32_t tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t total = A.counts[1], G = A.G;
-    uint32_t u = 0, tb_lo = 1, tb_hi = 0;  // tiles [tb_lo, tb_hi) belong to unit u
-    for (uint32_t t = blockIdx.x; t < total; t += gridDim.x) {
+    const uint32_t t0 = min(blockIdx.x * tile_share(total), total), t1 = min(t0 + tile_share(total), total);
+    uint32_t acc = t0 < t1 ? A.tile_part[blockIdx.x] : 0u;  // runs before the tile, over every unit
+    uint32_t u = 0, tb_lo = 1, tb_hi = 0;                   // tiles [tb_lo, tb_hi) belong to unit u
+    for (uint32_t t = t0; t < t1; ++t) {
         if (t < tb_lo || t >= tb_hi) {
             u = find_unit(A.tile_base, A.U, t);
             tb_lo = A.tile_base[u];
@@ -674,56 +651,70 @@ __device__ __forceinline__ void rle_pass_body(const LosslessArgs& A)
         const uint64_t nw = ui.S / (4ull * G), nruns = ui.nruns;
         uint8_t* pay = A.arena + A.pay_off[u];
         uint32_t* sym = reinterpret_cast<uint32_t*>(pay + 8);
-        uint32_t* lslot = reinterpret_cast<uint32_t*>(pay + 8 + 4ull * G * nruns);
+        uint32_t* lens = reinterpret_cast<uint32_t*>(pay + 8 + 4ull * G * nruns);
         const uint32_t lt = t - tb_lo;
         const uint64_t i0 = (uint64_t)lt * kRleTileWords + (uint64_t)tid * kRlePer;
-        uint32_t flags = 0, cnt = 0;
+        uint32_t flags = 0;
         for (int k = 0; k < kRlePer; ++k) {
             const uint64_t i = i0 + k;
             const bool f = i < nw && (i == 0 || word_ne(g, i, i - 1, G));
             flags |= f ? (1u << k) : 0u;
-            cnt += f ? 1u : 0u;
         }
+        // the first start past this tile: later tiles of the unit, 256 at a time
+        uint32_t past = (uint32_t)nw;
+        for (uint32_t q = t + 1; q < tb_hi; q += kThreads) {
+            const uint32_t f = q + tid < tb_hi ? A.tile_first[q + tid] : kNoStart;
+            const unsigned long long has = __ballot(f != kNoStart);
+            const uint32_t fw = has ? (uint32_t)__builtin_amdgcn_readlane((int)f, __ffsll(has) - 1) : kNoStart;
+            if (lane == 0) s_wave[wave] = fw;
+            __syncthreads();
+            const uint32_t f4 = min(min(s_wave[0], s_wave[1]), min(s_wave[2], s_wave[3]));
+            __syncthreads();
+            if (f4 != kNoStart) {  // starts ascend, so the smallest is the next
+                past = f4;
+                break;
+            }
+        }
+        const uint32_t first = flags ? (uint32_t)i0 + (uint32_t)__ffs(flags) - 1 : kNoStart;
+        const unsigned long long any = __ballot(flags != 0);
+        s_first[tid] = first;
+        if (lane == 0) s_wfirst[wave] = any ? (uint32_t)__ffsll(any) - 1 + 64 * wave : kNoStart;  // a thread
         uint32_t excl;
-        block_excl_scan(cnt, s_wave, excl);
-        uint64_t r = (uint64_t)(A.tile_runs[t] - A.tile_runs[tb_lo]) + excl;
-        if (!LEN && lt == 0 && tid == 0) {
+        const uint32_t tile_total = block_excl_scan((uint32_t)__popc(flags), s_wave, excl);  // (a barrier inside)
+        uint32_t next = past;  // the first start after this thread's words
+        {
+            const unsigned long long later = lane == 63 ? 0 : any >> (lane + 1);
+            uint32_t th = later ? tid + (uint32_t)__ffsll(later) : kNoStart;
+            for (uint32_t w = wave + 1; w < kThreads / 64 && th == kNoStart; ++w) th = s_wfirst[w];
+            if (th != kNoStart) next = s_first[th];
+        }
+        uint64_t r = (uint64_t)(acc - A.rle_lo[u]) + excl;
+        if (lt == 0 && tid == 0) {
             reinterpret_cast<uint32_t*>(pay)[0] = (uint32_t)nruns;
             reinterpret_cast<uint32_t*>(pay)[1] = 4 * G;
         }
-        for (int k = 0; k < kRlePer; ++k) {
-            const uint64_t i = i0 + k;
-            if (i >= nw) break;
-            const bool start = (flags >> k) & 1u;
-            if (!LEN) {
-                if (start && r < nruns) {
-                    sym[r * G] = g[i * G];
-                    if (G == 2) sym[r * G + 1] = g[i * G + 1];
-                    lslot[r] = (uint32_t)i;
-                }
-                r += start ? 1 : 0;
-            } else {
-                r += start ? 1 : 0;  // now one past the run holding word i
-                const bool end = i + 1 == nw || word_ne(g, i + 1, i, G);
-                if (end && r - 1 < nruns) lslot[r - 1] = (uint32_t)(i + 1) - lslot[r - 1];
+        while (flags) {
+            const uint32_t k = (uint32_t)__ffs(flags) - 1;
+            flags &= flags - 1;
+            const uint32_t i = (uint32_t)i0 + k, end = flags ? (uint32_t)i0 + (uint32_t)__ffs(flags) - 1 : next;
+            if (r < nruns) {
+                sym[r * G] = g[(uint64_t)i * G];
+                if (G == 2) sym[r * G + 1] = g[(uint64_t)i * G + 1];
+                lens[r] = end - i;
             }
+            ++r;
         }
+        acc += tile_total;
+        __syncthreads();  // s_first, s_wfirst are written again by the next tile
     }
 }
 
-// Payload writes: Huffman streams, then the first run-length pass (the two
-// touch different units).
+// Payload writes: Huffman streams, then run-length ones (different units).
 __global__ __launch_bounds__(kThreads) void k_write(const LosslessArgs* __restrict__ Ap, uint32_t buf_words)
 {
     const LosslessArgs& A = *Ap;
     huf_write_body(A, buf_words);
-    rle_pass_body<false>(A);
-}
-
-// the second run-length pass (lengths); it reads starts other workgroups wrote
-__global__ __launch_bounds__(kThreads) void k_rle_len(const LosslessArgs* __restrict__ Ap)
-{
-    rle_pass_body<true>(*Ap);
+    rle_write_body(A);
 }
 
 // ------------------------------------------------------------------ Huffman decode
@@ -1196,28 +1187,16 @@ hipError_t launch_scan_exclusive(const uint32_t* in, uint32_t* out, uint64_t n, 
     return hipGetLastError();
 }
 
-hipError_t launch_lossless_batch(const LosslessArgs& a, const LosslessArgs* a_dev, uint32_t* scan_part,
-                                 hipStream_t s)
+hipError_t launch_lossless_batch(const LosslessArgs& a, const LosslessArgs* a_dev, hipStream_t s)
 {
     if (a.U == 0) return hipSuccess;
     const dim3 P(kPersistWg), T(kThreads);
     hipLaunchKernelGGL(k_unit_plan, dim3(1), dim3(1024), 0, s, a_dev);
     hipLaunchKernelGGL(k_counts, P, T, 0, s, a_dev);
-    ScanPair sp{};
-    sp.data[0] = a.chunk_words;
-    sp.count[0] = a.counts + 0;
-    sp.part[0] = scan_part;
-    sp.data[1] = a.tile_runs;
-    sp.count[1] = a.counts + 1;
-    sp.part[1] = scan_part + kPersistWg + 32;
-    hipLaunchKernelGGL(k_scan_dev_part, P, T, 0, s, sp);
-    hipLaunchKernelGGL(k_scan_dev_mid, dim3(1), dim3(1024), 0, s, sp, kPersistWg);
-    hipLaunchKernelGGL(k_scan_dev_fin, P, T, 0, s, sp);
     hipLaunchKernelGGL(k_unit_sizes, dim3(1), dim3(1024), 0, s, a_dev);
     const uint32_t buf_words = huf_buf_words(a.huf_chunk);
     const size_t shmem = (size_t)(kThreads / 64) * buf_words * sizeof(uint32_t);
     hipLaunchKernelGGL(k_write, P, T, shmem, s, a_dev, buf_words);
-    hipLaunchKernelGGL(k_rle_len, P, T, 0, s, a_dev);
     return hipGetLastError();
 }
 

@@ -1377,6 +1377,8 @@ __global__ __launch_bounds__(NT) void k_select(const SelectParams job, const Sel
             ui.maxlen = 0;
             ui.pad = 0;
             lv.units[u] = ui;
+            lv.work[u] = (uint64_t)ui.method << 62;
+            lv.bytes[u] = ui.method == 2 ? kHufHeaderBytes + 4 : ui.method == 1 ? 8 : 0;
         }
         return;
     }
@@ -1602,6 +1604,9 @@ __global__ __launch_bounds__(NT) void k_select(const SelectParams job, const Sel
         ui.maxlen = s_maxlen;
         ui.pad = 0;
         lv.units[u] = ui;
+        const uint64_t tiles = (S / (4ull * G) + kRleTileWords - 1) / kRleTileWords;
+        lv.work[u] = (uint64_t)method << 62 | (method == 2 ? nchunks : method == 1 ? tiles << 32 : 0);
+        lv.bytes[u] = method == 2 ? kHufHeaderBytes + 4 * (nchunks + 1) : method == 1 ? est_rle : S;
     }
 }
 

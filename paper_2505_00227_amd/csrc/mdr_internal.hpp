@@ -89,6 +89,8 @@ struct SelectLevel {
     unsigned long long* keys_out;    // [kKeyStride] their maxima (unit 0's workgroup)
     const uint32_t* recs;   // [grid][kMaxRows][2G]
     UnitInfo* units;        // [nunits]
+    uint64_t* work;         // [nunits], see LosslessArgs
+    uint64_t* bytes;        // [nunits] stream bytes (Huffman: without the words)
     uint8_t* lens;          // [nunits][256]
     uint32_t* codes;        // [nunits][256]
 };
@@ -107,20 +109,30 @@ struct SelectParams {
 // r0 = i == 0 ? 0 : 1 + (i - 1) m.  Sizes are decided on the device, so the
 // stage needs no host round trip; payloads go to one arena of capacity `cap`.
 constexpr uint32_t kRleTileWords = 4096;  // W-bit words per run-length tile
+constexpr uint64_t kWorkCounts = (1ull << 62) - 1;  // of a unit's work: chunks and tiles
+constexpr uint32_t kHufHeaderBytes = 8 + 256;        // Huffman payload: symbol count and code lengths
 constexpr uint32_t kPersistWg = 1024;     // workgroups of the persistent lossless kernels
 constexpr uint32_t kSelectManyUnits = 1024;  // units of a pass from which the selection runs 256-thread workgroups
 
 struct LosslessArgs {
     const EncodeJob* jobs;  // rows and nbd of each level
     const UnitInfo* units;  // [U] selection results
+    const uint64_t* work;   // [U] Huffman chunks | run-length tiles << 32 | method << 62
     const uint8_t* lens;    // [U][256]
     const uint32_t* codes;  // [U][256]
     uint32_t* chunk_base;   // [U+1] first Huffman chunk of each unit (0 if not HUF)
     uint32_t* tile_base;    // [U+1] first run-length tile of each unit
-    uint32_t* chunk_words;  // [chunks+1] words per chunk, scanned in place to offsets
-    uint32_t* tile_runs;    // [tiles+1] runs starting in each tile, scanned in place
+    // the lossless launches share the chunks out among kPersistWg * 4 wavefronts
+    // and the tiles among kPersistWg workgroups, contiguously; counts within a
+    // share, then absolute (exclusive scans over all units)
+    uint32_t* wave_part;    // [kPersistWg * 4] words of each wavefront's chunks
+    uint32_t* tile_part;    // [kPersistWg] runs of each workgroup's tiles
+    uint32_t* huf_lo;       // [U] words before the unit's first chunk
+    uint32_t* huf_hi;       // [U] words up to the end of its last chunk (within the share only)
+    uint32_t* rle_lo;       // [U] runs before the unit's first tile
+    uint32_t* tile_first;   // [tiles] word of the first run start in each tile
     uint64_t* pay_off;      // [U] payload offset in the arena (DC: unused)
-    uint64_t* unit_bytes;   // [U] stream bytes
+    uint64_t* unit_bytes;   // [U] stream bytes (from the selection; a Huffman stream's words are added)
     uint32_t* counts;       // [0] chunks, [1] tiles, [2] arena overflow, [3] pad, [4..5] arena bytes
     uint8_t* arena;
     uint64_t cap;
@@ -157,9 +169,7 @@ hipError_t launch_scan_exclusive(const uint32_t* in, uint32_t* out, uint64_t n, 
                                  hipStream_t s);
 // Huffman and run-length encoding of every unit the selection chose, sizes
 // and arena offsets decided on the device (grid sizes fixed: graph-capturable).
-// scan_part: 2 * kPersistWg + 64 u32 of scratch.
-hipError_t launch_lossless_batch(const LosslessArgs& a, const LosslessArgs* a_dev, uint32_t* scan_part,
-                                 hipStream_t s);
+hipError_t launch_lossless_batch(const LosslessArgs& a, const LosslessArgs* a_dev, hipStream_t s);
 // Huffman decode of many streams in one launch (payload u64 nsym | u8 len[256] |
 // u32 off[nchunks+1] | u32 words[]); kThreads chunks per workgroup
 struct DecodeJob {

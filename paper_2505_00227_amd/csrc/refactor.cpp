@@ -131,12 +131,12 @@ struct Layout {
     uint32_t G = 1, B = 0, m = 0, nunits = 0, J = 0, U = 0;
     std::vector<JobPlan> jobs;
     std::vector<uint32_t> var_first;  // first job of each variable, plus J
-    uint64_t rows_bytes = 0, pay_cap = 0, max_chunks = 0, max_tiles = 0;
+    uint64_t rows_bytes = 0, pay_cap = 0, max_tiles = 0;
     // workspace: metadata block (read back in one copy), then scratch
     uint64_t o_stats = 0, o_keys = 0, o_units = 0, o_payoff = 0, o_ubytes = 0, o_counts = 0,
              meta_bytes = 0;
     uint64_t o_lens = 0, o_codes = 0, o_hist = 0, o_recs = 0, o_trans = 0, o_kcopy = 0, o_tot_end = 0, o_cbase = 0,
-             o_tbase = 0, o_cwords = 0, o_truns = 0, o_scan = 0, o_desc = 0, ws_bytes = 0;
+             o_tbase = 0, o_parts = 0, o_starts = 0, o_work = 0, o_tfirst = 0, o_desc = 0, ws_bytes = 0;
     // descriptor (uploaded before every pass)
     uint64_t d_sjobs = 0, d_ejobs = 0, d_slev = 0, d_largs = 0, d_map[4] = {}, desc_bytes = 0;
     std::vector<uint32_t> map[4];  // workgroup -> job: stats (unaligned, aligned), encode (same)
@@ -223,7 +223,6 @@ mdr_status make_layout(const mdr_context* ctx, const VarLevels* vars, uint32_t n
             const uint64_t S = 4ull * (r1 - r0) * jp.nbd;
             L.pay_cap += unit_cap(S, prm, L.G);
             L.wide = L.wide || S >= (1ull << 30);
-            L.max_chunks += ceil_div(S, prm.huf_chunk);
             L.max_tiles += ceil_div(S / (4ull * L.G), kRleTileWords);
         }
     }
@@ -269,9 +268,10 @@ mdr_status make_layout(const mdr_context* ctx, const VarLevels* vars, uint32_t n
     L.o_tot_end = o;
     L.o_cbase = take(4ull * (L.U + 1));
     L.o_tbase = take(4ull * (L.U + 1));
-    L.o_cwords = take(4ull * (L.max_chunks + 1));
-    L.o_truns = take(4ull * (L.max_tiles + 1));
-    L.o_scan = take(4ull * (2 * kPersistWg + 64));
+    L.o_parts = take(4ull * 5 * kPersistWg);
+    L.o_starts = take(4ull * 3 * L.U);
+    L.o_work = take(8ull * L.U);
+    L.o_tfirst = take(4ull * L.max_tiles);
     // descriptor
     uint64_t d = 0;
     auto dtake = [&](uint64_t bytes) {
@@ -358,18 +358,25 @@ void fill_descriptor(const Layout& L, const mdr_codec_params& prm, uint8_t* ws, 
         s.keys_out = reinterpret_cast<unsigned long long*>(ws + L.o_keys) + (uint64_t)j * kKeyStride;
         s.recs = e.recs;
         s.units = reinterpret_cast<UnitInfo*>(ws + L.o_units) + (uint64_t)j * L.nunits;
+        s.work = reinterpret_cast<uint64_t*>(ws + L.o_work) + (uint64_t)j * L.nunits;
+        s.bytes = reinterpret_cast<uint64_t*>(ws + L.o_ubytes) + (uint64_t)j * L.nunits;
         s.lens = ws + L.o_lens + (uint64_t)j * L.nunits * 256;
         s.codes = reinterpret_cast<uint32_t*>(ws + L.o_codes) + (uint64_t)j * L.nunits * 256;
     }
     LosslessArgs* la = reinterpret_cast<LosslessArgs*>(desc + L.d_largs);
     la->jobs = reinterpret_cast<const EncodeJob*>(ws + L.o_desc + L.d_ejobs);
     la->units = reinterpret_cast<const UnitInfo*>(ws + L.o_units);
+    la->work = reinterpret_cast<const uint64_t*>(ws + L.o_work);
     la->lens = ws + L.o_lens;
     la->codes = reinterpret_cast<const uint32_t*>(ws + L.o_codes);
     la->chunk_base = reinterpret_cast<uint32_t*>(ws + L.o_cbase);
     la->tile_base = reinterpret_cast<uint32_t*>(ws + L.o_tbase);
-    la->chunk_words = reinterpret_cast<uint32_t*>(ws + L.o_cwords);
-    la->tile_runs = reinterpret_cast<uint32_t*>(ws + L.o_truns);
+    la->wave_part = reinterpret_cast<uint32_t*>(ws + L.o_parts);
+    la->tile_part = la->wave_part + 4 * kPersistWg;
+    la->huf_lo = reinterpret_cast<uint32_t*>(ws + L.o_starts);
+    la->huf_hi = la->huf_lo + L.U;
+    la->rle_lo = la->huf_hi + L.U;
+    la->tile_first = reinterpret_cast<uint32_t*>(ws + L.o_tfirst);
     la->pay_off = reinterpret_cast<uint64_t*>(ws + L.o_payoff);
     la->unit_bytes = reinterpret_cast<uint64_t*>(ws + L.o_ubytes);
     la->counts = reinterpret_cast<uint32_t*>(ws + L.o_counts);
@@ -439,13 +446,9 @@ mdr_status enqueue_pass(mdr_context* ctx, const Layout& L, const mdr_codec_param
     {
         StageTimer tm(tctx, MDR_STAGE_LOSSLESS, s);
         LosslessArgs a{};
-        a.chunk_words = reinterpret_cast<uint32_t*>(ws + L.o_cwords);
-        a.tile_runs = reinterpret_cast<uint32_t*>(ws + L.o_truns);
-        a.counts = reinterpret_cast<uint32_t*>(ws + L.o_counts);
         a.U = L.U;
         a.huf_chunk = prm.huf_chunk;
-        MDR_HIP(launch_lossless_batch(a, reinterpret_cast<const LosslessArgs*>(desc + L.d_largs),
-                                      reinterpret_cast<uint32_t*>(ws + L.o_scan), s));
+        MDR_HIP(launch_lossless_batch(a, reinterpret_cast<const LosslessArgs*>(desc + L.d_largs), s));
     }
     {
         StageTimer tm(tctx, MDR_STAGE_ASSEMBLE, s);
