@@ -718,13 +718,15 @@ __global__ __launch_bounds__(kThreads) void k_write(const LosslessArgs* __restri
 }
 
 // ------------------------------------------------------------------ Huffman decode
-// The first-code table of a stream, built in LDS by a 256-thread workgroup
+// The first-code table of a stream, built in LDS by a workgroup of kTabThreads
 // from the 256 code lengths of its header: entry i of the 2^lmax-entry table
 // holds (length << 8) | symbol of the code that the lmax-bit window i starts
 // with (codes are prefix-free, so the bits after it do not matter).  A window
 // that starts with no code (possible only for an incomplete code) consumes
 // lmax bits as symbol 0.  Ends with a barrier.
-__device__ void build_first_code_table(const uint8_t* __restrict__ payload, uint32_t lmax,
+constexpr int kTabThreads = 1024;  // four windows a thread: a launch of few streams waits on their chains
+
+__device__ __forceinline__ void build_first_code_table(const uint8_t* __restrict__ payload, uint32_t lmax,
                                        uint16_t* s_one, uint32_t (*s_wcnt)[kLutBitsMax + 1],
                                        uint8_t* s_sym)
 {
@@ -733,15 +735,26 @@ __device__ void build_first_code_table(const uint8_t* __restrict__ payload, uint
     // canonical code of symbol `tid`: the first code of its length plus the
     // smaller symbols of that length (wavefront ballots, then the counts of
     // the earlier wavefronts)
-    const uint32_t L = payload[8 + tid];
+    const uint32_t L = tid < 256 ? payload[8 + tid] : 0u;
     const bool has = L != 0 && L <= lmax;
-    uint32_t before = 0;
-    for (uint32_t l = 1; l <= lmax; ++l) {
+    uint32_t before = 0, mine = 0;  // lane l of mine: this wavefront's symbols of length l
+#pragma unroll
+    for (uint32_t l = 1; l <= (uint32_t)kLutBitsMax; ++l) {
         const unsigned long long bl = __ballot(has && L == l);
-        if (lane == 0) s_wcnt[wave][l] = (uint32_t)__popcll(bl);
+        mine = lane == l ? (uint32_t)__popcll(bl) : mine;
         if (has && L == l) before = (uint32_t)__popcll(bl & ((1ull << lane) - 1));
     }
+    if (wave < 4 && lane >= 1 && lane <= (uint32_t)kLutBitsMax) s_wcnt[wave][lane] = mine;
     __syncthreads();
+    uint32_t all = 0, earlier = 0;  // lane l: symbols of length l in all, and in the earlier wavefronts
+    if (lane >= 1 && lane <= (uint32_t)kLutBitsMax) {
+#pragma unroll
+        for (uint32_t w = 0; w < 4; ++w) {
+            const uint32_t c = s_wcnt[w][lane];
+            all += c;
+            earlier += w < wave ? c : 0u;
+        }
+    }
     // per length l (all in registers): lim[l] = end of the lmax-bit windows
     // whose first code has length <= l (non-decreasing in l); base[l] = index
     // of the first symbol of length l minus the first code of that length
@@ -750,13 +763,9 @@ __device__ void build_first_code_table(const uint8_t* __restrict__ payload, uint
         uint32_t first = 0, idx = 0;
 #pragma unroll
         for (int l = 1; l <= kLutBitsMax; ++l) {
-            uint32_t cnt = 0;
-            if (l <= (int)lmax)
-                for (uint32_t w = 0; w < kThreads / 64; ++w) cnt += s_wcnt[w][l];
-            if (has && (uint32_t)l == L) {
-                for (uint32_t w = 0; w < wave; ++w) before += s_wcnt[w][l];
-                s_sym[idx + before] = (uint8_t)tid;
-            }
+            const uint32_t cnt = (uint32_t)__builtin_amdgcn_readlane((int)all, l);  // 0 past lmax
+            const uint32_t e = (uint32_t)__builtin_amdgcn_readlane((int)earlier, l);
+            if (has && (uint32_t)l == L) s_sym[idx + e + before] = (uint8_t)tid;
             base[l] = idx - first;
             lim[l] = l <= (int)lmax ? (first + cnt) << (lmax - l) : nent;
             if (l == (int)lmax) lim_all = lim[l];
@@ -766,7 +775,7 @@ __device__ void build_first_code_table(const uint8_t* __restrict__ payload, uint
     }
     __syncthreads();
     // first code of every window (independent entries)
-    for (uint32_t i = tid; i < nent; i += kThreads) {
+    for (uint32_t i = tid; i < nent; i += kTabThreads) {
         uint32_t Lx = 1, bx = base[1];
 #pragma unroll
         for (int l = 1; l < kLutBitsMax; ++l) {
@@ -782,64 +791,95 @@ __device__ void build_first_code_table(const uint8_t* __restrict__ payload, uint
 
 // The decode tables of a launch, one workgroup per stream, built once and
 // stored to the job's table slot (the decoders' workgroups copy them to LDS
-// instead of each building them).  MULTI: the multi-symbol table of the
-// one-thread decoder, 2^lmax entries mapping the next lmax bits to up to
-// three symbols (every code lying wholly inside the window is decoded by that
-// one lookup): symbols | count << 24 | bits << 26.  Otherwise the first-code
-// table (length << 8 | symbol) of the G-lane decoder.
-template <bool MULTI>
-__global__ __launch_bounds__(kThreads) void k_huf_tables(const DecodeJob* __restrict__ jobs)
+// instead of each building them).  The multi-symbol table: 2^lmax entries
+// mapping the next lmax bits to up to three symbols (every code lying wholly
+// inside the window is decoded by that one lookup): symbols | count << 24 |
+// bits << 26.  COUNT (the G-lane decoder): behind it the counting table, all
+// whole codes of the window (up to lmax) and the first one's length: count |
+// bits << 4 | first << 8, 16 bits an entry.
+template <bool COUNT>
+__global__ __launch_bounds__(kTabThreads) void k_huf_tables(const DecodeJob* __restrict__ jobs)
 {
     const DecodeJob& job = jobs[blockIdx.x];
     const uint32_t lmax = job.lmax, nent = 1u << lmax, mask = nent - 1, tid = threadIdx.x;
     __shared__ uint16_t s_one[1 << kLutBitsMax];
-    __shared__ uint32_t s_wcnt[kThreads / 64][kLutBitsMax + 1];
+    __shared__ uint32_t s_three[COUNT ? 1 << kLutBitsMax : 1];
+    __shared__ uint32_t s_wcnt[4][kLutBitsMax + 1];
     __shared__ uint8_t s_sym[256];
     build_first_code_table(job.payload, lmax, s_one, s_wcnt, s_sym);
-    if (!MULTI) {
-        const auto t = gmem(reinterpret_cast<uint32_t*>(job.table));
-        for (uint32_t i = tid; i < nent / 2; i += kThreads)
-            t[i] = reinterpret_cast<const uint32_t*>(s_one)[i];
-        return;
-    }
     // up to three whole codes per window: chains of first-code lookups, four
     // windows at a time so their LDS latencies overlap
     const auto t = gmem(reinterpret_cast<uint32_t*>(job.table));
-    for (uint32_t i0 = tid; i0 < nent; i0 += 4 * kThreads) {
+    for (uint32_t i0 = tid; i0 < nent; i0 += 4 * kTabThreads) {
         uint32_t syms[4] = {0, 0, 0, 0}, k[4] = {0, 0, 0, 0}, used[4] = {0, 0, 0, 0};
-        bool open[4] = {true, true, true, true};
 #pragma unroll
-        for (int step = 0; step < 3; ++step) {
+        for (uint32_t step = 0; step < 3; ++step) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const uint32_t i = i0 + q * kThreads;
-                if (!open[q] || i >= nent) continue;
+                const uint32_t i = i0 + q * kTabThreads;
                 const uint32_t e = s_one[(i << used[q]) & mask];
                 const uint32_t l = e >> 8;
-                if (used[q] + l > lmax) {
-                    open[q] = false;  // the next code does not fit in the window
-                    continue;
+                if (k[q] == step && used[q] + l <= lmax) {  // no earlier code ended the chain, and this one fits
+                    syms[q] |= (e & 0xFFu) << (8 * step);
+                    ++k[q];
+                    used[q] += l;
                 }
-                syms[q] |= (e & 0xFFu) << (8 * step);
-                ++k[q];
-                used[q] += l;
             }
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const uint32_t i = i0 + q * kThreads;
-            if (i < nent) t[i] = syms[q] | (k[q] << 24) | (used[q] << 26);
+            const uint32_t i = i0 + q * kTabThreads;
+            if (i >= nent) continue;
+            const uint32_t e = syms[q] | (k[q] << 24) | (used[q] << 26);
+            t[i] = e;
+            if (COUNT) s_three[i] = e;
+        }
+    }
+    if (!COUNT) return;
+    __syncthreads();
+    // all whole codes: three at a time while they fit, then one at a time
+    const auto tc = gmem(reinterpret_cast<uint16_t*>(job.table) + 2 * nent);
+    for (uint32_t i0 = tid; i0 < nent; i0 += 4 * kTabThreads) {
+        uint32_t k[4], used[4];
+        bool open[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t e = s_three[(i0 + q * kTabThreads) & mask];
+            k[q] = (e >> 24) & 3u;
+            used[q] = e >> 26;
+            open[q] = k[q] == 3 && used[q] < lmax;  // fewer than three: the next code does not fit
+        }
+        while (__ballot(open[0] || open[1] || open[2] || open[3])) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t at = ((i0 + q * kTabThreads) << used[q]) & mask;
+                const uint32_t e = s_three[at], l = (uint32_t)s_one[at] >> 8, left = lmax - used[q];
+                const bool three = (e >> 26) <= left;
+                const uint32_t dk = three ? (e >> 24) & 3u : 1u, du = three ? e >> 26 : l;
+                const bool fits = open[q] && du <= left;
+                k[q] += fits ? dk : 0u;
+                used[q] += fits ? du : 0u;
+                // a group of fewer than three that fits was cut by the window's
+                // end or its last code's: one code at a time finds what is left
+                open[q] = fits && used[q] < lmax;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t i = i0 + q * kTabThreads;
+            if (i < nent) tc[i] = (uint16_t)(k[q] | (used[q] << 4) | (((uint32_t)s_one[i] >> 8) << 8));
         }
     }
 }
 
 // copies a job's table of `words` 32-bit words to LDS with 16-byte loads
-// (tables sit at 16 KiB strides, and 2^lmax / 2 words is a multiple of 4 for lmax >= 3)
+// (tables sit at kHufTableBytes strides, and 2^lmax words are a multiple of 8 for lmax >= 3)
+template <int NT>
 __device__ __forceinline__ void load_table(const void* table, uint32_t words, uint32_t* lds)
 {
     const auto src = gmem(reinterpret_cast<const u32x4*>(table));
     u32x4* dst = reinterpret_cast<u32x4*>(lds);
-    for (uint32_t i = threadIdx.x; i < (words + 3) / 4; i += kThreads) dst[i] = src[i];
+    for (uint32_t i = threadIdx.x; i < (words + 3) / 4; i += NT) dst[i] = src[i];
 }
 
 // One thread per chunk, kThreads chunks per workgroup (the launch for many
@@ -858,7 +898,7 @@ __global__ __launch_bounds__(kThreads) void k_huf_decode(const DecodeJob* __rest
     const uint32_t chunk = job.chunk, lmax = job.lmax, nchunks = job.nchunks;
     __shared__ __align__(16) uint32_t s_multi[1 << kLutBitsMax];  // symbols | count << 24 | bits << 26
     const uint32_t tid = threadIdx.x;
-    load_table(job.table, 1u << lmax, s_multi);
+    load_table<kThreads>(job.table, 1u << lmax, s_multi);
     __syncthreads();  // the only barrier
 
     const uint32_t c = (blockIdx.x - job.wg_base) * kThreads + tid;
@@ -976,61 +1016,99 @@ __global__ __launch_bounds__(kThreads) void k_huf_decode(const DecodeJob* __rest
 // few codes, so two or three rounds are usual).  A prefix sum of the lanes'
 // counts places their symbols, a last walk writes them to LDS, and the
 // workgroup stores its chunks' bytes with 16-byte stores.
+// Bound by the walks' dependent LDS lookups: the counting walks take all whole
+// codes of a 12-bit window at once, the last one up to three symbols (one code
+// a lookup, a workgroup took 45000 cycles instead of 24000, and the smallest
+// launch 21 us instead of 14).
 constexpr uint32_t kSplitOut = 16384;                            // decoded bytes a workgroup holds
 constexpr uint32_t kSplitWords = kSplitOut * kLutBitsMax / 32;   // their compressed words, at most
-constexpr uint32_t kSplitWordsPer = kSplitWords / kThreads;
 
-// Walks the codes of a chunk (words W[qb..ql], bits MSB first) that start in
-// [pos, hi); returns where the walk stops (the start of the first code at or
-// past hi) and their count in n; kWrite: the first `room` symbols go to out.
-template <bool kWrite>
-__device__ __forceinline__ uint32_t huf_walk(const uint32_t* W, uint32_t qb, uint32_t ql,
-                                             const uint16_t* tab, uint32_t lmax, uint32_t pos,
-                                             uint32_t hi, uint32_t& n, uint8_t* out, uint32_t room)
-{
-    uint32_t q = qb + (pos >> 5);
-    const uint32_t sh = pos & 31u;
-    uint64_t buf = ((((uint64_t)W[min(q, ql)]) << 32) | W[min(q + 1, ql)]) << sh;
-    uint32_t nb = 64 - sh;  // valid bits at the top of buf, never fewer than 32 at a lookup
-    q += 2;
-    uint32_t j = 0;
-    while (pos < hi) {
-        if (nb < 32) {
-            buf |= (uint64_t)W[min(q, ql)] << (32 - nb);
-            nb += 32;
-            ++q;
-        }
-        const uint32_t e = tab[buf >> (64 - lmax)];
-        const uint32_t L = e >> 8;
-        if (kWrite && j < room) out[j] = (uint8_t)e;
-        buf <<= L;
-        nb -= L;
-        pos += L;
-        ++j;
+// The bits of a chunk (words W[qb..ql], MSB first) from bit `pos` on: at least
+// 32 valid at a lookup, the next word loaded ahead of its use.
+struct BitReader {
+    const uint32_t* W;
+    uint32_t q, ql, next, nb;
+    uint64_t buf;
+    __device__ __forceinline__ BitReader(const uint32_t* W_, uint32_t qb, uint32_t ql_, uint32_t pos) : W(W_), ql(ql_)
+    {
+        q = qb + (pos >> 5);
+        const uint32_t sh = pos & 31u;
+        buf = ((((uint64_t)W[min(q, ql)]) << 32) | W[min(q + 1, ql)]) << sh;
+        next = W[min(q + 2, ql)];
+        nb = 64 - sh;
+        q += 3;
     }
-    n = j;
+    __device__ __forceinline__ uint32_t window(uint32_t lmax)
+    {
+        if (nb < 32) {
+            buf |= (uint64_t)next << (32 - nb);
+            nb += 32;
+            next = W[min(q++, ql)];
+        }
+        return (uint32_t)(buf >> (64 - lmax));
+    }
+    __device__ __forceinline__ void skip(uint32_t n)
+    {
+        buf <<= n;
+        nb -= n;
+    }
+};
+
+// Counts the codes that start in [pos, hi); returns where the walk stops, the
+// start of the first code at or past hi.  A lookup takes all whole codes of its
+// window while the window ends before hi, then one at a time.
+__device__ __forceinline__ uint32_t huf_count(const uint32_t* W, uint32_t qb, uint32_t ql, const uint16_t* tab,
+                                              uint32_t lmax, uint32_t pos, uint32_t hi, uint32_t& n)
+{
+    BitReader br(W, qb, ql, pos);
+    n = 0;
+    while (pos < hi) {
+        const uint32_t e = tab[br.window(lmax)];
+        const bool whole = pos + lmax <= hi;
+        const uint32_t L = whole ? (e >> 4) & 15u : e >> 8;
+        n += whole ? e & 15u : 1u;
+        br.skip(L);
+        pos += L;
+    }
     return pos;
 }
 
+// Writes the `n` symbols from bit pos on to out, up to three a lookup.
+__device__ __forceinline__ void huf_symbols(const uint32_t* W, uint32_t qb, uint32_t ql, const uint32_t* tab,
+                                            uint32_t lmax, uint32_t pos, uint32_t n, uint8_t* out)
+{
+    BitReader br(W, qb, ql, pos);
+    for (uint32_t j = 0; j < n;) {
+        const uint32_t e = tab[br.window(lmax)];
+        const uint32_t k = (e >> 24) & 3u;
+        out[j] = (uint8_t)e;
+        if (k > 1 && j + 1 < n) out[j + 1] = (uint8_t)(e >> 8);
+        if (k > 2 && j + 2 < n) out[j + 2] = (uint8_t)(e >> 16);
+        br.skip(e >> 26);
+        j += k;
+    }
+}
+
 // Dynamic LDS of a launch whose largest chunk is cap_chunk symbols: the
-// first-code table, then the compressed words and the decoded bytes of the
+// multi-symbol and the counting table, then the compressed words and the decoded bytes of the
 // workgroup's chunks.
+constexpr uint32_t kSplitTables = (4u << kLutBitsMax) + (2u << kLutBitsMax);
 __host__ __device__ constexpr uint32_t split_words_cap(uint32_t cpw, uint32_t cap_chunk)
 {
     return cpw * cap_chunk * kLutBitsMax / 32;
 }
 __host__ __device__ constexpr uint32_t split_lds_bytes(uint32_t cpw, uint32_t cap_chunk)
 {
-    return (2u << kLutBitsMax) + 4 * split_words_cap(cpw, cap_chunk) + cpw * cap_chunk;
+    return kSplitTables + 4 * split_words_cap(cpw, cap_chunk) + cpw * cap_chunk;
 }
 
-template <int G>
-__global__ __launch_bounds__(kThreads) void k_huf_decode_split(const DecodeJob* __restrict__ jobs,
+template <int G, int NT>
+__global__ __launch_bounds__(NT) void k_huf_decode_split(const DecodeJob* __restrict__ jobs,
                                                                const uint32_t* __restrict__ wg_job,
                                                                uint32_t cap_chunk)
 {
     static_assert(G >= 4 && G <= 64 && (G & (G - 1)) == 0, "G lanes a chunk: 4..64, a power of two");
-    constexpr uint32_t kCpw = kThreads / G;  // chunks per workgroup
+    constexpr uint32_t kCpw = NT / G;  // chunks per workgroup
     const DecodeJob& job = jobs[wg_job[blockIdx.x]];
     const uint8_t* payload = job.payload;
     const uint64_t S = job.S;
@@ -1038,10 +1116,11 @@ __global__ __launch_bounds__(kThreads) void k_huf_decode_split(const DecodeJob* 
     // the launcher sizes LDS for cap_chunk and raises G so that kCpw * cap_chunk <= kSplitOut
     if (chunk > cap_chunk || kCpw * cap_chunk > kSplitOut) return;
     extern __shared__ __align__(16) uint8_t s_dyn[];
-    uint16_t* s_one = reinterpret_cast<uint16_t*>(s_dyn);
+    uint32_t* s_multi = reinterpret_cast<uint32_t*>(s_dyn);
+    const uint16_t* s_count = reinterpret_cast<const uint16_t*>(s_dyn + (4u << lmax));
     const uint32_t wcap = split_words_cap(kCpw, cap_chunk);
-    uint32_t* s_words = reinterpret_cast<uint32_t*>(s_dyn + (2u << kLutBitsMax));
-    uint8_t* s_out = s_dyn + (2u << kLutBitsMax) + 4 * wcap;
+    uint32_t* s_words = reinterpret_cast<uint32_t*>(s_dyn + kSplitTables);
+    uint8_t* s_out = s_dyn + kSplitTables + 4 * wcap;
     const uint32_t tid = threadIdx.x;
     const uint32_t c0 = (blockIdx.x - job.wg_base) * kCpw, c1 = min(c0 + kCpw, nchunks);
     const auto off = gmem(reinterpret_cast<const uint32_t*>(payload + kHufHeader));
@@ -1049,16 +1128,17 @@ __global__ __launch_bounds__(kThreads) void k_huf_decode_split(const DecodeJob* 
     // the workgroup's compressed words (its chunks are adjacent) and the
     // stream's table, both loads in flight at once
     const uint32_t w0 = off[c0], nw = min(off[c1] - w0, wcap);
-    uint32_t held[kSplitWordsPer];
+    constexpr uint32_t kPer = kSplitWords / NT;
+    uint32_t held[kPer];
 #pragma unroll
-    for (uint32_t r = 0; r < kSplitWordsPer; ++r) {
-        const uint32_t i = tid + r * kThreads;
+    for (uint32_t r = 0; r < kPer; ++r) {
+        const uint32_t i = tid + r * NT;
         held[r] = i < nw ? wp[w0 + i] : 0u;
     }
-    load_table(job.table, (1u << lmax) / 2, reinterpret_cast<uint32_t*>(s_one));
+    load_table<NT>(job.table, (1u << lmax) + (1u << lmax) / 2, s_multi);
 #pragma unroll
-    for (uint32_t r = 0; r < kSplitWordsPer; ++r) {
-        const uint32_t i = tid + r * kThreads;
+    for (uint32_t r = 0; r < kPer; ++r) {
+        const uint32_t i = tid + r * NT;
         if (i < nw) s_words[i] = held[r];
     }
     __syncthreads();
@@ -1078,7 +1158,7 @@ __global__ __launch_bounds__(kThreads) void k_huf_decode_split(const DecodeJob* 
     const uint32_t lo_g = min(g * Lb, nbits), hi_g = min(lo_g + Lb, nbits);
     uint32_t start = lo_g, n = 0;
     for (int round = 0; round < G; ++round) {
-        const uint32_t end = huf_walk<false>(s_words, qb, ql, s_one, lmax, start, hi_g, n, nullptr, 0);
+        const uint32_t end = huf_count(s_words, qb, ql, s_count, lmax, start, hi_g, n);
         const uint32_t prev = __shfl_up(end, 1, G);
         // a lane whose range is empty (past the chunk's bits) decodes nothing
         // from any start: left out, it cannot hold the others up
@@ -1094,14 +1174,14 @@ __global__ __launch_bounds__(kThreads) void k_huf_decode_split(const DecodeJob* 
     }
     const uint32_t o = incl - n;
     if (live && o < cnt)
-        huf_walk<true>(s_words, qb, ql, s_one, lmax, start, hi_g, n, s_out + cl * chunk + o, cnt - o);
+        huf_symbols(s_words, qb, ql, s_multi, lmax, start, min(n, cnt - o), s_out + cl * chunk + o);
     __syncthreads();
     // the chunks' bytes are adjacent in the output too: a multiple of 4 bytes
     const uint64_t lo0 = (uint64_t)c0 * chunk;
     const uint32_t T = (uint32_t)(min((uint64_t)c1 * chunk, S) - lo0);
     const auto dst4 = gmem(reinterpret_cast<u32x4*>(job.out + lo0));
     const u32x4* src4 = reinterpret_cast<const u32x4*>(s_out);
-    for (uint32_t i = tid; i < T / 16; i += kThreads) dst4[i] = src4[i];
+    for (uint32_t i = tid; i < T / 16; i += NT) dst4[i] = src4[i];
     const uint32_t tw = (T & 15u) / 4;
     if (tid < tw) {
         const uint32_t i = (T & ~15u) / 4 + tid;
@@ -1201,27 +1281,28 @@ hipError_t launch_lossless_batch(const LosslessArgs& a, const LosslessArgs* a_de
 }
 
 hipError_t launch_huf_decode_batch(const DecodeJob* jobs, uint32_t njobs, const uint32_t* wg_job,
-                                   uint32_t grid, uint32_t lanes, uint32_t cap_chunk, hipStream_t s)
+                                   uint32_t grid, uint32_t lanes, uint32_t threads, uint32_t cap_chunk, hipStream_t s)
 {
     if (grid == 0 || njobs == 0) return hipSuccess;
-    const dim3 P(grid), T(kThreads);
-    if (lanes == 1)
-        hipLaunchKernelGGL(k_huf_tables<true>, dim3(njobs), T, 0, s, jobs);
-    else
-        hipLaunchKernelGGL(k_huf_tables<false>, dim3(njobs), T, 0, s, jobs);
+    const dim3 P(grid), T(threads);
+    if (lanes == 1) {
+        hipLaunchKernelGGL(k_huf_tables<false>, dim3(njobs), dim3(kTabThreads), 0, s, jobs);
+        hipLaunchKernelGGL(k_huf_decode, P, T, 0, s, jobs, wg_job);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL(k_huf_tables<true>, dim3(njobs), dim3(kTabThreads), 0, s, jobs);
+    const size_t shmem = split_lds_bytes(threads / lanes, cap_chunk);
+    if (threads == kSplitThreadsMax && lanes == 16) {
+        hipLaunchKernelGGL((k_huf_decode_split<16, kSplitThreadsMax>), P, T, shmem, s, jobs, wg_job, cap_chunk);
+        return hipGetLastError();
+    }
+    if (threads != kThreads) return hipErrorInvalidValue;
     switch (lanes) {
-    case 1: hipLaunchKernelGGL(k_huf_decode, P, T, 0, s, jobs, wg_job); break;
-#define MDR_SPLIT(g)                                                                              \
-    case g:                                                                                       \
-        hipLaunchKernelGGL(k_huf_decode_split<g>, P, T, split_lds_bytes(kThreads / g, cap_chunk), s, jobs, \
-                           wg_job, cap_chunk);                                                    \
-        break;
-    MDR_SPLIT(4)
-    MDR_SPLIT(8)
-    MDR_SPLIT(16)
-    MDR_SPLIT(32)
-    MDR_SPLIT(64)
-#undef MDR_SPLIT
+    case 4: hipLaunchKernelGGL((k_huf_decode_split<4, kThreads>), P, T, shmem, s, jobs, wg_job, cap_chunk); break;
+    case 8: hipLaunchKernelGGL((k_huf_decode_split<8, kThreads>), P, T, shmem, s, jobs, wg_job, cap_chunk); break;
+    case 16: hipLaunchKernelGGL((k_huf_decode_split<16, kThreads>), P, T, shmem, s, jobs, wg_job, cap_chunk); break;
+    case 32: hipLaunchKernelGGL((k_huf_decode_split<32, kThreads>), P, T, shmem, s, jobs, wg_job, cap_chunk); break;
+    case 64: hipLaunchKernelGGL((k_huf_decode_split<64, kThreads>), P, T, shmem, s, jobs, wg_job, cap_chunk); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -1240,6 +1321,11 @@ uint32_t huf_decode_lanes(uint32_t want, uint64_t total_chunks, uint32_t max_chu
     if (g == 1) return 1;
     while (g < 64 && (uint64_t)g * kSplitOut < (uint64_t)kThreads * max_chunk) g <<= 1;  // staging fits
     return g;
+}
+
+uint32_t huf_decode_threads(uint32_t lanes, uint64_t total_chunks, uint32_t max_chunk)
+{
+    return lanes == 16 && max_chunk == 256 && total_chunks >= kHufWideChunks ? kSplitThreadsMax : kThreads;
 }
 
 hipError_t launch_rle_decode_batch(const RleJob* jobs, const uint32_t* wg_gather, uint32_t n_gather,

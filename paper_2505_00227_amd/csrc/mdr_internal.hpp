@@ -180,19 +180,27 @@ struct DecodeJob {
     uint32_t nchunks, chunk, lmax;
     uint32_t wg_base;       // first workgroup of this job in the launch
 };
-constexpr uint64_t kHufTableBytes = 4ull << kLutBitsMax;  // 2^lmax 32-bit entries at most
-// lanes per chunk: 1 (kThreads chunks per workgroup) or 4..64 (kThreads / lanes
-// chunks per workgroup); cap_chunk: the largest chunk of the jobs.  A first
+constexpr uint64_t kHufTableBytes = 6ull << kLutBitsMax;  // 2^lmax 32-bit and as many 16-bit entries at most
+// lanes per chunk: 1 or 4..64; threads: of a workgroup, which takes threads / lanes
+// chunks (kThreads, or what huf_decode_threads gives); cap_chunk: the largest chunk of the jobs.  A first
 // launch builds every job's decode table into its table slot, which the
 // decoding workgroups copy
 hipError_t launch_huf_decode_batch(const DecodeJob* jobs, uint32_t njobs, const uint32_t* wg_job,
-                                   uint32_t grid, uint32_t lanes, uint32_t cap_chunk, hipStream_t s);
+                                   uint32_t grid, uint32_t lanes, uint32_t threads, uint32_t cap_chunk, hipStream_t s);
 // lanes per chunk for a launch of total_chunks chunks, the largest chunk
 // max_chunk symbols: want = 0 picks by the symbol count (16 symbols a lane
 // below kHufOneLaneSymbols); 1 stays 1; 4..64 is raised where a workgroup's
 // chunks would not fit its LDS staging
 constexpr uint64_t kHufOneLaneSymbols = 196608ull * 256;  // one thread a chunk from this many symbols on
 uint32_t huf_decode_lanes(uint32_t want, uint64_t total_chunks, uint32_t max_chunk);
+// threads of the launch's workgroups: the G-lane decoder's tables take 24 KB of
+// LDS a workgroup, so a launch that fills the chip shares them among 16
+// wavefronts (full occupancy), a smaller one spreads over more CUs with four
+// (20480 chunks: 38 us with 16 against 34 with four; 40960: 38 against 44;
+// 163840: 72 against 100)
+constexpr uint32_t kSplitThreadsMax = 1024;
+constexpr uint64_t kHufWideChunks = 32768;
+uint32_t huf_decode_threads(uint32_t lanes, uint64_t total_chunks, uint32_t max_chunk);
 // RLE decode of every run-length group of a retrieval: payload u32 nruns |
 // u32 wbytes | symbols[nruns][G] | u32 lengths[nruns]
 struct RleJob {

@@ -256,7 +256,8 @@ mdr_status retrieve_many(mdr_context* ctx, RetrieveTask* tasks, size_t ntasks, h
         map_re.insert(map_re.end(), (rle[i].nwords + kRlePerWg - 1) / kRlePerWg, i);
     }
     const uint32_t lanes = huf_decode_lanes(ctx->decode_lanes, dec_chunks, dec_chunk_max);
-    const uint32_t cpw = kThreads / lanes;
+    const uint32_t threads = huf_decode_threads(lanes, dec_chunks, dec_chunk_max);
+    const uint32_t cpw = threads / lanes;
     for (uint32_t i = 0; i < dec.size(); ++i) {
         dec[i].wg_base = (uint32_t)map_dec.size();
         map_dec.insert(map_dec.end(), (dec[i].nchunks + cpw - 1) / cpw, i);
@@ -320,7 +321,7 @@ mdr_status retrieve_many(mdr_context* ctx, RetrieveTask* tasks, size_t ntasks, h
             StageTimer tm(ctx, MDR_STAGE_HUF_DECODE, s);
             MDR_HIP(launch_huf_decode_batch(reinterpret_cast<const DecodeJob*>(dv + o_dec), (uint32_t)dec.size(),
                                             reinterpret_cast<const uint32_t*>(dv + o_md),
-                                            (uint32_t)map_dec.size(), lanes, dec_chunk_max, s));
+                                            (uint32_t)map_dec.size(), lanes, threads, dec_chunk_max, s));
         }
         for (int d = 0; d < 2; ++d) {
             if (map_r[d].empty()) continue;
