@@ -146,8 +146,11 @@ hipError_t launch_fill_u32(uint32_t* p, uint64_t count, uint32_t value, hipStrea
 // behind it start without waiting on another engine; under capture the kernel
 // reads the host memory at every replay
 hipError_t launch_copy_in(void* dst, const void* host, uint64_t bytes, hipStream_t s);
-// level statistics [count] to their neutral values, z[n] to zero
-hipError_t launch_init_pass(LevelStats* st, uint32_t count, uint32_t* z, uint64_t n, hipStream_t s);
+// the start of a pass in one launch: launch_copy_in of the descriptor (bytes > 0),
+// level statistics [count] to their neutral values, zbytes (a multiple of 16)
+// at z to zero
+hipError_t launch_begin_pass(void* dst, const void* host, uint64_t bytes, LevelStats* st, uint32_t count, void* z,
+                             uint64_t zbytes, hipStream_t s);
 // statistics of every job; wg_job maps each of `grid` workgroups to its job
 hipError_t launch_stats_batch(const StatsJob* jobs, const uint32_t* wg_job, uint32_t grid, bool f64,
                               bool vec, hipStream_t s);

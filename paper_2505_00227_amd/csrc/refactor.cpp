@@ -402,7 +402,6 @@ mdr_status enqueue_pass(mdr_context* ctx, const Layout& L, const mdr_codec_param
     (void)hipGetLastError();
     mdr_context* tctx = timed ? ctx : nullptr;
     uint8_t* desc = ws + L.o_desc;
-    MDR_HIP(launch_copy_in(desc, stage, L.desc_bytes, s));
     const StatsJob* sj = reinterpret_cast<const StatsJob*>(desc + L.d_sjobs);
     const EncodeJob* ej = reinterpret_cast<const EncodeJob*>(desc + L.d_ejobs);
     const SelectLevel* sl = reinterpret_cast<const SelectLevel*>(desc + L.d_slev);
@@ -412,8 +411,8 @@ mdr_status enqueue_pass(mdr_context* ctx, const Layout& L, const mdr_codec_param
         StageTimer tm(tctx, MDR_STAGE_STATS, s);
         // the encoder adds its workgroups' histograms, transitions and key
         // maxima into zeroed level totals (a kernel: safe under capture)
-        MDR_HIP(launch_init_pass(reinterpret_cast<LevelStats*>(ws + L.o_stats), L.J,
-                                 reinterpret_cast<uint32_t*>(ws + L.o_hist), (L.o_tot_end - L.o_hist) / 4, s));
+        MDR_HIP(launch_begin_pass(desc, stage, L.desc_bytes, reinterpret_cast<LevelStats*>(ws + L.o_stats), L.J,
+                                  ws + L.o_hist, L.o_tot_end - L.o_hist, s));
         MDR_HIP(launch_stats_batch(sj, map[0], (uint32_t)L.map[0].size(), L.f64, false, s));
         MDR_HIP(launch_stats_batch(sj, map[1], (uint32_t)L.map[1].size(), L.f64, true, s));
     }
