@@ -351,9 +351,13 @@ def _dtype_code(t) -> int:
 class Refactored:
     """Refactored variable (mdr_refactored): plane streams + error tables on the device."""
 
-    def __init__(self, ctx: Context, handle):
+    def __init__(self, ctx: Context, handle, like: Refactored | None = None, nlevels: int = 0):
         self.ctx = ctx
         self.handle = handle
+        if like is not None:  # of the same batch: only the level count can differ
+            self.nlevels, self.dtype, self.nplanes = nlevels, like.dtype, like.nplanes
+            self.params = mdr_codec_params.from_buffer_copy(like.params)
+            return
         nl, dt, B = _u32(), C.c_int(), _u32()
         prm = mdr_codec_params()
         _check(_lib.mdr_refactored_shape(handle, C.byref(nl), C.byref(dt), C.byref(B), C.byref(prm)))
@@ -480,7 +484,8 @@ def refactor_batch(ctx: Context, variables, nplanes: int, params: mdr_codec_para
     _check(_lib.mdr_refactor_batch(ctx.handle, bv.vp, bv.nl, bv.n, bv.dt, nplanes,
                                    C.byref(params) if params is not None else None,
                                    _stream_ptr(stream), hs))
-    return [Refactored(ctx, _vp(h)) for h in hs]
+    first = Refactored(ctx, _vp(hs[0]))
+    return [first] + [Refactored(ctx, _vp(hs[v]), first, bv.nl[v]) for v in range(1, bv.n)]
 
 
 class Retriever:

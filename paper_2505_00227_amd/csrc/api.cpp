@@ -498,8 +498,6 @@ mdr_status mdr_retriever_create(mdr_context* ctx, const mdr_refactored* r, mdr_r
     rt->ctx = ctx;
     rt->r = r;
     rt->k.assign(r->levels.size(), 0);
-    rt->dec.resize(r->levels.size());
-    for (auto& v : rt->dec) v.resize(kMaxRows);
     *out = rt;
     return MDR_OK;
 }

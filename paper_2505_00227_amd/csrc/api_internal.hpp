@@ -99,14 +99,43 @@ struct PoolBuf {
 };
 
 struct UnitRec {
-    int32_t method = MDR_PLACEHOLDER;
     uint64_t bytes = 0;    // payload bytes (0 for placeholders)
     uint64_t S = 0;        // decoded bytes of the unit
     uint64_t nruns = 0;    // RLE runs
     uint64_t est_huf = 0, est_rle = 0;
+    uint8_t* dev = nullptr;  // payload (DC: the plane rows themselves)
+    int32_t method = MDR_PLACEHOLDER;
     uint32_t nchunks = 0;  // Huffman chunks
     uint32_t maxlen = 0;   // longest Huffman code
-    uint8_t* dev = nullptr;  // payload (DC: the plane rows themselves)
+};
+
+// The units of a level: the sign row, then one per group of m planes.  A table
+// slot is 0 for the sign and 1 + p for plane p; only a group's first plane
+// leads a unit, every other slot reads as a placeholder.  A record per slot
+// was 4.7 KB a level, most of it placeholders to write, copy and free (with the
+// per-slot buffers of the retrievers, 0.5 of the 2.3 ms in which a pass over
+// the 1280 levels of 256 variables left the device idle).
+class UnitTable {
+public:
+    void init(uint32_t B, uint32_t m)
+    {
+        m_ = m;
+        u_.assign(1 + (B + m - 1) / m, UnitRec());
+    }
+    uint32_t count() const { return (uint32_t)u_.size(); }
+    uint32_t slot(uint32_t unit) const { return unit == 0 ? 0 : 1 + (unit - 1) * m_; }
+    UnitRec& unit(uint32_t i) { return u_[i]; }
+    const UnitRec& unit(uint32_t i) const { return u_[i]; }
+    const UnitRec& operator[](uint32_t slot) const
+    {
+        static const UnitRec placeholder;
+        if (slot == 0) return u_[0];
+        const uint32_t i = (slot - 1) / m_;
+        return (slot - 1) % m_ == 0 && i + 1 < u_.size() ? u_[i + 1] : placeholder;
+    }
+private:
+    uint32_t m_ = 1;
+    std::vector<UnitRec> u_;
 };
 
 struct LevelRec {
@@ -117,7 +146,7 @@ struct LevelRec {
     std::vector<double> E;      // B+1
     std::vector<double> E2;     // B+1 squared-L2 errors, once mdr_l2_table has run (else empty)
     uint32_t* rows = nullptr;   // [(B+1)][nbd]
-    UnitRec units[kMaxRows];    // slot 0 = sign, 1+p = plane p
+    UnitTable units;
 };
 
 // first row / row count of the unit at table slot s
@@ -316,6 +345,7 @@ struct mdr_retriever {
     mdr_context* ctx = nullptr;
     const mdr_refactored* r = nullptr;
     std::vector<uint32_t> k;                      // planes held per level
-    std::vector<std::vector<mdr::PoolBuf>> dec;   // [level][slot] decoded non-DC units
+    std::vector<const uint8_t*> dec;              // [level][unit] decoded non-DC units (null: none)
+    std::vector<mdr::PoolBuf> held;               // their memory, one block per call that decoded
     uint64_t bytes_held = 0;
 };

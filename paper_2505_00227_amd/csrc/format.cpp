@@ -417,16 +417,17 @@ mdr_status mdr_deserialize(mdr_context* ctx, const void* host, uint64_t bytes, m
         const uint64_t rec_end = table + 16ull * (1 + B);
         if (get<uint32_t>(in + rec_end) != crc32(in + rec, rec_end - rec)) return after_crcs(corrupt("level record CRC mismatch"));
         pos = rec_end + 8;
+        L.units.init(B, m);
         for (uint32_t s = 0; s <= B; ++s) {
             const uint8_t* ent = in + table + 16ull * s;
-            UnitRec& u = L.units[s];
-            u.method = ent[0];
             const uint64_t nb = get<uint64_t>(ent + 8);
             const bool leader = s == 0 || (s - 1) % m == 0;
             if (!leader) {
-                if (u.method != MDR_PLACEHOLDER || nb != 0) return after_crcs(corrupt("bad placeholder slot"));
+                if (ent[0] != MDR_PLACEHOLDER || nb != 0) return after_crcs(corrupt("bad placeholder slot"));
                 continue;
             }
+            UnitRec& u = L.units.unit(s == 0 ? 0 : 1 + (s - 1) / m);
+            u.method = ent[0];
             if (u.method > MDR_HUF) return after_crcs(corrupt("bad method in a leading slot"));
             if (nb > bytes - pos) return after_crcs(corrupt("payload runs past the end of the blob"));
             u.bytes = nb;
@@ -460,7 +461,7 @@ mdr_status mdr_deserialize(mdr_context* ctx, const void* host, uint64_t bytes, m
     std::vector<Span> sp;
     for (const Src& sr : srcs) {
         LevelRec& L = R->levels[sr.level];
-        UnitRec& u = L.units[sr.slot];
+        UnitRec& u = L.units.unit(sr.slot == 0 ? 0 : 1 + (sr.slot - 1) / m);
         if (u.method == MDR_DC) {
             uint32_t r0, r1;
             slot_rows(sr.slot, B, m, r0, r1);

@@ -84,10 +84,9 @@ std::unique_ptr<mdr_refactored> device_view(const mdr_pipeline* p, const HostChu
         LevelRec& L = R->levels[l];
         L.rows = reinterpret_cast<uint32_t*>(rows + roff);
         roff += align256(4ull * (p->B + 1) * L.nbd);
-        for (uint32_t s = 0; s <= p->B; ++s) {
-            UnitRec& u = L.units[s];
-            if (u.method == MDR_PLACEHOLDER) continue;
-            const uint64_t o = hc.unit_off[(uint64_t)l * kMaxRows + s];
+        for (uint32_t i = 0; i < L.units.count(); ++i) {
+            UnitRec& u = L.units.unit(i);
+            const uint64_t o = hc.unit_off[(uint64_t)l * kMaxRows + L.units.slot(i)];
             u.dev = (u.method == MDR_DC ? rows : pay) + o;
         }
     }
@@ -104,9 +103,8 @@ void keep_meta(const mdr_refactored* R, HostChunk& hc, uint64_t& pay_used)
     pay_used = 0;
     hc.dc.clear();
     for (size_t l = 0; l < R->levels.size(); ++l)
-        for (uint32_t s = 0; s <= R->B; ++s) {
-            const UnitRec& u = R->levels[l].units[s];
-            if (u.method == MDR_PLACEHOLDER) continue;
+        for (uint32_t i = 0; i < R->levels[l].units.count(); ++i) {
+            const UnitRec& u = R->levels[l].units.unit(i);
             uint64_t o;
             if (u.method == MDR_DC) {
                 o = (uint64_t)(u.dev - rows0);
@@ -115,8 +113,8 @@ void keep_meta(const mdr_refactored* R, HostChunk& hc, uint64_t& pay_used)
                 o = (uint64_t)(u.dev - pay0);
                 pay_used = std::max(pay_used, o + u.bytes);
             }
-            hc.unit_off[l * kMaxRows + s] = o;
-            hc.levels[l].units[s].dev = nullptr;
+            hc.unit_off[l * kMaxRows + hc.levels[l].units.slot(i)] = o;
+            hc.levels[l].units.unit(i).dev = nullptr;
         }
     for (LevelRec& L : hc.levels) L.rows = nullptr;
     std::sort(hc.dc.begin(), hc.dc.end());
@@ -465,8 +463,6 @@ mdr_status mdr_pipeline_retrieve(mdr_pipeline* p, mdr_bound kind, double tol, vo
         rts[c]->ctx = p->ctx;
         rts[c]->r = views[c].get();
         rts[c]->k.assign(p->nlevels, 0);
-        rts[c]->dec.resize(p->nlevels);
-        for (auto& d : rts[c]->dec) d.resize(kMaxRows);
         RetrieveTask t;
         t.rt = rts[c];
         t.knew = plans[c];

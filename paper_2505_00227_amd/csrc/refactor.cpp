@@ -152,7 +152,10 @@ mdr_status make_layout(const mdr_context* ctx, const VarLevels* vars, uint32_t n
     L.B = B;
     L.m = prm.group_planes;
     L.nunits = 1 + (B + L.m - 1) / L.m;
-    uint64_t total_tiles = 0, total_values = 0;
+    uint64_t total_tiles = 0, total_values = 0, total_levels = 0;
+    for (uint32_t v = 0; v < nvars; ++v) total_levels += vars[v].nlevels;
+    L.jobs.reserve(total_levels);
+    L.var_first.reserve(nvars + 1);
     for (uint32_t v = 0; v < nvars; ++v) {
         L.var_first.push_back((uint32_t)L.jobs.size());
         for (uint32_t l = 0; l < vars[v].nlevels; ++l) {
@@ -217,13 +220,14 @@ mdr_status make_layout(const mdr_context* ctx, const VarLevels* vars, uint32_t n
         trans += 4ull * kMaxRows * jp.copies;
         jp.keys_off = keys;
         keys += 8ull * kKeyStride * jp.copies;
-        for (uint32_t i = 0; i < L.nunits; ++i) {
-            const uint32_t r0 = i == 0 ? 0 : 1 + (i - 1) * L.m;
-            const uint32_t r1 = i == 0 ? 1 : std::min(B + 1, r0 + L.m);
-            const uint64_t S = 4ull * (r1 - r0) * jp.nbd;
-            L.pay_cap += unit_cap(S, prm, L.G);
+        // units by their rows: the sign's, full groups, a last shorter group
+        const uint64_t kinds[3][2] = {{1, 1}, {L.m, B / L.m}, {B % L.m, B % L.m ? 1u : 0u}};
+        for (const auto& kd : kinds) {
+            if (kd[1] == 0) continue;
+            const uint64_t S = 4ull * kd[0] * jp.nbd;
+            L.pay_cap += kd[1] * unit_cap(S, prm, L.G);
             L.wide = L.wide || S >= (1ull << 30);
-            L.max_tiles += ceil_div(S / (4ull * L.G), kRleTileWords);
+            L.max_tiles += kd[1] * ceil_div(S / (4ull * L.G), kRleTileWords);
         }
     }
 
@@ -234,11 +238,11 @@ mdr_status make_layout(const mdr_context* ctx, const VarLevels* vars, uint32_t n
         jp.wg_base_s = (uint32_t)ms.size();
         ms.insert(ms.end(), jp.grid_s, j);
     }
-    std::vector<uint32_t> order(L.J);
-    for (uint32_t j = 0; j < L.J; ++j) order[j] = j;
-    std::stable_sort(order.begin(), order.end(),
-                     [&](uint32_t a, uint32_t b) { return L.jobs[a].tpw > L.jobs[b].tpw; });
-    for (uint32_t j : order) {
+    std::vector<uint64_t> order(L.J);  // tiles a workgroup (descending), then job (ascending)
+    for (uint32_t j = 0; j < L.J; ++j) order[j] = (uint64_t)(~L.jobs[j].tpw) << 32 | j;
+    std::sort(order.begin(), order.end());
+    for (uint64_t key : order) {
+        const uint32_t j = (uint32_t)key;
         JobPlan& jp = L.jobs[j];
         std::vector<uint32_t>& me = L.map[jp.vec || L.small ? 3 : 2];
         jp.wg_base_e = (uint32_t)me.size();
@@ -290,6 +294,7 @@ mdr_status make_layout(const mdr_context* ctx, const VarLevels* vars, uint32_t n
 
     // shape key: everything the captured launches depend on
     std::string& key = L.key;
+    key.reserve(8ull * (12 + 2ull * L.J));
     auto put = [&](uint64_t v) { key.append(reinterpret_cast<const char*>(&v), 8); };
     put((uint64_t)dtype);
     put(B);
@@ -314,7 +319,8 @@ mdr_status make_layout(const mdr_context* ctx, const VarLevels* vars, uint32_t n
 void fill_descriptor(const Layout& L, const mdr_codec_params& prm, uint8_t* ws, uint8_t* rows_base,
                      uint8_t* pay_base, uint8_t* desc)
 {
-    std::memset(desc, 0, L.desc_bytes);
+    uint16_t hist_off[kMaxRows] = {};
+    for (uint32_t r = 0; r <= L.B; ++r) hist_off[r] = (uint16_t)((r == 0 ? 0 : 1 + (r - 1) / L.m) * 256);
     StatsJob* sj = reinterpret_cast<StatsJob*>(desc + L.d_sjobs);
     EncodeJob* ej = reinterpret_cast<EncodeJob*>(desc + L.d_ejobs);
     SelectLevel* sl = reinterpret_cast<SelectLevel*>(desc + L.d_slev);
@@ -345,8 +351,7 @@ void fill_descriptor(const Layout& L, const mdr_codec_params& prm, uint8_t* ws, 
         e.recs = reinterpret_cast<uint32_t*>(ws + L.o_recs + jp.recs_off);
         e.keys = reinterpret_cast<unsigned long long*>(ws + L.o_kcopy + jp.keys_off);
         e.copies = jp.copies;
-        for (uint32_t r = 0; r <= L.B; ++r)
-            e.hist_off[r] = (uint16_t)((r == 0 ? 0 : 1 + (r - 1) / L.m) * 256);
+        std::memcpy(e.hist_off, hist_off, sizeof hist_off);
 
         SelectLevel& s = sl[j];
         s.nbd = jp.nbd;
@@ -364,6 +369,7 @@ void fill_descriptor(const Layout& L, const mdr_codec_params& prm, uint8_t* ws, 
         s.codes = reinterpret_cast<uint32_t*>(ws + L.o_codes) + (uint64_t)j * L.nunits * 256;
     }
     LosslessArgs* la = reinterpret_cast<LosslessArgs*>(desc + L.d_largs);
+    std::memset(la, 0, sizeof *la);
     la->jobs = reinterpret_cast<const EncodeJob*>(ws + L.o_desc + L.d_ejobs);
     la->units = reinterpret_cast<const UnitInfo*>(ws + L.o_units);
     la->work = reinterpret_cast<const uint64_t*>(ws + L.o_work);
@@ -526,11 +532,12 @@ mdr_status assemble(mdr_context* ctx, const Layout& L, mdr_dtype dtype, const md
                     LR.E[k] = ek > small ? ek : small;
                 }
             }
+            LR.units.init(L.B, L.m);
             for (uint32_t i = 0; i < L.nunits; ++i) {
                 const uint64_t u = (uint64_t)j * L.nunits + i;
                 const UnitInfo& ui = hun[u];
-                const uint32_t slot = i == 0 ? 0 : 1 + (i - 1) * L.m;
-                UnitRec& ur = LR.units[slot];
+                const uint32_t slot = LR.units.slot(i);
+                UnitRec& ur = LR.units.unit(i);
                 ur.method = (int32_t)ui.method;
                 ur.S = ui.S;
                 ur.nruns = ui.nruns;

@@ -86,10 +86,11 @@ DescSlot* acquire_slot(mdr_context* ctx, uint64_t bytes, uint64_t dev_bytes, mdr
     return &d;
 }
 
+// a coded unit entering a plan: its place in the retriever's table and in the
+// block that holds what this call decodes for it
 struct Fresh {
-    size_t task;
-    uint32_t level, slot;
-    PoolBuf buf;
+    uint32_t level, unit;
+    uint64_t off;
 };
 
 }  // namespace
@@ -126,8 +127,13 @@ mdr_status retrieve_many(mdr_context* ctx, RetrieveTask* tasks, size_t ntasks, h
                 return fail(MDR_ERR_INVALID_ARG, "level_out[" + std::to_string(l) + "] is NULL");
     }
 
-    // groups entering each plan; state is committed only at the end
-    std::vector<Fresh> fresh;
+    // groups entering each plan; state is committed only at the end.  The units
+    // a call decodes for one retriever share one block of device memory (a
+    // block each cost 2000 pool calls in a batch of 256 variables, and as many
+    // when they were freed).
+    std::vector<PoolBuf> block(ntasks);
+    std::vector<std::vector<const uint8_t*>> decoded(ntasks);  // each retriever's table after the call
+    std::vector<Fresh> fresh;  // of one task
     std::vector<DecodeJob> dec;
     std::vector<RleJob> rle;
     uint64_t rle_runs = 0;
@@ -144,58 +150,74 @@ mdr_status retrieve_many(mdr_context* ctx, RetrieveTask* tasks, size_t ntasks, h
     for (size_t t = 0; t < ntasks; ++t) {
         mdr_retriever* rt = tasks[t].rt;
         const mdr_refactored* r = rt->r;
-        const uint32_t B = r->B, m = r->m, G = r->G;
+        const uint32_t G = r->G;
+        uint64_t need = 0;
+        fresh.clear();
         for (uint32_t l = 0; l < r->levels.size(); ++l) {
             const LevelRec& LR = r->levels[l];
             const uint32_t k0 = rt->k[l], k1 = tasks[t].knew[l];
-            for (uint32_t slot = 0; slot <= B; slot = slot == 0 ? 1 : slot + m) {
+            if (k1 <= k0) continue;
+            for (uint32_t i = 0; i < LR.units.count(); ++i) {
+                const uint32_t slot = LR.units.slot(i);
                 const bool before = slot == 0 ? k0 > 0 : (slot - 1) < k0;
                 const bool now = slot == 0 ? k1 > 0 : (slot - 1) < k1;
                 if (!now || before) continue;
-                const UnitRec& ur = LR.units[slot];
+                const UnitRec& ur = LR.units.unit(i);
                 fetched[t] += ur.bytes;
                 ++groups[t];
                 if (ur.method == MDR_DC || LR.n == 0) continue;
-                Fresh f{t, l, slot, PoolBuf()};
-                hipError_t e = f.buf.alloc(rt->ctx->pool, std::max<uint64_t>(ur.S, 4));
-                if (e != hipSuccess) return hip_fail(e, "hipMalloc(decoded group)");
-                if (ur.method == MDR_HUF) {
-                    DecodeJob dj{};
-                    dj.payload = ur.dev;
-                    dj.out = static_cast<uint8_t*>(f.buf.p);
-                    dj.S = ur.S;
-                    dj.nchunks = ur.nchunks;
-                    dj.chunk = r->prm.huf_chunk;
-                    dj.lmax = r->prm.huf_lmax;
-                    dec.push_back(dj);
-                } else if (ur.method == MDR_RLE) {
-                    RleJob rj{};
-                    rj.payload = ur.dev;
-                    rj.out = static_cast<uint8_t*>(f.buf.p);
-                    rj.nwords = ur.S / 4 / G;
-                    rj.nruns = ur.nruns;
-                    rj.G = G;
-                    if (rj.nwords >= (1ull << 32)) return fail(MDR_ERR_UNSUPPORTED, "run-length group of 2^32 words");
-                    if (rj.nwords && rj.nruns) {
-                        rj.run_base = rle_runs;
-                        rle_runs += rj.nruns;
-                        rle.push_back(rj);
-                    }
-                } else {
-                    return fail(MDR_ERR_CORRUPT_STREAM, "unknown lossless method");
+                fresh.push_back({l, i, need});
+                need += align256(std::max<uint64_t>(ur.S, 4));
+            }
+        }
+        decoded[t] = rt->dec;
+        if (fresh.empty()) continue;
+        const size_t nunits = r->levels[0].units.count();
+        decoded[t].resize(r->levels.size() * nunits, nullptr);
+        hipError_t e = block[t].alloc(rt->ctx->pool, need);
+        if (e != hipSuccess) return hip_fail(e, "hipMalloc(decoded groups)");
+        for (const Fresh& f : fresh) {
+            const UnitRec& ur = r->levels[f.level].units.unit(f.unit);
+            uint8_t* out = static_cast<uint8_t*>(block[t].p) + f.off;
+            decoded[t][f.level * nunits + f.unit] = out;
+            if (ur.method == MDR_HUF) {
+                DecodeJob dj{};
+                dj.payload = ur.dev;
+                dj.out = out;
+                dj.S = ur.S;
+                dj.nchunks = ur.nchunks;
+                dj.chunk = r->prm.huf_chunk;
+                dj.lmax = r->prm.huf_lmax;
+                dec.push_back(dj);
+            } else if (ur.method == MDR_RLE) {
+                RleJob rj{};
+                rj.payload = ur.dev;
+                rj.out = out;
+                rj.nwords = ur.S / 4 / G;
+                rj.nruns = ur.nruns;
+                rj.G = G;
+                if (rj.nwords >= (1ull << 32)) return fail(MDR_ERR_UNSUPPORTED, "run-length group of 2^32 words");
+                if (rj.nwords && rj.nruns) {
+                    rj.run_base = rle_runs;
+                    rle_runs += rj.nruns;
+                    rle.push_back(rj);
                 }
-                fresh.push_back(std::move(f));
+            } else {
+                return fail(MDR_ERR_CORRUPT_STREAM, "unknown lossless method");
             }
         }
     }
 
     // reconstruction jobs, one list per dtype
-    std::vector<std::vector<const uint8_t*>> fsrc(ntasks);
-    for (size_t t = 0; t < ntasks; ++t) fsrc[t].assign(tasks[t].rt->r->levels.size() * kMaxRows, nullptr);
-    for (const Fresh& f : fresh) fsrc[f.task][(size_t)f.level * kMaxRows + f.slot] = static_cast<const uint8_t*>(f.buf.p);
     std::vector<ReconJob> rj[2];
-    // t: the task whose fresh groups apply (ntasks: none)
-    auto add_jobs = [&](size_t t, const mdr_retriever* rt, const std::vector<uint32_t>& k,
+    {
+        size_t most[2] = {0, 0};
+        for (size_t t = 0; t < ntasks; ++t)
+            if (tasks[t].reconstruct) most[tasks[t].rt->r->dtype == MDR_F64 ? 1 : 0] += tasks[t].rt->r->levels.size();
+        for (size_t i = 0; i < nextra; ++i) most[extra[i].rt->r->dtype == MDR_F64 ? 1 : 0] += extra[i].k.size();
+        for (int d = 0; d < 2; ++d) rj[d].reserve(most[d]);
+    }
+    auto add_jobs = [&](const std::vector<const uint8_t*>& held, const mdr_retriever* rt, const std::vector<uint32_t>& k,
                         const std::vector<uint32_t>* kprev, void* const* out) {
         const mdr_refactored* r = rt->r;
         const uint32_t B = r->B, m = r->m;
@@ -203,7 +225,7 @@ mdr_status retrieve_many(mdr_context* ctx, RetrieveTask* tasks, size_t ntasks, h
             const LevelRec& LR = r->levels[l];
             if (LR.n == 0) continue;
             if (kprev && k[l] == (*kprev)[l]) continue;  // output already holds these planes
-            ReconJob job{};
+            ReconJob& job = rj[r->dtype == MDR_F64 ? 1 : 0].emplace_back();
             job.out = out[l];
             job.n = LR.n;
             job.nbd = LR.nbd;
@@ -211,25 +233,20 @@ mdr_status retrieve_many(mdr_context* ctx, RetrieveTask* tasks, size_t ntasks, h
             job.k = k[l];
             job.e = LR.e;
             job.vec = ((uintptr_t)job.out % 16) == 0 ? 1u : 0u;
-            if (job.k > 0) {
-                for (uint32_t row = 0; row <= B; ++row) {
-                    if (row > 0 && row - 1 >= job.k) break;
-                    const uint32_t slot = row == 0 ? 0 : 1 + ((row - 1) / m) * m;
-                    uint32_t r0, r1;
-                    slot_rows(slot, B, m, r0, r1);
-                    const uint8_t* src = nullptr;
-                    if (t < ntasks) src = fsrc[t][(size_t)l * kMaxRows + slot];
-                    if (!src) src = static_cast<const uint8_t*>(rt->dec[l][slot].p);
-                    if (!src) src = r->levels[l].units[slot].dev;  // direct copy: the payload is the plane rows
+            for (uint32_t i = 0; job.k > 0 && i < LR.units.count(); ++i) {
+                uint32_t r0, r1;
+                slot_rows(LR.units.slot(i), B, m, r0, r1);
+                if (r0 > job.k) break;
+                const uint8_t* src = held.empty() ? nullptr : held[(size_t)l * LR.units.count() + i];
+                if (!src) src = LR.units.unit(i).dev;  // direct copy: the payload is the plane rows
+                for (uint32_t row = r0; row < r1 && row <= job.k; ++row)
                     job.rows[row] = reinterpret_cast<const uint32_t*>(src) + (uint64_t)(row - r0) * LR.nbd;
-                }
             }
-            rj[r->dtype == MDR_F64 ? 1 : 0].push_back(job);
         }
     };
     for (size_t t = 0; t < ntasks; ++t)
         if (tasks[t].reconstruct)
-            add_jobs(t, tasks[t].rt, tasks[t].knew, tasks[t].all_levels ? nullptr : &tasks[t].rt->k, tasks[t].out);
+            add_jobs(decoded[t], tasks[t].rt, tasks[t].knew, tasks[t].all_levels ? nullptr : &tasks[t].rt->k, tasks[t].out);
     for (size_t i = 0; i < nextra; ++i) {
         size_t t = ntasks;
         for (size_t u = 0; u < ntasks; ++u)
@@ -237,7 +254,7 @@ mdr_status retrieve_many(mdr_context* ctx, RetrieveTask* tasks, size_t ntasks, h
         const std::vector<uint32_t>& held = t < ntasks ? tasks[t].knew : extra[i].rt->k;
         for (size_t l = 0; l < held.size(); ++l)
             if (extra[i].k[l] > held[l]) return fail(MDR_ERR_INVALID_ARG, "reconstruction beyond the planes held");
-        add_jobs(t, extra[i].rt, extra[i].k, extra[i].kprev, extra[i].out);
+        add_jobs(t < ntasks ? decoded[t] : extra[i].rt->dec, extra[i].rt, extra[i].k, extra[i].kprev, extra[i].out);
     }
 
     // descriptor: decode jobs, reconstruction jobs, workgroup maps
@@ -342,9 +359,10 @@ mdr_status retrieve_many(mdr_context* ctx, RetrieveTask* tasks, size_t ntasks, h
 
     // commit
     sync_on_fail.armed = false;
-    for (Fresh& f : fresh) tasks[f.task].rt->dec[f.level][f.slot] = std::move(f.buf);
     for (size_t t = 0; t < ntasks; ++t) {
         mdr_retriever* rt = tasks[t].rt;
+        rt->dec = std::move(decoded[t]);
+        if (block[t].p) rt->held.push_back(std::move(block[t]));
         rt->k = tasks[t].knew;
         rt->bytes_held += fetched[t];
         if (mdr_retrieve_info* info = tasks[t].info) {
