@@ -70,4 +70,37 @@ __device__ __forceinline__ void transpose32(uint32_t (&a)[32])
     }
 }
 
+// The same for 32 values of 16 bits, values p and p + 16 in the halves of a[p]:
+// afterwards bit r of a[c] is bit c of value r.
+__device__ __forceinline__ void transpose16(uint32_t (&a)[16])
+{
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+        const uint32_t x = a[k], y = a[k + 8];
+        a[k] = __builtin_amdgcn_perm(y, x, 0x06020400u);      // x0 y0 x2 y2
+        a[k + 8] = __builtin_amdgcn_perm(y, x, 0x07030501u);  // x1 y1 x3 y3
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        if (k & 4) continue;
+        const uint32_t x = a[k], y = a[k + 4];
+        a[k] = (x & 0x0F0F0F0Fu) | ((y << 4) & 0xF0F0F0F0u);
+        a[k + 4] = ((x >> 4) & 0x0F0F0F0Fu) | (y & 0xF0F0F0F0u);
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        if (k & 2) continue;
+        const uint32_t x = a[k], y = a[k + 2];
+        a[k] = (x & 0x33333333u) | ((y << 2) & 0xCCCCCCCCu);
+        a[k + 2] = ((x >> 2) & 0x33333333u) | (y & 0xCCCCCCCCu);
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        if (k & 1) continue;
+        const uint32_t x = a[k], y = a[k + 1];
+        a[k] = (x & 0x55555555u) | ((y << 1) & 0xAAAAAAAAu);
+        a[k + 1] = ((x >> 1) & 0x55555555u) | (y & 0xAAAAAAAAu);
+    }
+}
+
 }  // namespace mdr

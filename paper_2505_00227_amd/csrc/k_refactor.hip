@@ -234,6 +234,21 @@ __global__ __launch_bounds__(kStatsThreads) void k_stats(const StatsJob* __restr
 // and folded in with an LDS max; the others cannot change the result.  Cuts
 // with K_k < 1/2 take the direct per-block maximum; k = 0 is max |x|, known from
 // the statistics.  Stale maxima only add candidates, so the result is exact.
+//
+// f64 FAST takes the same test to the plane words from a workgroup's second tile
+// on: after the transpose a run of ones below a cut is an AND of plane words,
+// one operation for 32 values (with 16 more planes of fraction bits for the
+// lowest cuts), against 46 per value.  A word of flagged values comes out of
+// it; their keys are then taken from the values, loaded again while the rows go
+// out (a few a tile, and the values need not stay in registers: 128 of them
+// against 168).  Cuts with no bit below them so far are checked by one key, and
+// the cuts above them whose keys cannot rise while that holds are left out, so
+// data of few significant bits does not fall back to the per-value test.
+// 2^27 values: exponents over 100 binades 867 -> 810 us, uniform 1311 -> 707,
+// 10-bit values 2164 -> 629; 2^30 values of 32 slabs 5.36 -> 4.95 ms, of which
+// the loads and stores alone take 4.0 and the histograms most of the rest.  In
+// f32 the per-value test costs half as much and hides under the histograms: the
+// plane test changed 2^27 values by -1 to +5%, so it is not used there.
 // FAST: 32 planes of f32 or 64 planes of f64, in groups of 4 (every row, its
 // unit and its histogram offset known at compile time): rows go from registers
 // straight to memory, neighbours come by lane shuffle, runs are counted per
@@ -300,7 +315,21 @@ __device__ __forceinline__ void encode_body(const EncodeJob& job, const uint32_t
     uint32_t frac_max = 0;  // f32: bits of max fract(y) = the k = B key (nonnegative: bits order as values)
     uint64_t frac_max64 = 0;  // the same for f64
     T small = 0;
+    uint32_t per_value = 0;  // FAST: tiles to go before the plane test is tried again
 
+    // y < 1, the values below every cut, in terms of |x|
+    const T tiny_below = F64 ? (T)__builtin_amdgcn_ldexp(1.0, e - (int)B) : (T)__builtin_amdgcn_ldexpf(1.0f, e - (int)B);
+    uint32_t tiny_high;  // its high word
+    if constexpr (F64)
+        tiny_high = (uint32_t)((uint64_t)__double_as_longlong(tiny_below) >> 32);
+    else
+        tiny_high = __float_as_uint(tiny_below);
+    const auto fabs_t = [](T a) -> T {
+        if constexpr (F64)
+            return __builtin_fabs(a);
+        else
+            return __builtin_fabsf(a);
+    };
     const uint32_t t0 = wg * tpw;
     const uint32_t t1 = min(ntiles, t0 + tpw);
     const uint32_t last_blk = min(nbd, t1 * kTileBlocks) - 1;
@@ -356,6 +385,46 @@ __device__ __forceinline__ void encode_body(const EncodeJob& job, const uint32_t
         uint32_t sgn = 0;
         uint32_t lo[32];
         uint32_t hi[F64 ? 32 : 1];
+        if constexpr (FAST) {
+            uint32_t least = ~0u;  // of the high words of |x|: tells whether any value may lie below every cut
+#pragma unroll
+            for (int j = 31; j >= 0; --j) {
+                uint32_t h;
+                if constexpr (F64)
+                    h = (uint32_t)((uint64_t)__double_as_longlong(v[j]) >> 32);
+                else
+                    h = __float_as_uint(v[j]);
+                sgn = __builtin_amdgcn_alignbit(sgn, h, 31);
+                least = min(least, h & 0x7FFFFFFFu);
+            }
+            asm volatile("" : "+v"(sgn));  // here, or the raw values would live on
+            if (__ballot(least <= tiny_high)) {
+#pragma unroll
+                for (int j = 0; j < 32; ++j) {
+                    // mag = floor(y) = 0: |x| to `small`, the value to zero.  By
+                    // mask: two selects in a row on one condition take 23 cycles
+                    const T a = fabs_t(v[j]);
+                    uint32_t mask = a < tiny_below ? ~0u : 0u;
+                    asm volatile("" : "+v"(mask));
+                    if constexpr (F64) {
+                        const uint64_t b = (uint64_t)__double_as_longlong(a), mask2 = (uint64_t)mask << 32 | mask;
+                        small = __builtin_fmax(small, __longlong_as_double((long long)(b & mask2)));
+                        v[j] = __longlong_as_double((long long)(b & ~mask2));
+                    } else {
+                        const uint32_t b = __float_as_uint(a);
+                        small = __builtin_fmaxf(small, __uint_as_float(b & mask));
+                        v[j] = __uint_as_float(b & ~mask);
+                    }
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < 32; ++j) {
+                if constexpr (F64)
+                    v[j] = __builtin_amdgcn_ldexp(fabs_t(v[j]), (int)B - e);
+                else
+                    v[j] = __builtin_amdgcn_ldexpf(fabs_t(v[j]), (int)B - e);
+            }
+        } else
 #pragma unroll
         for (int j = 0; j < 32; ++j) {
             if constexpr (F64) {
@@ -383,7 +452,55 @@ __device__ __forceinline__ void encode_body(const EncodeJob& job, const uint32_t
         for (int j = 0; j < 32; ++j) asm volatile("" : "+v"(v[j]));
         asm volatile("" : "+v"(small));
         // ---- exact error keys, k = 0..B
-        if constexpr (F64) {
+        // f64 FAST: by plane words once the running maxima are high (see above)
+        constexpr bool PLANES = FAST && F64;
+        bool by_plane = false;
+        uint64_t free8 = 0, free12 = 0, free16 = 0;  // cuts (bit c) that need no run of 8, 12, 16 ones
+        if constexpr (PLANES) {
+            if (t > t0) {
+                uint32_t tl = 0;  // lane c: the leading ones of cut c's running maximum
+                const double M = __longlong_as_double((long long)s_key64[64 - lane]);
+                if (M >= 0.5) tl = __clz(~(uint32_t)(M * 0x1p32));
+                uint64_t s4 = __ballot(tl >= 4);
+                const uint64_t s8 = __ballot(tl >= 8);
+                // Cuts 0 .. z without a bit below them so far.  While that stays
+                // so, cut c's key has c - z bits: at all ones it cannot rise
+                const uint64_t none = __ballot(M == 0.0);
+                uint64_t done = none;
+                if (none) {
+                    const int z = 63 - __clzll((long long)none);
+                    double km = 0.0;
+#pragma unroll
+                    for (int j = 0; j < 32; ++j)
+                        km = __builtin_fmax(km, __builtin_amdgcn_fract(__builtin_amdgcn_ldexp(v[j], -z)));
+                    done = __ballot(km != 0.0) ? 0 : none | __ballot((int)lane > z && (int)tl >= (int)lane - z);
+                }
+                by_plane = __popcll(s4 | done) >= 56 && __popcll(s8 | done) >= 48 && per_value == 0;
+                per_value -= per_value ? 1u : 0u;
+                uint64_t direct = ~(s4 | done);
+                s4 &= ~done;
+                free8 = s4 & ~s8;
+                free12 = s4 & ~__ballot(tl >= 12);
+                free16 = s4 & ~__ballot(tl >= 16);
+                if (by_plane) {
+                    // the few cuts whose maximum is below 1 - 2^-4: directly, from
+                    // the highest: no bit below a cut, none below the lower ones
+                    while (direct) {
+                        const int c = 63 - __clzll((long long)direct);
+                        direct &= ~(1ull << c);
+                        double km = 0.0;
+#pragma unroll
+                        for (int j = 0; j < 32; ++j)
+                            km = __builtin_fmax(km, __builtin_amdgcn_fract(__builtin_amdgcn_ldexp(v[j], -c)));
+                        if (!__ballot(km != 0.0)) break;
+                        km = wave_max(km);
+                        if (lane == 0) atomicMax(&s_key64[64 - c], (unsigned long long)__double_as_longlong(km));
+                    }
+                }
+            }
+        }
+        if (by_plane) {
+        } else if constexpr (F64) {
             // The f32 pruning below on the 128-bit fixed point of y: words
             // X3:X2 = magnitude (hi[j]:lo[j]), X1 = the top 32 fraction bits.
             // Cut c (1..B-1) is bit 64+c-1; a tested run is at most 12 bits
@@ -396,8 +513,7 @@ __device__ __forceinline__ void encode_body(const EncodeJob& job, const uint32_t
                 double km = 0.0;
 #pragma unroll
                 for (int j = 0; j < 32; ++j) {
-                    const double key = __builtin_amdgcn_fract(__builtin_amdgcn_ldexp(v[j], -c));
-                    km = key > km ? key : km;
+                    km = __builtin_fmax(km, __builtin_amdgcn_fract(__builtin_amdgcn_ldexp(v[j], -c)));
                 }
                 atomicMax(&s_key64[B - c], (unsigned long long)__double_as_longlong(km));
                 __syncthreads();
@@ -430,7 +546,7 @@ __device__ __forceinline__ void encode_body(const EncodeJob& job, const uint32_t
                 for (int j = 0; j < 32; ++j) {
                     const double y = v[j];
                     const double f = __builtin_amdgcn_fract(y);
-                    frac_max64 = max(frac_max64, (uint64_t)__double_as_longlong(f));
+                    frac_max64 = (uint64_t)__double_as_longlong(__builtin_fmax(__longlong_as_double((long long)frac_max64), f));
                     asm volatile("" : "+v"(frac_max64));  // fold in now, not at the end
                     const double yh = __builtin_trunc(y * 0x1p-32);
                     const uint32_t X3 = (uint32_t)yh, X2 = (uint32_t)(y - yh * 0x1p32), X1 = (uint32_t)(f * 0x1p32);
@@ -463,33 +579,24 @@ __device__ __forceinline__ void encode_body(const EncodeJob& job, const uint32_t
                     }
                 }
             };
-            if (S12 == (B > 1 ? (1ull << (B - 1)) - 1ull : 0ull)) {
-                key_pass(std::true_type{});
+            if (!FAST && S12 == (B > 1 ? (1ull << (B - 1)) - 1ull : 0ull)) {
+                if constexpr (!FAST) key_pass(std::true_type{});
             } else {
                 key_pass(std::false_type{});
                 const uint64_t all = B > 1 ? (1ull << (B - 1)) - 1ull : 0ull;  // cuts 1 .. B-1
                 uint64_t weak = all & ~strong;
-                while (weak) {
-                    const int c = __ffsll((unsigned long long)weak);
-                    weak &= weak - 1;
+                while (weak) {  // from the highest: no bit below a cut, none below the lower ones
+                    const int c = 64 - __clzll((long long)weak);
+                    weak &= ~(1ull << (c - 1));
                     double km = 0.0;
 #pragma unroll
                     for (int j = 0; j < 32; ++j) {
-                        const double key = __builtin_amdgcn_fract(__builtin_amdgcn_ldexp(v[j], -c));
-                        km = key > km ? key : km;
+                        km = __builtin_fmax(km, __builtin_amdgcn_fract(__builtin_amdgcn_ldexp(v[j], -c)));
                     }
+                    if (!__ballot(km != 0.0)) break;
                     km = wave_max(km);
                     if (lane == 0) atomicMax(&s_key64[B - c], (unsigned long long)__double_as_longlong(km));
                 }
-            }
-            // mag = hi:lo (0 when tiny), converted afresh: reusing the key
-            // pass's conversions would keep 64 more registers alive through it
-#pragma unroll
-            for (int j = 0; j < 32; ++j) {
-                asm volatile("" : "+v"(v[j]));
-                const double yh = __builtin_trunc(v[j] * 0x1p-32);
-                hi[j] = (uint32_t)yh;
-                lo[j] = (uint32_t)(v[j] - yh * 0x1p32);
             }
         } else {
             // Cut c = B - k (k = 1..B-1) is bit c-1 of y; k = B is the fraction
@@ -552,31 +659,106 @@ __device__ __forceinline__ void encode_body(const EncodeJob& job, const uint32_t
             for (int j = 0; j < 32; ++j) one(v[j]);
             const uint32_t all = (1u << (B - 1)) - 1u;  // cuts 1 .. B-1
             uint32_t weak = all & ~strong;
-            while (weak) {
-                const int c = __ffs(weak);
-                weak &= weak - 1;
+            while (weak) {  // from the highest, as for f64
+                const int c = 32 - __clz(weak);
+                weak &= ~(1u << (c - 1));
                 float km = 0.0f;
 #pragma unroll
                 for (int j = 0; j < 32; ++j)
                     km = fmaxf(km, __builtin_amdgcn_fractf(__builtin_amdgcn_ldexpf(v[j], -c)));
+                if (!__ballot(km != 0.0f)) break;
                 km = wave_max(km);
                 if (lane == 0) atomicMax(&s_key32[B - c], __float_as_uint(km));
             }
         }
 
-        if constexpr (!F64) {
-            // mag = floor(y) (0 when tiny), converted afresh: reusing the key
-            // loop's conversions would keep 32 more registers alive through it
+        if constexpr (PLANES) {
+            // the maximum fraction (cut 0) too is in LDS after every tile
+            if (!by_plane) {
+                const uint64_t fm = wave_max(frac_max64);
+                if (lane == 0) atomicMax(&s_key64[64], (unsigned long long)fm);
+            }
+        }
+        // ---- mag = hi:lo (0 when tiny), converted afresh: reusing the key
+        // pass's conversions would keep 32 or 64 more registers alive through it.
+        // PLANES: and the top 16 bits of the fractions of values p and p + 16 in fr[p]
+        uint32_t fr[PLANES ? 16 : 1];
 #pragma unroll
-            for (int j = 0; j < 32; ++j) {
+        for (int p = 0; p < 16; ++p) {
+            uint32_t f2[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int j = p + 16 * h;
                 asm volatile("" : "+v"(v[j]));
-                lo[j] = (uint32_t)v[j];
+                if constexpr (F64) {
+                    const double yh = __builtin_trunc(v[j] * 0x1p-32), yl = v[j] - yh * 0x1p32;
+                    hi[j] = (uint32_t)yh;
+                    lo[j] = (uint32_t)yl;
+                    if constexpr (PLANES) f2[h] = (uint32_t)(__builtin_amdgcn_fract(yl) * 0x1p16);
+                } else {
+                    lo[j] = (uint32_t)v[j];
+                }
+            }
+            if constexpr (PLANES) {
+                fr[p] = f2[0] | (f2[1] << 16);
+                asm volatile("" : "+v"(fr[p]));  // here, or the values would live through the transposes
             }
         }
         // ---- bit transpose: lo[c] (and hi[c]) become the plane words of bit c (32 + c);
         // row 0 = sign, row r >= 1 = plane r-1 = bit B-r
         transpose32(lo);
         if constexpr (F64) transpose32(hi);
+        uint32_t raised = 0;  // PLANES: this block's values that may raise a key maximum
+        T raise_x = 0;        // the first of them
+        if constexpr (PLANES) {
+            if (by_plane) {
+                transpose16(fr);  // fr[i]: bit i - 16
+                // X(i): the plane word of bit i - 16; cut c's key begins with bit c - 1
+                auto X = [&](int i) -> uint32_t { return i < 16 ? fr[i & 15] : i < 48 ? lo[(i - 16) & 31] : hi[(i - 48) & 31]; };
+                uint32_t r2[79], r4[79];  // runs of 2 and 4 ones down from a bit
+#pragma unroll
+                for (int i = 1; i < 79; ++i) {
+                    r2[i] = X(i) & X(i - 1);
+                    if (i >= 3) r4[i] = r2[i] & r2[i - 2];
+                    if (i >= 15) {
+                        const int c = i - 15;
+                        auto ones_if = [&](uint64_t cuts) -> uint32_t {  // all ones if it holds cut c
+                            return 0u - ((uint32_t)(cuts >> (c & 32)) >> (c & 31) & 1u);
+                        };
+                        const uint32_t f8 = ones_if(free8), f12 = ones_if(free12), f16 = ones_if(free16);
+                        raised |= r4[i] & (r4[i - 4] | f8) & (r4[i - 8] | f12) & (r4[i - 12] | f16);
+                        asm volatile("" : "+v"(raised));
+                    }
+                }
+                // its value again, in flight while the rows go out
+                if (raised) raise_x = x[(uint64_t)blk * 32 + (__ffs(raised) - 1)];
+            }
+        }
+        // the flagged values' keys, a value of every lane at a time
+        auto raise_keys = [&]() {
+            // many flagged values: the per-value test is faster, for some tiles
+            if (__ballot(__popc(raised) > 8)) per_value = 7;
+            while (raised) {
+                const double y = __builtin_amdgcn_ldexp(__builtin_fabs(raise_x), (int)B - e);
+                raised &= raised - 1;
+                if (raised) raise_x = x[(uint64_t)blk * 32 + (__ffs(raised) - 1)];
+                // the same runs along this value's bits: Y.F its integer and 32 fraction bits
+                const double f = __builtin_amdgcn_fract(y), yh = __builtin_trunc(y * 0x1p-32);
+                const uint64_t Y = (uint64_t)(uint32_t)yh << 32 | (uint32_t)(y - yh * 0x1p32);
+                const uint64_t F = (uint64_t)(uint32_t)(f * 0x1p32) << 32;
+                atomicMax(&s_key64[64], (unsigned long long)__double_as_longlong(f));
+                const uint64_t F2 = F & (F << 1), F4 = F2 & (F2 << 2);
+                const uint64_t Y2 = Y & (Y << 1 | F >> 63), Y4 = Y2 & (Y2 << 2 | F2 >> 62);
+                uint64_t cand = Y4 & ((Y4 << 4 | F4 >> 60) | free8 >> 1) & ((Y4 << 8 | F4 >> 56) | free12 >> 1) &
+                                ((Y4 << 12 | F4 >> 52) | free16 >> 1) & (~0ull >> 1);  // bit c - 1: cut c
+                while (cand) {
+                    const int c = __ffsll((unsigned long long)cand);
+                    cand &= cand - 1;
+                    const double key = __builtin_amdgcn_fract(__builtin_amdgcn_ldexp(y, -c));
+                    atomicMax(&s_key64[64 - c], (unsigned long long)__double_as_longlong(key));
+                }
+            }
+        };
         if constexpr (FAST && F64) {
             // row r (0..64) is sgn, hi[32 - r] (r <= 32) or lo[64 - r]; unit
             // of row r is (r + 3) / 4.  Lanes l and l + 32 hold the halves of
@@ -663,6 +845,7 @@ __device__ __forceinline__ void encode_body(const EncodeJob& job, const uint32_t
                 rows_out(std::true_type{});
             else
                 rows_out(std::false_type{});
+            raise_keys();
 #undef MDR_ROW64
             continue;
         } else if constexpr (FAST) {
@@ -851,7 +1034,7 @@ __device__ __forceinline__ void encode_body(const EncodeJob& job, const uint32_t
     if (tid < kMaxRows && s_trans[tid]) atomicAdd(&job.trans[copy * kMaxRows + tid], s_trans[tid]);
 }
 
-// f32 fits five waves per SIMD (96 registers) with LDS to spare; f64 two
+// f32 fits five waves per SIMD (96 registers) with LDS to spare; general f64 two
 // (256 registers, without spills: left alone the compiler takes 259 and one)
 template <bool VEC, bool FAST>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5, 8))) void k_encode_f32(
@@ -869,10 +1052,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))
     encode_body<true, VEC, FAST>(job, blockIdx.x - job.wg_base);
 }
 
-// the f64 fast path: two waves per SIMD (up to 256 registers); at four (128
-// registers) it spilled and ran 12% slower, at three (168) within 4% of two
+// the f64 fast path: four waves per SIMD (128 registers; a few scalars spill),
+// as many as its LDS allows; within 2% of three (140 registers) from 2^28 values
+// on, 4 to 8% faster on 2^23 and 2^24
 template <bool VEC>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 8))) void k_encode_f64_fast(
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))) void k_encode_f64_fast(
     const EncodeJob* __restrict__ jobs, const uint32_t* __restrict__ wg_job)
 {
     const EncodeJob& job = jobs[wg_job[blockIdx.x]];
