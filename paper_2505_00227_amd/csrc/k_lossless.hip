@@ -800,11 +800,28 @@ __device__ __forceinline__ void build_first_code_table(const uint8_t* __restrict
 // bits << 26.  COUNT (the G-lane decoder): behind it the counting table, all
 // whole codes of the window (up to lmax) and the first one's length: count |
 // bits << 4 | first << 8, 16 bits an entry.
+// The first launch to need the descriptor can also bring it: with `words`, the
+// jobs are read from pinned host memory and the workgroups past them copy the
+// descriptor from src to dst (a launch of its own took 4 us).
 template <bool COUNT>
-__global__ __launch_bounds__(kTabThreads) void k_huf_tables(const DecodeJob* __restrict__ jobs)
+__global__ __launch_bounds__(kTabThreads) void k_huf_tables(const DecodeJob* jobs, uint32_t njobs, const uint64_t* src,
+                                                            uint64_t* __restrict__ dst, uint64_t words)
 {
-    const DecodeJob& job = jobs[blockIdx.x];
-    const uint32_t lmax = job.lmax, nent = 1u << lmax, mask = nent - 1, tid = threadIdx.x;
+    const uint32_t tid = threadIdx.x;
+    if (blockIdx.x >= njobs) {
+        const uint64_t stride = (uint64_t)(gridDim.x - njobs) * kTabThreads;
+        for (uint64_t i = (uint64_t)(blockIdx.x - njobs) * kTabThreads + tid; i < words; i += stride)
+            dst[i] = __hip_atomic_load(src + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        return;
+    }
+    __shared__ DecodeJob s_job;
+    static_assert(sizeof(DecodeJob) % 8 == 0 && sizeof(DecodeJob) / 8 <= 64, "a job is a few 64-bit words");
+    if (tid < sizeof(DecodeJob) / 8)
+        reinterpret_cast<uint64_t*>(&s_job)[tid] = __hip_atomic_load(
+            reinterpret_cast<const uint64_t*>(jobs + blockIdx.x) + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __syncthreads();
+    const DecodeJob job = s_job;
+    const uint32_t lmax = job.lmax, nent = 1u << lmax, mask = nent - 1;
     __shared__ uint16_t s_one[1 << kLutBitsMax];
     __shared__ uint32_t s_three[COUNT ? 1 << kLutBitsMax : 1];
     __shared__ uint32_t s_wcnt[4][kLutBitsMax + 1];
@@ -1284,16 +1301,29 @@ hipError_t launch_lossless_batch(const LosslessArgs& a, const LosslessArgs* a_de
 }
 
 hipError_t launch_huf_decode_batch(const DecodeJob* jobs, uint32_t njobs, const uint32_t* wg_job,
-                                   uint32_t grid, uint32_t lanes, uint32_t threads, uint32_t cap_chunk, hipStream_t s)
+                                   uint32_t grid, uint32_t lanes, uint32_t threads, uint32_t cap_chunk, hipStream_t s,
+                                   const DescCopy& desc)
 {
     if (grid == 0 || njobs == 0) return hipSuccess;
     const dim3 P(grid), T(threads);
+    const uint64_t words = desc.bytes / 8;
+    const DecodeJob* first = jobs;  // where the tables' launch reads the jobs
+    void* src = nullptr;
+    if (words) {
+        const hipError_t e = hipHostGetDevicePointer(&src, const_cast<void*>(desc.host), 0);
+        if (e != hipSuccess) return e;
+        const uint64_t at = reinterpret_cast<const uint8_t*>(jobs) - static_cast<const uint8_t*>(desc.dev);
+        first = reinterpret_cast<const DecodeJob*>(static_cast<const uint8_t*>(src) + at);
+    }
+    const dim3 PT(njobs + (words ? blocks_for(words, kTabThreads, 256) : 0));
+    const uint64_t* from = static_cast<const uint64_t*>(src);
+    uint64_t* to = static_cast<uint64_t*>(desc.dev);
     if (lanes == 1) {
-        hipLaunchKernelGGL(k_huf_tables<false>, dim3(njobs), dim3(kTabThreads), 0, s, jobs);
+        hipLaunchKernelGGL(k_huf_tables<false>, PT, dim3(kTabThreads), 0, s, first, njobs, from, to, words);
         hipLaunchKernelGGL(k_huf_decode, P, T, 0, s, jobs, wg_job);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_huf_tables<true>, dim3(njobs), dim3(kTabThreads), 0, s, jobs);
+    hipLaunchKernelGGL(k_huf_tables<true>, PT, dim3(kTabThreads), 0, s, first, njobs, from, to, words);
     const size_t shmem = split_lds_bytes(threads / lanes, cap_chunk);
     if (threads == kSplitThreadsMax && lanes == 16) {
         hipLaunchKernelGGL((k_huf_decode_split<16, kSplitThreadsMax>), P, T, shmem, s, jobs, wg_job, cap_chunk);

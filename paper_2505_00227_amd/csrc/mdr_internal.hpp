@@ -187,9 +187,16 @@ constexpr uint64_t kHufTableBytes = 6ull << kLutBitsMax;  // 2^lmax 32-bit and a
 // lanes per chunk: 1 or 4..64; threads: of a workgroup, which takes threads / lanes
 // chunks (kThreads, or what huf_decode_threads gives); cap_chunk: the largest chunk of the jobs.  A first
 // launch builds every job's decode table into its table slot, which the
-// decoding workgroups copy
+// decoding workgroups copy; with desc.bytes it also brings the descriptor that
+// holds the jobs and the map (as launch_copy_in, dev to be 8-byte aligned)
+struct DescCopy {
+    const void* host = nullptr;  // pinned
+    void* dev = nullptr;
+    uint64_t bytes = 0;          // a multiple of 8; 0: it is there already
+};
 hipError_t launch_huf_decode_batch(const DecodeJob* jobs, uint32_t njobs, const uint32_t* wg_job,
-                                   uint32_t grid, uint32_t lanes, uint32_t threads, uint32_t cap_chunk, hipStream_t s);
+                                   uint32_t grid, uint32_t lanes, uint32_t threads, uint32_t cap_chunk, hipStream_t s,
+                                   const DescCopy& desc);
 // lanes per chunk for a launch of total_chunks chunks, the largest chunk
 // max_chunk symbols: want = 0 picks by the symbol count (16 symbols a lane
 // below kHufOneLaneSymbols); 1 stays 1; 4..64 is raised where a workgroup's

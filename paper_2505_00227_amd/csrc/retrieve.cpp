@@ -324,7 +324,12 @@ mdr_status retrieve_many(mdr_context* ctx, RetrieveTask* tasks, size_t ntasks, h
         put(o_rle, rle.data(), sizeof(RleJob) * rle.size());
         put(o_mrg, map_rg.data(), 4 * map_rg.size());
         put(o_mre, map_re.data(), 4 * map_re.size());
-        MDR_HIP(launch_copy_in(dv, h, o, s));
+        // the descriptor goes with the first launch where that is the decode tables'
+        DescCopy desc;
+        if (!map_dec.empty() && rle.empty())
+            desc = {h, dv, o};
+        else
+            MDR_HIP(launch_copy_in(dv, h, o, s));
         if (!rle.empty()) {
             StageTimer tm(ctx, MDR_STAGE_RLE_DECODE, s);
             MDR_HIP(launch_rle_decode_batch(reinterpret_cast<const RleJob*>(dv + o_rle),
@@ -338,7 +343,7 @@ mdr_status retrieve_many(mdr_context* ctx, RetrieveTask* tasks, size_t ntasks, h
             StageTimer tm(ctx, MDR_STAGE_HUF_DECODE, s);
             MDR_HIP(launch_huf_decode_batch(reinterpret_cast<const DecodeJob*>(dv + o_dec), (uint32_t)dec.size(),
                                             reinterpret_cast<const uint32_t*>(dv + o_md),
-                                            (uint32_t)map_dec.size(), lanes, threads, dec_chunk_max, s));
+                                            (uint32_t)map_dec.size(), lanes, threads, dec_chunk_max, s, desc));
         }
         for (int d = 0; d < 2; ++d) {
             if (map_r[d].empty()) continue;
