@@ -186,10 +186,11 @@ mdr_status make_layout(const mdr_context* ctx, const VarLevels* vars, uint32_t n
         uint32_t tk[5];
         tune_key(dtype, B, L.m, total_values, L.J, tk);
         L.shape = effective_shape(ctx, tk);
-        // the selection builds each unit's code on one lane: with many units,
-        // smaller workgroups let more of them build at once (the 4896 units
-        // of 32 slabs of the 1024^3 field: 0.19 ms at 256 threads, 0.25 at
-        // 512), with few the larger ones' faster histogram and rank steps win
+        // a wavefront builds each unit's code while the others wait: with many
+        // units, smaller workgroups let more of them build at once (4896 units:
+        // 46 us at 256 threads, 63 at 512; 11520: 80 and 137), with few the
+        // larger ones' faster histogram and rank steps win (81 units: 36 us at
+        // 512, 39 at 256; 9: 28 and 30)
         if (L.shape.select_threads == 0) L.shape.select_threads = L.U >= kSelectManyUnits ? 256u : 512u;
     }
 
@@ -462,7 +463,6 @@ mdr_status enqueue_pass(mdr_context* ctx, const Layout& L, const mdr_codec_param
     return MDR_OK;
 }
 
-// handles from the metadata read back after the pass
 // x * 2^n rounded once, as std::ldexp: a product with the power of two when
 // that power is a double (-1074 <= n <= 1023; the product of x and an exact
 // power of two is the exact value rounded), ldexp otherwise.  A level's error
@@ -477,6 +477,7 @@ static inline double scale2(double x, int n)
     return x * p;
 }
 
+// handles from the metadata read back after the pass
 mdr_status assemble(mdr_context* ctx, const Layout& L, mdr_dtype dtype, const mdr_codec_params& prm,
                     const uint8_t* meta, const std::shared_ptr<PoolBuf>& rows,
                     const std::shared_ptr<PoolBuf>& pay, uint32_t nvars, mdr_refactored** outs)
