@@ -121,8 +121,9 @@ mdr_status mdr_context_timing(mdr_context* ctx, double* ms, uint64_t* launches, 
 /* Launch shape of the refactor pass (the autotuner's knobs; results do not
  * depend on them, bit for bit):
  *   enc_target_wg   encoder workgroups a pass aims for (tiles of 256 blocks are
- *                   split evenly among them; passes of few values take tiles of
- *                   32 blocks and at most 1024 workgroups); 64..65536, default 2304;
+ *                   split evenly among them; small and mid-size passes take at
+ *                   most 1024, those of few values in tiles of 32 blocks);
+ *                   64..65536, default 2304;
  *   stats_wg_values values per statistics workgroup (at most 256 workgroups
  *                   per level); 1024..2^24, default 65536.
  * Zero leaves a knob unchanged.  `graphs` (0/1, -1 = unchanged): whether
