@@ -130,7 +130,7 @@ struct LosslessArgs {
     uint32_t* huf_lo;       // [U] words before the unit's first chunk
     uint32_t* huf_hi;       // [U] words up to the end of its last chunk (within the share only)
     uint32_t* rle_lo;       // [U] runs before the unit's first tile
-    uint32_t* tile_first;   // [tiles] word of the first run start in each tile
+    uint32_t* tile_first;   // [tiles] first run start in each tile, from the tile's first word
     uint64_t* pay_off;      // [U] payload offset in the arena (DC: unused)
     uint64_t* unit_bytes;   // [U] stream bytes (from the selection; a Huffman stream's words are added)
     uint32_t* counts;       // [0] chunks, [1] tiles, [2] arena overflow, [3] pad, [4..5] arena bytes
