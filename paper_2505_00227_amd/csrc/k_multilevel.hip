@@ -382,6 +382,10 @@ __device__ __forceinline__ uint32_t xcd_block(uint32_t id, uint32_t blocks)
     return id / kMlXcds < per && at < blocks ? at : ~0u;
 }
 
+// this workgroup's number in its launch, and how many there are (see ml_grid)
+__device__ __forceinline__ uint32_t ml_id() { return blockIdx.y * gridDim.x + blockIdx.x; }
+__device__ __forceinline__ uint32_t ml_launched() { return gridDim.y * gridDim.x; }
+
 template <typename T, bool DEC, int J, bool FUSED = false>
 __device__ __forceinline__ void ml_block(const MlStep& st, T* coeffs, T* field, uint32_t n1, uint32_t n2, uint32_t blk)
 {
@@ -419,10 +423,10 @@ template <typename T>
 __global__ __launch_bounds__(kMl) void k_ml_decompose(const MlSteps S, T* field, T* coeffs, uint32_t n0, uint32_t n1,
                                                       uint32_t n2, uint32_t nsteps)
 {
-    const uint32_t blk = blockIdx.x;
+    const uint32_t blk = ml_id();
     if (blk >= S.blk_raw) {
         ml_raw<T, true>(coeffs, field, n0, n1, n2, nsteps, (uint64_t)(blk - S.blk_raw) * kMl + threadIdx.x,
-                        (uint64_t)(gridDim.x - S.blk_raw) * kMl);
+                        (uint64_t)(ml_launched() - S.blk_raw) * kMl);
         return;
     }
     uint32_t i = 0;
@@ -440,7 +444,7 @@ __global__ __launch_bounds__(kMl) void k_ml_decompose(const MlSteps S, T* field,
 template <typename T, int J, bool FUSED>
 __global__ __launch_bounds__(kMl) void k_ml_recompose(const MlStep st, T* coeffs, T* field, uint32_t n1, uint32_t n2)
 {
-    ml_block<T, false, J, FUSED>(st, coeffs, field, n1, n2, blockIdx.x);
+    ml_block<T, false, J, FUSED>(st, coeffs, field, n1, n2, ml_id());
 }
 
 template <typename T>
@@ -536,6 +540,18 @@ bool plan_step(uint32_t n0, uint32_t n1, uint32_t n2, uint32_t j, uint64_t coef,
 // workgroups a step is launched with: whole rounds over the XCDs
 uint32_t launch_blocks(const MlStep& st) { return (st.blocks + kMlXcds - 1) / kMlXcds * kMlXcds; }
 
+// The grid of a launch of `blocks` workgroups.  x may hold 2^32 - 1 threads
+// (more are taken modulo 2^32, without an error), so from 2^24 workgroups on
+// they go in rows of 2^20; what the last row has too many finds no work.
+// Fields of about 3 x 10^10 values get there whose rows fill little more than
+// half of their wavefronts.
+dim3 ml_grid(uint32_t blocks)
+{
+    constexpr uint32_t kRow = 1u << 20;  // whole rounds over the XCDs
+    if ((uint64_t)blocks * kMl <= 0xFFFFFFFFull) return dim3(blocks);
+    return dim3(kRow, (blocks + kRow - 1) / kRow);
+}
+
 uint32_t raw_blocks(uint64_t nodes)
 {
     const uint64_t b = (nodes + kMl - 1) / kMl;
@@ -557,7 +573,7 @@ hipError_t ml_decompose(T* field, uint32_t n0, uint32_t n1, uint32_t n2, uint32_
     }
     S.blk_raw = blk;
     blk += raw_blocks(axis_nodes(n0, nsteps) * axis_nodes(n1, nsteps) * axis_nodes(n2, nsteps));
-    hipLaunchKernelGGL(k_ml_decompose<T>, dim3(blk), dim3(kMl), 0, s, S, field, coeffs, n0, n1, n2, nsteps);
+    hipLaunchKernelGGL(k_ml_decompose<T>, ml_grid(blk), dim3(kMl), 0, s, S, field, coeffs, n0, n1, n2, nsteps);
     return hipGetLastError();
 }
 
@@ -585,7 +601,7 @@ hipError_t ml_recompose(T* coeffs, uint32_t n0, uint32_t n1, uint32_t n2, uint32
         if (fused) ++l;
         if (!plan_step(n0, n1, n2, fused ? 0 : j, off.off[l], st, fused)) continue;
         st.coef1 = fused ? off.off[l - 1] : 0;
-        const dim3 g(launch_blocks(st));
+        const dim3 g = ml_grid(launch_blocks(st));
         if (fused)
             hipLaunchKernelGGL((k_ml_recompose<T, 0, true>), g, dim3(kMl), 0, s, st, coeffs, field, n1, n2);
         else if (j == 0)
