@@ -120,10 +120,11 @@ mdr_status mdr_context_timing(mdr_context* ctx, double* ms, uint64_t* launches, 
 
 /* Launch shape of the refactor pass (the autotuner's knobs; results do not
  * depend on them, bit for bit):
- *   enc_target_wg   encoder workgroups a pass aims for (tiles of 256 blocks are
- *                   split evenly among them; small and mid-size passes take at
- *                   most 1024, those of few values in tiles of 32 blocks);
- *                   64..65536, default 2304;
+ *   enc_target_wg   encoder workgroups a pass aims for (tiles of 256 blocks, in
+ *                   passes of few values of 32, are split evenly among them);
+ *                   64..65536, default 2304, which stands for the library's own
+ *                   choice: 512 or 1024 in small and mid-size passes, 2304 in
+ *                   others.  Any other value is taken as it is;
  *   stats_wg_values values per statistics workgroup (at most 256 workgroups
  *                   per level); 1024..2^24, default 65536.
  * Zero leaves a knob unchanged.  `graphs` (0/1, -1 = unchanged): whether

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "mdr.h"
+#include "encode_rule.hpp"
 #include "mdr_internal.hpp"
 
 struct mdr_context;
@@ -308,7 +309,7 @@ struct mdr_context {
     mdr::DevBuf ws;    // refactor workspace (statistics, histograms, codebooks)
     mdr::DevBuf qacc;  // V_total estimate accumulator
     // batch refactor: launch shape and captured graphs
-    uint32_t enc_target_wg = 2304;   // encoder workgroups a batch aims for
+    uint32_t enc_target_wg = mdr::kEncTargetDefault;  // encoder workgroups a batch aims for
     uint32_t stats_wg_values = 65536;  // values per statistics workgroup (at most kStatsMaxWg per level)
     uint32_t select_threads = 0;       // selection workgroup size (0: by the pass's unit count)
     // launch-shape tuning table, its file, and tune-on-first-use

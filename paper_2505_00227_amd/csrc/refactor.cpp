@@ -96,28 +96,6 @@ uint64_t unit_cap(uint64_t S, const mdr_codec_params& prm, uint32_t G)
     return align256(cap);
 }
 
-// Passes of at most this many values take the small passes' encoder (eight
-// lanes a block, tiles of 32 blocks).  Its advantage is latency (2^18 values: 11
-// against 28 us in f32, 18 against 44 in f64; 2^21 f32 values 22 against 30,
-// 2^20 f64 ones 30 against 44), its cost instructions a value (2^22: 33 against
-// 35, a unit per plane 46 against 46; f64 78 against 57).
-constexpr uint64_t small_pass_values(bool f64) { return f64 ? 1u << 20 : 1u << 21; }
-// and aims for this many workgroups at most: each ends by adding its
-// histograms into the level's, a KiB a unit (2^21 f32 values in 9 units: 22 us
-// at 1024, 25 at 512; in 33 units: 43 and 33; 2^20 f64 in 17: 36 and 30)
-constexpr uint32_t small_target_wg(uint32_t nunits) { return nunits <= 12 ? 1024 : 512; }
-
-// A pass of up to this many tiles in the register fast paths aims for one round
-// of workgroups, as many as are resident at once (four a CU in f64): a
-// workgroup's first tile and its end cost more than the others, and a second
-// round of as few tiles is not full (2^25 f64 values, 4096 tiles: 233 us with 1024
-// workgroups, 251 with 2048; 12288 tiles: 535 and 562; 2^24 f32 values: 66 and 71,
-// 4096 tiles: 106 and 110).  Past it more workgroups spread the load better
-// (2^28 f64 values: 1330 us with 1024, 1288 to 1310 with 2048 and 2185; 6144 f32
-// tiles: 154 and 151).
-constexpr uint32_t kOneRoundWg = 1024;
-constexpr uint64_t one_round_tiles(bool f64) { return f64 ? 12288 : 4096; }
-
 // A level's totals are kept in this many copies, a power of two, one per
 // kWgPerCopy of its encoder workgroups: device atomics on one cache line take
 // turns, about 40 ns each (2^20 f32 values, 512 workgroups: 22.5 us with one
@@ -212,11 +190,7 @@ mdr_status make_layout(const mdr_context* ctx, const VarLevels* vars, uint32_t n
         total_tiles = 0;
         for (JobPlan& jp : L.jobs) total_tiles += jp.ntiles = (uint32_t)ceil_div(jp.nbd, kSmallTileBlocks);
     }
-    uint32_t target = L.shape.enc_target_wg;
-    if (L.small)
-        target = std::min(target, small_target_wg(L.nunits));
-    else if (L.m == 4 && L.B == (L.f64 ? 64u : 32u) && total_tiles <= one_round_tiles(L.f64))
-        target = std::min(target, kOneRoundWg);
+    const uint32_t target = encode_target_wg(L.shape.enc_target_wg, L.f64, B, L.m, L.nunits, L.small, total_tiles);
     const uint64_t tpw_all = std::max<uint64_t>(1, ceil_div(total_tiles, std::max<uint32_t>(1, target)));
     uint64_t hist = 0, recs = 0, trans = 0, keys = 0;
     for (JobPlan& jp : L.jobs) {
