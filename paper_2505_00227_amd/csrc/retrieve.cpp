@@ -86,6 +86,13 @@ DescSlot* acquire_slot(mdr_context* ctx, uint64_t bytes, uint64_t dev_bytes, mdr
     return &d;
 }
 
+// Units of a power of two of bytes would all start at one place of the memory
+// channels' interleave, where a reconstruction reads every plane's row at once:
+// large units of a block are moved apart.  2^24 f64 values, 17 units of 8 MiB:
+// reconstruction 56 us in a block without gaps, 53 in a block of memory each, 46
+// with these (48 with 256 bytes, 45 with 69888); the whole retrieval 158, 153, 142.
+constexpr uint64_t kUnitShift = 17 * 256, kShiftedUnit = 65536;
+
 // a coded unit entering a plan: its place in the retriever's table and in the
 // block that holds what this call decodes for it
 struct Fresh {
@@ -167,7 +174,7 @@ mdr_status retrieve_many(mdr_context* ctx, RetrieveTask* tasks, size_t ntasks, h
                 ++groups[t];
                 if (ur.method == MDR_DC || LR.n == 0) continue;
                 fresh.push_back({l, i, need});
-                need += align256(std::max<uint64_t>(ur.S, 4));
+                need += align256(std::max<uint64_t>(ur.S, 4)) + (ur.S >= kShiftedUnit ? kUnitShift : 0);
             }
         }
         decoded[t] = rt->dec;
