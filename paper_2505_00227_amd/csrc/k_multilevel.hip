@@ -53,7 +53,7 @@ __host__ __device__ __forceinline__ uint64_t axis_nodes(uint32_t n, uint32_t j)
 // One step's work: its grid, level offset and wavefront units.
 struct MlStep {
     uint64_t coef;     // offset of the step's level in the coefficient buffer
-    uint64_t coef1;    // FUSED: and of step 1's
+    uint64_t coef1;    // and of the level its coarse nodes come from, if not the field
     uint32_t m0, m1, m2;
     uint32_t j;
     uint32_t segs;     // wavefronts along a row
@@ -229,13 +229,19 @@ __device__ __forceinline__ void stride2_rows(const T* __restrict__ lv1, const T*
 }
 
 // One wavefront unit of a step.  DEC: field -> coefficients; else the other
-// way, writing the nodes of the step (j = 0: whole rows).  FUSED (j = 0 of a
-// recomposition): step 1 too, with its level at lv1.
-template <typename T, bool DEC, int J, bool FUSED>
+// way, writing the nodes of the step (j = 0: whole rows).  FROM (j = 0 of a
+// recomposition), where the coarse nodes come from and what else is written:
+// kField, the field, which holds them; kStep1, step 1 is done too, its level at
+// coef1; kRaw, level 0 at coef1, the only step (with a copy of level 0 into every
+// second value of the field first, partial lines that were read back as such,
+// 4000 x 4000 f64 values took 80 us, now 54: a copy of them takes 41).
+enum { kField, kStep1, kRaw };
+template <typename T, bool DEC, int J, int FROM>
 __device__ __forceinline__ void ml_unit(const MlStep& st, T* __restrict__ coeffs, T* field, uint32_t n1, uint32_t n2,
                                         uint32_t unit)
 {
 #pragma clang fp contract(off)
+    constexpr bool FUSED = FROM == kStep1, RAW = FROM == kRaw;
     const uint32_t lane = threadIdx.x & 63;
     const uint32_t j = J < 2 ? (uint32_t)J : st.j;
     const uint32_t seg = unit % st.segs, yz = unit / st.segs;
@@ -261,6 +267,7 @@ __device__ __forceinline__ void ml_unit(const MlStep& st, T* __restrict__ coeffs
     T u01[4], u10[4], u11[4];          // DEC: the cell's other rows; else their coefficients
     T k0[2] = {T(0), T(0)};            // else: the first row's odd coefficients
     const uint32_t e1 = (m1 + 1) >> 1, e2 = (m2 + 1) >> 1;
+    auto raw = [&](uint32_t a, uint32_t b) { return coeffs + st.coef1 + ((uint64_t)a * e1 + b) * e2; };
     // coefficients of the cell's rows: position of each row's first in the level
     const uint64_t pl0 = (uint64_t)2 * A * m1 * m2 - (uint64_t)A * e1 * e2;
     const uint64_t pl1 = (uint64_t)(2 * A + 1) * m1 * m2 - (uint64_t)(A + 1) * e1 * e2;
@@ -274,7 +281,21 @@ __device__ __forceinline__ void ml_unit(const MlStep& st, T* __restrict__ coeffs
     const bool edge = !FUSED && lane == 63 && x + 4 < m2;  // the next node is in the next wavefront's segment
     const bool has2 = x + 2 < m2, has4 = x + 4 < m2;
     if (live) {
-        if (!FUSED) {
+        if (RAW) {
+#pragma unroll
+            for (uint32_t da = 0; da < 2; ++da)
+#pragma unroll
+                for (uint32_t db = 0; db < 2; ++db) {
+                    if ((da && !z2) || (db && !y2)) continue;
+                    const T* c = raw(A + da, B + db) + x / 2;
+                    T w[2] = {T(0), T(0)};
+                    if (has2)
+                        load_vec<T, 2>(c, w);
+                    else
+                        w[0] = *gmem(c);
+                    e[da][db][0] = w[0], e[da][db][2] = w[1];
+                }
+        } else if (!FUSED) {
             load_nodes<T, J>(c00, x, cnt, n2, j, e00);
             if (y2) load_nodes<T, J>(row(2 * A, 2 * B + 2), x, cnt, n2, j, e01);
             if (z2) load_nodes<T, J>(row(2 * A + 2, 2 * B), x, cnt, n2, j, e10);
@@ -293,7 +314,13 @@ __device__ __forceinline__ void ml_unit(const MlStep& st, T* __restrict__ coeffs
             if (zo) load_nodes<T, 0, true>(r10 - x, x, cnt, m2, 0, u10);
             if (yo && zo) load_nodes<T, 0, true>(r11 - x, x, cnt, m2, 0, u11);
         }
-        if (edge) {
+        if (RAW && edge) {
+            const uint32_t at = x / 2 + 2;
+            nx00 = gmem(raw(A, B))[at];
+            if (y2) nx01 = gmem(raw(A, B + 1))[at];
+            if (z2) nx10 = gmem(raw(A + 1, B))[at];
+            if (y2 && z2) nx11 = gmem(raw(A + 1, B + 1))[at];
+        } else if (edge) {
             const uint64_t at = (uint64_t)(x + 4) << j;
             nx00 = gmem(c00)[at];
             if (y2) nx01 = gmem(row(2 * A, 2 * B + 2))[at];
@@ -346,13 +373,13 @@ __device__ __forceinline__ void ml_unit(const MlStep& st, T* __restrict__ coeffs
         T* const f00 = row(2 * A, 2 * B);
         T o[4] = {e00[0], k0[0] + p00[1], e00[2], k0[1] + p00[3]};
         if (J == 0 && cnt == 4) {
-            // the even values again, unchanged: whole lines, where single odd
+            // the even values too (kField: again, unchanged): whole lines, where single odd
             // values would be partial ones (readers of the row see the same bits)
             store_vec<T, 4>(f00 + x, o);
         } else {
-            // (FUSED: the even nodes may be step 1's)
+            // (not from the field: the even nodes are new to it)
 #pragma unroll
-            for (uint32_t k = FUSED ? 0 : 1; k < 4; k += FUSED ? 1 : 2)
+            for (uint32_t k = FROM != kField ? 0 : 1; k < 4; k += FROM != kField ? 1 : 2)
                 if (k < cnt) gmem(f00)[(uint64_t)(x + k) << j] = o[k];
         }
         auto put = [&](T* r, const T (&c)[4], const T (&q)[4]) {
@@ -386,14 +413,14 @@ __device__ __forceinline__ uint32_t xcd_block(uint32_t id, uint32_t blocks)
 __device__ __forceinline__ uint32_t ml_id() { return blockIdx.y * gridDim.x + blockIdx.x; }
 __device__ __forceinline__ uint32_t ml_launched() { return gridDim.y * gridDim.x; }
 
-template <typename T, bool DEC, int J, bool FUSED = false>
+template <typename T, bool DEC, int J, int FROM = kField>
 __device__ __forceinline__ void ml_block(const MlStep& st, T* coeffs, T* field, uint32_t n1, uint32_t n2, uint32_t blk)
 {
     const uint32_t at = xcd_block(blk, st.blocks);
     const uint32_t unit = at * (kMl / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t cells0 = (st.m0 + 1) >> 1;
     if (at == ~0u || unit >= cells0 * st.groups * st.segs) return;
-    ml_unit<T, DEC, J, FUSED>(st, coeffs, field, n1, n2, unit);
+    ml_unit<T, DEC, J, FROM>(st, coeffs, field, n1, n2, unit);
 }
 
 // The decomposition: every step and the raw coarsest grid in one launch.
@@ -440,11 +467,11 @@ __global__ __launch_bounds__(kMl) void k_ml_decompose(const MlSteps S, T* field,
         ml_block<T, true, 2>(st, coeffs, field, n1, n2, blk - st.blk0);
 }
 
-// One step of the recomposition (FUSED: steps 1 and 0).
-template <typename T, int J, bool FUSED>
+// One step of the recomposition (FROM: see ml_unit).
+template <typename T, int J, int FROM>
 __global__ __launch_bounds__(kMl) void k_ml_recompose(const MlStep st, T* coeffs, T* field, uint32_t n1, uint32_t n2)
 {
-    ml_block<T, false, J, FUSED>(st, coeffs, field, n1, n2, ml_id());
+    ml_block<T, false, J, FROM>(st, coeffs, field, n1, n2, ml_id());
 }
 
 template <typename T>
@@ -585,6 +612,14 @@ hipError_t ml_recompose(T* coeffs, uint32_t n0, uint32_t n1, uint32_t n2, uint32
     // the raw grid and as many steps as fit one workgroup's LDS; a grid too
     // large for it is copied by a launch of its own
     uint32_t l = 0;
+    if (nsteps == 1 && nodes(0) > kMlSmallBytes / sizeof(T)) {
+        MlStep st;
+        plan_step(n0, n1, n2, 0, off.off[1], st);
+        st.coef1 = off.off[0];
+        hipLaunchKernelGGL((k_ml_recompose<T, 0, kRaw>), ml_grid(launch_blocks(st)), dim3(kMl), 0, s, st, coeffs, field,
+                           n1, n2);
+        return hipGetLastError();
+    }
     if (nodes(nsteps) <= kMlSmallBytes / sizeof(T)) {
         while (l < nsteps && nodes(nsteps - l - 1) <= kMlSmallBytes / sizeof(T)) ++l;
         hipLaunchKernelGGL(k_ml_recompose_small<T>, dim3(1), dim3(kMlSmallThreads), 0, s, off, coeffs, field, n0, n1, n2,
@@ -603,11 +638,11 @@ hipError_t ml_recompose(T* coeffs, uint32_t n0, uint32_t n1, uint32_t n2, uint32
         st.coef1 = fused ? off.off[l - 1] : 0;
         const dim3 g = ml_grid(launch_blocks(st));
         if (fused)
-            hipLaunchKernelGGL((k_ml_recompose<T, 0, true>), g, dim3(kMl), 0, s, st, coeffs, field, n1, n2);
+            hipLaunchKernelGGL((k_ml_recompose<T, 0, kStep1>), g, dim3(kMl), 0, s, st, coeffs, field, n1, n2);
         else if (j == 0)
-            hipLaunchKernelGGL((k_ml_recompose<T, 0, false>), g, dim3(kMl), 0, s, st, coeffs, field, n1, n2);
+            hipLaunchKernelGGL((k_ml_recompose<T, 0, kField>), g, dim3(kMl), 0, s, st, coeffs, field, n1, n2);
         else
-            hipLaunchKernelGGL((k_ml_recompose<T, 2, false>), g, dim3(kMl), 0, s, st, coeffs, field, n1, n2);
+            hipLaunchKernelGGL((k_ml_recompose<T, 2, kField>), g, dim3(kMl), 0, s, st, coeffs, field, n1, n2);
         e = hipGetLastError();
     }
     return e;
