@@ -1433,73 +1433,57 @@ __device__ __forceinline__ uint32_t huf_lengths(CodeScratch<W>& cs, const uint32
         for (int h = 0; h < 4; ++h)
             if (d[h]) atomicAdd(&cs.bits[d[h]], 1u);
         wave_fence();
-        if (most >= 64) {
-            // deeper than a wavefront has lanes (counts past 2^40): one lane
-            if (lane == 0) {
-                for (uint32_t i = most; i > lmax; --i) {
-                    while (cs.bits[i] > 0) {
-                        uint32_t j = i - 2;
-                        while (cs.bits[j] == 0) --j;
-                        cs.bits[i] -= 2;
-                        cs.bits[i - 1] += 1;
-                        cs.bits[j + 1] += 2;
-                        cs.bits[j] -= 1;
-                    }
-                }
-            }
-            wave_fence();
-        }
-        // lane l holds the count of length l
+        // Lane l holds the count of length l.  Lengths stay below 64: a tree of
+        // depth d takes weights of Fibonacci(d + 2) in all, and a unit has at
+        // most 2^35 bytes (64 rows of 2^27 words): d <= 50.
         int b = (int)cs.bits[lane];
-        if (most < 64) {
-            // Per step, two codes of the deepest length i: one moves up to i - 1,
-            // the other to a code split at the longest shorter length j <= i - 2
-            // that has one (j -> two of j + 1).  Splitting one code of length j
-            // all the way down to i - 1, as consecutive steps do, takes
-            // T = 2^(i-1-j) - 1 steps and leaves 2^(i-1-j) codes there, so
-            // codes are split whole while the steps last; of the next one the
-            // steps left split a path (at each length one code stays, or is
-            // split whole).  (One step at a time was up to 50 us of a large
-            // skewed unit's selection.)
-            const int l = (int)lane;
-            for (int i = (int)most; i > (int)lmax; --i) {
-                int left = __builtin_amdgcn_readlane(b, i) >> 1;  // steps at this length, at most 127
-                b += (l == i ? -2 * left : 0) + (l == i - 1 ? left : 0);
-                while (left > 0) {
-                    const unsigned long long nzm = __ballot(b != 0) & ((1ull << (i - 1)) - 1);
-                    if (!nzm) break;  // cannot happen for a full tree
-                    const int j = 63 - __clzll((long long)nzm);
-                    int d = i - 1 - j, T = (1 << min(d, 16)) - 1;  // 16 levels stand for more: T > left
-                    const int bj = __builtin_amdgcn_readlane(b, j);
-                    // left / T, exact for these small numbers
-                    int q = (int)((float)left * __builtin_amdgcn_rcpf((float)T) + 1e-3f);
-                    q = min(__builtin_amdgcn_readfirstlane(q), bj);
-                    left -= q * T;
-                    int deep = q << min(d, 16);       // codes left at i - 1
-                    unsigned long long stay = 0;      // lengths that keep one code of the split path
-                    if (q < bj && left > 0) {
-                        ++q;                          // the partly split code
-                        for (int c = j; left > 0;) {
-                            --left;                   // split: two of length c + 1
-                            ++c;
-                            --d;
-                            T = (1 << min(d, 16)) - 1;
-                            if (left >= T) {          // one of them whole (T = 0 at c = i - 1)
-                                left -= T;
-                                deep += 1 << d;
-                            } else {
-                                stay |= 1ull << c;
-                            }
-                            if (left == 0) {          // the other stays as it is
-                                if (d == 0)
-                                    ++deep;
-                                else
-                                    b += l == c ? 1 : 0;
-                            }
+        // Per step, two codes of the deepest length i: one moves up to i - 1,
+        // the other to a code split at the longest shorter length j <= i - 2
+        // that has one (j -> two of j + 1).  Splitting one code of length j
+        // all the way down to i - 1, as consecutive steps do, takes
+        // T = 2^(i-1-j) - 1 steps and leaves 2^(i-1-j) codes there, so
+        // codes are split whole while the steps last; of the next one the
+        // steps left split a path (at each length one code stays, or is
+        // split whole).  (One step at a time was up to 50 us of a large
+        // skewed unit's selection.)
+        const int l = (int)lane;
+        for (int i = (int)most; i > (int)lmax; --i) {
+            int left = __builtin_amdgcn_readlane(b, i) >> 1;  // steps at this length, at most 127
+            b += (l == i ? -2 * left : 0) + (l == i - 1 ? left : 0);
+            while (left > 0) {
+                const unsigned long long nzm = __ballot(b != 0) & ((1ull << (i - 1)) - 1);
+                if (!nzm) break;  // cannot happen for a full tree
+                const int j = 63 - __clzll((long long)nzm);
+                int d = i - 1 - j, T = (1 << min(d, 16)) - 1;  // 16 levels stand for more: T > left
+                const int bj = __builtin_amdgcn_readlane(b, j);
+                // left / T, exact for these small numbers
+                int q = (int)((float)left * __builtin_amdgcn_rcpf((float)T) + 1e-3f);
+                q = min(__builtin_amdgcn_readfirstlane(q), bj);
+                left -= q * T;
+                int deep = q << min(d, 16);       // codes left at i - 1
+                unsigned long long stay = 0;      // lengths that keep one code of the split path
+                if (q < bj && left > 0) {
+                    ++q;                          // the partly split code
+                    for (int c = j; left > 0;) {
+                        --left;                   // split: two of length c + 1
+                        ++c;
+                        --d;
+                        T = (1 << min(d, 16)) - 1;
+                        if (left >= T) {          // one of them whole (T = 0 at c = i - 1)
+                            left -= T;
+                            deep += 1 << d;
+                        } else {
+                            stay |= 1ull << c;
+                        }
+                        if (left == 0) {          // the other stays as it is
+                            if (d == 0)
+                                ++deep;
+                            else
+                                b += l == c ? 1 : 0;
                         }
                     }
-                    b += (l == j ? -q : 0) + (l == i - 1 ? deep : 0) + (int)((stay >> l) & 1);
                 }
+                b += (l == j ? -q : 0) + (l == i - 1 ? deep : 0) + (int)((stay >> l) & 1);
             }
         }
         // hand the lengths out again, the heaviest leaf (last) the shortest
