@@ -5,9 +5,9 @@
 namespace mdr {
 
 // Passes of at most this many values take the small passes' encoder (eight
-// lanes a block, tiles of 32 blocks).  Its advantage is latency (2^18 values: 11
-// against 28 us in f32, 18 against 44 in f64; 2^21 f32 values 22 against 30,
-// 2^20 f64 ones 30 against 44), its cost instructions a value (2^22: 33 against
+// lanes a block, tiles of 32 blocks).  Its advantage is latency (2^18 values: 9
+// against 26 us in f32, 16 against 41 in f64; 2^21 f32 values 19 against 28,
+// 2^20 f64 ones 28 against 42), its cost instructions a value (2^22: 33 against
 // 35, a unit per plane 46 against 46; f64 78 against 57).
 constexpr uint64_t small_pass_values(bool f64) { return f64 ? 1u << 20 : 1u << 21; }
 // and aims for this many workgroups at most: each ends by adding its

@@ -1066,8 +1066,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 8))
 // ------------------------------------------------------------------ bitplane encoder, small passes
 // The same results for a pass of few values, where the kernels above leave most
 // of the chip idle and a thread's 32 values, one after the other through 20 to
-// 70 KB of unrolled code fetched cold, are the pass's latency (33 us for 32768
-// f32 values, 74 us for 2^21 f64 ones).  Eight lanes share a block of 32 values,
+// 70 KB of unrolled code fetched cold, are the pass's latency (32768 values:
+// 25 us in f32, 40 in f64, against 7 and 13 here).  Eight lanes share a block of 32 values,
 // four values each (a wavefront reads 1 or 2 KiB in one go); the bit transpose
 // exchanges words between the eight lanes in three rounds and finishes in
 // registers; the tile's rows go through LDS and are stored, counted and compared

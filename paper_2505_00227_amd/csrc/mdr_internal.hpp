@@ -207,7 +207,8 @@ uint32_t huf_decode_lanes(uint32_t want, uint64_t total_chunks, uint32_t max_chu
 // LDS a workgroup, so a launch that fills the chip shares them among 16
 // wavefronts (full occupancy), a smaller one spreads over more CUs with four
 // (20480 chunks: 38 us with 16 against 34 with four; 40960: 38 against 44;
-// 163840: 72 against 100)
+// 163840: 72 against 100).  Larger chunks take more lanes each and keep four
+// wavefronts: sharing was measured for chunks of 256 symbols alone
 constexpr uint32_t kSplitThreadsMax = 1024;
 constexpr uint64_t kHufWideChunks = 32768;
 uint32_t huf_decode_threads(uint32_t lanes, uint64_t total_chunks, uint32_t max_chunk);
