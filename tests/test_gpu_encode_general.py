@@ -5,7 +5,9 @@ values.  Here 64 workgroups take several such tiles each, from levels that start
 on and off a 16-byte boundary and end inside a tile, so the state that a
 workgroup carries from tile to tile counts: the general encoders (a group size
 other than 4, or fewer planes than the type has) of both types, which the sizes
-below those limits do not reach, and the register fast path of float32."""
+below those limits do not reach, and the register fast path of float32 (which
+tests every value for its error keys: plane words are tested for them in the
+fast path of float64 alone)."""
 import numpy as np
 import pytest
 
